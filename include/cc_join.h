@@ -426,7 +426,11 @@ CC_API cc_status cc_sort_affinity(int32_t n_viewers, const int64_t *key_offsets,
  *                  of 8,192 polls so that every wave exits; a wait that reached it (not
  *                  expected) would leave the call's output undefined, every output row still a
  *                  copy of one of the call's input rows (memory-safe).
- *   CC_SORT_AUTO   CC_SORT_RADIX from CC_SORT_RADIX_MIN_RECORDS records on, else CC_SORT_MERGE.
+ *   CC_SORT_AUTO   one launch where the lists are short enough for it (their number times the
+ *                  longest's length, or its estimate where max_keys is 0, decides): every
+ *                  workgroup finds and sorts one part of a viewer in key order, or, in the smallest
+ *                  calls, counts its records' places by comparison. Otherwise CC_SORT_RADIX from
+ *                  CC_SORT_RADIX_MIN_RECORDS records on, else CC_SORT_MERGE.
  *   key_bits       0, or an upper bound on the bit length of (largest key - smallest key) over
  *                  the call (at most 64): the radix method then launches only the passes such a
  *                  span needs (ceil(key_bits / 9), e.g. 3 for author ids below 2^27), where it

@@ -1,0 +1,902 @@
+// Alg. 1 Step 1 in one launch (Connected Content Retriever §3.1): the affinity-record sort for calls
+// whose lists are not very long. A launch that depends on the one before costs 3 to 5 us here
+// however small it is, and the merge method takes 4 to 10 of them; both methods below need one.
+// 64-byte rows, 24-bit ids: one viewer of 5,000 records 46.9 -> 8.3 us (ranks by comparison), 64
+// viewers of 100 to 30,000 records 106 -> 40 us (partition; 49 MB, 1.2 TB/s: the parts of the
+// longest viewers set the time, through their steps 2 and 3).
+//
+// The partition method needs no plan, no histogram over the call and no pass over global memory
+// that a later launch waits for. A viewer of n records is cut into G parts of about `part` records
+// in key order, one workgroup each, and every workgroup finds its part by itself:
+//   1. sample: the same pseudo-random positions of the viewer's input in every workgroup (one
+//      per stratum of n / S records), put in (key, position) order; its records of rank g S / G
+//      and (g + 1) S / G bound part g. No two records are equal in that order, so repeated keys
+//      split like any others.
+//   2. select: the workgroup reads every key of the viewer (8 n bytes, from L2 after the first
+//      part's read), counts the records below its part, which is where its output starts, and
+//      keeps the records of its part in LDS, in input order.
+//   3. sort: a stable least-significant-digit radix sort of the part in LDS (digits of at most 8
+//      bits over the span of the part's own keys; equal keys keep their input order).
+//   4. emit: keys and feature rows to the part's contiguous output.
+// What bounds a part is the length of its dependent chain (about 3 us of sample, 1 us per 4,096
+// keys selected, 2 us per digit, 3 to 5 us of rows), so a part is as short as the redundant key
+// reads allow. 512 threads and kCap = 4096 leave two workgroups per CU: 1,024 threads were 30%
+// slower from 64 x 5,000 records on (one workgroup per CU), and no faster below.
+//
+// A part that the sample judged wrong by more than kCap / part (or that malformed offsets made
+// so) does not fit in LDS: its records are then sorted by the same digit passes in chunks,
+// through the two element arrays of the workspace, by the one workgroup. Slower, never wrong. The
+// sample has kPerPart records per part: a part of more than kCap / kPartLarge = 3.2 times its
+// share is a 2e-6 event in key orders that know nothing of the sample.
+#include "join_internal.h"
+#include "sort_device.h"
+
+namespace ccj {
+namespace {
+
+constexpr int kPartThreads = 512;
+constexpr int kPartWaves = kPartThreads / 64;
+constexpr int kEpt = 8;                        // records per thread of a part in LDS
+constexpr int kCap = kEpt * kPartThreads;      // records a part sorts in LDS (4096)
+constexpr int kBits = 8;                       // widest digit
+constexpr int kRadix = 1 << kBits;
+constexpr int kSampleMin = 64;
+constexpr int kPerPart = 10;                   // sample records per part
+constexpr int kSampleCount = 256;              // samples up to this size are ranked by counting
+static_assert(kPartUnboundedTotal < kPartMaxRecords &&
+                  kPartMaxWork <= (kPartMaxRecords - 1) * (kPartMaxRecords - 1),
+              "every viewer of a call that the automatic choice sends here can be sorted");
+
+struct PartShared {
+    uint64_t key[kCap];              // key - smallest key (select: the key itself)
+    uint32_t pos[kCap];              // position in the viewer
+    uint16_t cnt[kPartWaves][kRadix];    // per wavefront: running count, then the first sorted index
+                                     // of the wavefront's records of that digit value
+    uint32_t start[kRadix];          // first sorted index of each digit value
+    uint32_t adj[kRadix];            // big_part: a chunk's sorted index to the part's
+    uint32_t run[2][kPartWaves];         // select: records of the part per wavefront (two turns)
+    uint32_t below[kPartWaves];          // ... and records below it
+    int64_t lo[kPartWaves], hi[kPartWaves];  // key range per wavefront
+    int64_t bound_key[2];
+    uint32_t bound_pos[2];
+};
+
+// Element of the chunked passes through the workspace.
+struct Elem {
+    uint64_t key;
+    uint64_t pos;
+};
+
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// threadIdx.x, opaque to the compiler: what is derived from it stays local to a step, where it
+// would otherwise be kept in registers from one step of the kernel to the next.
+__device__ __forceinline__ int thread_index() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// The wavefront's index in the workgroup, as a scalar.
+__device__ __forceinline__ int wave_index() {
+    return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+}
+
+__device__ __forceinline__ int lanes_below(uint64_t mask) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// x of the lane that DPP control CTRL names (rows masked out and lanes without a source get x).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int64_t dpp64(int64_t x) {
+    const int lo = (int)(uint32_t)x, hi = (int)(uint32_t)((uint64_t)x >> 32);
+    const int a = __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xF, false);
+    const int b = __builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xF, false);
+    return (int64_t)(((uint64_t)(uint32_t)b << 32) | (uint32_t)a);
+}
+
+// DPP steps of a wavefront reduction or scan: shifts by 1, 2, 4 and 8 lanes within rows of 16,
+// then lane 15 of a row to the next row, then lane 31 to the upper half. Lane 63 ends with all.
+constexpr int kShr1 = 0x111, kShr2 = 0x112, kShr4 = 0x114, kShr8 = 0x118;
+constexpr int kBcast15 = 0x142, kBcast31 = 0x143;
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void range_step(int64_t &lo, int64_t &hi) {
+    lo = min(lo, dpp64<CTRL, ROWS>(lo));
+    hi = max(hi, dpp64<CTRL, ROWS>(hi));
+}
+
+// Smallest lo and largest hi over the workgroup. Has one barrier.
+__device__ __forceinline__ void key_range(PartShared &sh, int64_t &lo, int64_t &hi) {
+    const int lane = thread_index() & 63, w = wave_index();
+    range_step<kShr1, 0xF>(lo, hi);
+    range_step<kShr2, 0xF>(lo, hi);
+    range_step<kShr4, 0xF>(lo, hi);
+    range_step<kShr8, 0xF>(lo, hi);
+    range_step<kBcast15, 0xA>(lo, hi);
+    range_step<kBcast31, 0xC>(lo, hi);
+    if (lane == 63) {
+        sh.lo[w] = lo;
+        sh.hi[w] = hi;
+    }
+    lds_sync();
+    lo = sh.lo[0];
+    hi = sh.hi[0];
+#pragma unroll
+    for (int k = 1; k < kPartWaves; ++k) {
+        lo = min(lo, sh.lo[k]);
+        hi = max(hi, sh.hi[k]);
+    }
+}
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t sum_step(uint32_t x) {
+    return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+}
+
+// Inclusive prefix sum over the wavefront.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
+    x = sum_step<kShr1, 0xF>(x);
+    x = sum_step<kShr2, 0xF>(x);
+    x = sum_step<kShr4, 0xF>(x);
+    x = sum_step<kShr8, 0xF>(x);
+    x = sum_step<kBcast15, 0xA>(x);
+    return sum_step<kBcast31, 0xC>(x);
+}
+
+// The digits of a span of kbits bits: passes of D bits.
+struct Digits {
+    int passes, D;
+    uint32_t mask;
+};
+
+__device__ __forceinline__ Digits digits_of(uint64_t span) {
+    const int kbits = span ? 64 - __clzll(span) : 0;
+    const int passes = (kbits + kBits - 1) / kBits;
+    const int D = passes ? (kbits + passes - 1) / passes : 0;
+    return Digits{passes, D, (1u << D) - 1};
+}
+
+// Ranks R rounds of 64 records per wavefront by digit: rd[m] = (records of the same digit before
+// this one in the wavefront) << 8 | digit, and the wavefront's digit counts in sh.cnt[w]. The
+// lanes that share a digit are found with one ballot per digit bit.
+template <int E>
+__device__ __forceinline__ void rank_rounds(PartShared &sh, const uint64_t (&key)[E], int R,
+                                            int first, int n, int shift, uint32_t mask,
+                                            uint32_t (&rd)[E]) {
+    const int lane = thread_index() & 63, w = wave_index();
+    __builtin_memset(&sh.cnt[w][lane * (kRadix / 64)], 0, kRadix / 64 * sizeof(uint16_t));
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+        if (m < R) {                                     // uniform
+            // The lanes of a round read what lanes of earlier rounds wrote: the wavefront's LDS
+            // accesses complete in order, the fence keeps the compiler to that order.
+            wave_lds_order();
+            const bool valid = first + m * 64 + lane < n;
+            const uint32_t d = (uint32_t)(key[m] >> shift) & mask;
+            const uint64_t all = __ballot(valid);
+            uint32_t plo = (uint32_t)all, phi = (uint32_t)(all >> 32);
+#pragma unroll
+            for (int b = 0; b < kBits; ++b) {
+                const uint32_t s = (uint32_t)((int32_t)(d << (31 - b)) >> 31);   // bit b, 0 or ~0
+                const uint64_t bal = __ballot(s != 0);
+                plo &= ~((uint32_t)bal ^ s);
+                phi &= ~((uint32_t)(bal >> 32) ^ s);
+            }
+            const uint64_t peers = (uint64_t)plo | ((uint64_t)phi << 32);
+            const int before = lanes_below(peers);
+            const uint32_t c = sh.cnt[w][d];
+            wave_lds_order();
+            if (valid && before == 0)
+                sh.cnt[w][d] = (uint16_t)(c + (uint32_t)__popcll(peers));
+            // Pinned, so that no mask or partial count stays alive until the scatter.
+            uint32_t x = ((c + (uint32_t)before) << 8) | d;
+            asm volatile("" : "+v"(x));
+            rd[m] = x;
+        }
+    }
+}
+
+// Between two barriers after rank_rounds: the wavefronts' counts become the first sorted index of
+// each wavefront's records of each digit value, and sh.start that of each digit value. Wavefront
+// 0 does it alone, four digit values per lane as 16-bit fields of one word (no field exceeds
+// kCap): one barrier and one round of LDS reads less than a scan over all threads.
+__device__ __forceinline__ void digit_offsets(PartShared &sh) {
+    if (wave_index() != 0)
+        return;
+    const int lane = thread_index() & 63;
+    uint64_t c[kPartWaves];
+#pragma unroll
+    for (int k = 0; k < kPartWaves; ++k)
+        __builtin_memcpy(&c[k], &sh.cnt[k][lane * 4], 8);
+    uint64_t tot = 0;
+#pragma unroll
+    for (int k = 0; k < kPartWaves; ++k)
+        tot += c[k];
+    const uint32_t t0 = (uint32_t)tot & 0xFFFFu, t1 = t0 + ((uint32_t)tot >> 16);
+    const uint32_t t2 = t1 + ((uint32_t)(tot >> 32) & 0xFFFFu), t3 = t2 + (uint32_t)(tot >> 48);
+    const uint32_t s0 = wave_scan(t3) - t3, s1 = s0 + t0, s2 = s0 + t1, s3 = s0 + t2;
+    uint64_t at = (uint64_t)(s0 | (s1 << 16)) | ((uint64_t)(s2 | (s3 << 16)) << 32);
+    sh.start[lane * 4] = s0;
+    sh.start[lane * 4 + 1] = s1;
+    sh.start[lane * 4 + 2] = s2;
+    sh.start[lane * 4 + 3] = s3;
+#pragma unroll
+    for (int k = 0; k < kPartWaves; ++k) {
+        __builtin_memcpy(&sh.cnt[k][lane * 4], &at, 8);
+        at += c[k];
+    }
+}
+static_assert(kRadix == 4 * 64, "four digit values per lane");
+
+// Records first + m * 64 + lane of a tile of n, m < R: the order (wavefront, round, lane).
+struct Rounds {
+    int n, R, first;
+    __device__ explicit Rounds(int n_) : n(n_), R((n_ + kPartThreads - 1) / kPartThreads) {
+        first = wave_index() * R * 64;
+    }
+    __device__ int at(int m) const { return first + m * 64 + (thread_index() & 63); }
+};
+
+// Sorts n <= kCap records stably by key: key and pos hold them in the order of Rounds (records
+// past n repeat the last one). Leaves the sorted offsets from the smallest key (returned) and
+// positions in sh.key / sh.pos, with a barrier behind them. Called with a barrier behind the last
+// use of sh.
+__device__ __forceinline__ int64_t sort_lds(PartShared &sh, const Rounds &rs,
+                                            uint64_t (&key)[kEpt], uint32_t (&pos)[kEpt]) {
+    int64_t lo = INT64_MAX, hi = INT64_MIN;
+#pragma unroll
+    for (int m = 0; m < kEpt; ++m) {
+        if (m < rs.R) {                                  // uniform
+            lo = min(lo, (int64_t)key[m]);
+            hi = max(hi, (int64_t)key[m]);
+        }
+    }
+    key_range(sh, lo, hi);
+    const Digits dg = digits_of((uint64_t)hi - (uint64_t)lo);
+#pragma unroll
+    for (int m = 0; m < kEpt; ++m) {
+        if (m < rs.R)
+            key[m] -= (uint64_t)lo;
+    }
+    const int w = wave_index();
+    // Equal keys (no digit to sort by) take one pass of one value, which leaves them in order.
+    for (int p = 0;; ++p) {
+        uint32_t rd[kEpt];
+        rank_rounds(sh, key, rs.R, rs.first, rs.n, p * dg.D, dg.mask, rd);
+        lds_sync();
+        digit_offsets(sh);
+        lds_sync();
+#pragma unroll
+        for (int m = 0; m < kEpt; ++m) {
+            if (m < rs.R && rs.at(m) < rs.n) {
+                const uint32_t to = sh.cnt[w][rd[m] & 0xFFu] + (rd[m] >> 8);
+                sh.key[to] = key[m];
+                sh.pos[to] = pos[m];
+            }
+        }
+        lds_sync();
+        if (p + 1 >= dg.passes)
+            return lo;
+#pragma unroll
+        for (int m = 0; m < kEpt; ++m) {
+            if (m < rs.R) {
+                const int i = min(rs.at(m), rs.n - 1);
+                key[m] = sh.key[i];
+                pos[m] = sh.pos[i];
+            }
+        }
+    }
+}
+
+// Part g of G of the viewer with records [kb, kb + n).
+struct Part {
+    int64_t kb;
+    uint32_t n;
+    uint32_t g, G;
+};
+
+// A viewer's sample: S records, record i anywhere in the i-th stratum (Knuth's multiplicative
+// hash of i), so that no regular pattern of the input falls in step with it.
+struct Sample {
+    uint32_t S, step;                                    // stratum width, 12 fractional bits
+    __device__ explicit Sample(const Part &pt) {
+        S = pt.G > kCap / kPerPart ? kCap : max((uint32_t)kSampleMin, pt.G * kPerPart);
+        S = min(S, pt.n);                                // n > part: at least a record per part
+        step = (pt.n << 12) / S;
+    }
+    __device__ uint32_t pos(uint32_t i) const {
+        const uint32_t a = (i * step) >> 12, b = ((i + 1) * step) >> 12;
+        return a + __umulhi(i * 2654435761u, b - a);
+    }
+};
+static_assert(kPartMaxRecords <= (int64_t)1 << 20 && kCap <= 1 << 12, "i * step fits 32 bits");
+
+// Bound `side` of part g (0: at or above it, 1: below it) is the sample record of this rank; the
+// first and the last part have none on their outer side.
+__device__ __forceinline__ uint32_t bound_rank(const Part &pt, uint32_t side, uint32_t S) {
+    return min((pt.g + side) * S / pt.G, S - 1);
+}
+
+__device__ __forceinline__ void open_bounds(PartShared &sh, const Part &pt) {
+    if (thread_index() == 0) {
+        // Below, and above, every record (positions are below 2^32 - 1).
+        if (pt.g == 0) {
+            sh.bound_key[0] = INT64_MIN;
+            sh.bound_pos[0] = 0;
+        }
+        if (pt.g + 1 == pt.G) {
+            sh.bound_key[1] = INT64_MAX;
+            sh.bound_pos[1] = ~0u;
+        }
+    }
+}
+
+// Bounds from a sample of at most kSampleCount records, whose ranks are counted: thread (h, i)
+// compares record i with share h of the sample. Positions grow with the sample index, so equal
+// keys order by index. Ends with a barrier.
+__device__ __forceinline__ void count_bounds(PartShared &sh, const int64_t *__restrict__ keys,
+                                             const Part &pt, const Sample &sm) {
+    constexpr int kShares = kPartThreads / kSampleCount;
+    const int tid = thread_index(), i = tid & (kSampleCount - 1), h = tid / kSampleCount;
+    const int S = (int)sm.S;
+    const uint32_t p = sm.pos(min(i, S - 1));
+    const int64_t x = keys[pt.kb + p];
+    if (h == 0)
+        sh.key[i] = (uint64_t)x;                         // records past S repeat the last one
+    lds_sync();
+    const int share = (S + kShares - 1) / kShares, j0 = h * share, j1 = min(S, j0 + share);
+    uint32_t rank = 0;
+    if ((wave_index() & (kSampleCount / 64 - 1)) * 64 < S) { // uniform per wavefront
+#pragma unroll 8
+        for (int j = j0; j < j1; ++j) {
+            const int64_t y = (int64_t)sh.key[j];
+            rank += (y < x || (y == x && j < i)) ? 1 : 0;
+        }
+    }
+    sh.pos[tid] = rank;
+    open_bounds(sh, pt);
+    lds_sync();
+    if (h == 0 && i < S) {
+#pragma unroll
+        for (int q = 1; q < kShares; ++q)
+            rank += sh.pos[q * kSampleCount + i];
+        if (pt.g > 0 && rank == bound_rank(pt, 0, S)) {
+            sh.bound_key[0] = x;
+            sh.bound_pos[0] = p;
+        }
+        if (pt.g + 1 < pt.G && rank == bound_rank(pt, 1, S)) {
+            sh.bound_key[1] = x;
+            sh.bound_pos[1] = p;
+        }
+    }
+    lds_sync();
+}
+
+// Bounds from the sorted sample. Ends with a barrier.
+__device__ __forceinline__ void pick_bounds(PartShared &sh, const Part &pt, uint32_t S,
+                                            int64_t kmin) {
+    const int tid = thread_index();
+    if (tid < 2 && (tid == 0 ? pt.g > 0 : pt.g + 1 < pt.G)) {
+        const uint32_t r = bound_rank(pt, tid, S);
+        sh.bound_key[tid] = (int64_t)(sh.key[r] + (uint64_t)kmin);
+        sh.bound_pos[tid] = sh.pos[r];
+    }
+    open_bounds(sh, pt);
+    lds_sync();
+}
+
+// (key, position) bounds: records at or above (k0, p0) and below (k1, p1).
+struct Bounds {
+    int64_t k0, k1;
+    uint32_t p0, p1;
+};
+
+constexpr int kScan = 8;                       // rounds of 64 keys read together
+constexpr uint32_t kTurn = kScan * kPartThreads;   // keys of the viewer per turn of the workgroup
+
+// The wavefront's keys of the turn that starts at t0: records first + u * 64 + lane, from
+// clamped positions; returns first.
+__device__ __forceinline__ uint32_t read_keys(const int64_t *__restrict__ keys, const Part &pt,
+                                              uint32_t t0, int64_t (&k)[kScan]) {
+    const uint32_t first = t0 + wave_index() * (kScan * 64);
+    const uint32_t i = first + (thread_index() & 63);
+#pragma unroll
+    for (int u = 0; u < kScan; ++u)
+        k[u] = keys[pt.kb + min(i + u * 64, pt.n - 1)];
+    return first;
+}
+
+// Goes through the viewer in turns of kTurn keys, input order being (turn, wavefront, round,
+// lane), and calls put(place, key, position) for every record of the part, place its index among
+// them in input order. The next turn's keys are read meanwhile; k holds the first turn's. Returns
+// the number of records of the part, below the number of records below it. Ends with a barrier.
+template <typename F>
+__device__ __forceinline__ uint32_t scan_viewer(PartShared &sh, const int64_t *__restrict__ keys,
+                                                const Part &pt, const Bounds &bd,
+                                                int64_t (&k)[kScan], uint32_t &below, F put) {
+    const int lane = thread_index() & 63, w = wave_index();
+    uint32_t m = 0, under = 0;
+    for (uint32_t t0 = 0, turn = 0; t0 < pt.n; t0 += kTurn, turn ^= 1) {
+        int64_t next[kScan];
+        read_keys(keys, pt, t0 + kTurn, next);
+        const uint32_t first = t0 + w * (kScan * 64), i = first + lane;
+        uint64_t mask[kScan];
+        uint32_t c = 0;
+        // By key alone; a turn with keys equal to a bound (one record each, unless keys repeat)
+        // or past the viewer's end settles them by position.
+        uint64_t rest = __ballot(i + (kScan - 1) * 64 >= pt.n);
+#pragma unroll
+        for (int u = 0; u < kScan; ++u) {
+            const uint64_t lt0 = __ballot(k[u] < bd.k0), lt1 = __ballot(k[u] < bd.k1);
+            rest |= __ballot(k[u] == bd.k0) | __ballot(k[u] == bd.k1);
+            under += __popcll(lt0);
+            mask[u] = lt1 & ~lt0;
+            c += __popcll(mask[u]);
+        }
+        if (rest) {                                      // uniform per wavefront
+            c = 0;
+#pragma unroll
+            for (int u = 0; u < kScan; ++u) {
+                const uint32_t p = i + u * 64;
+                const uint64_t lt0 = __ballot(k[u] < bd.k0), lt1 = __ballot(k[u] < bd.k1);
+                const uint64_t ok = __ballot(p < pt.n);
+                const uint64_t lt = ok & (lt0 | (__ballot(k[u] == bd.k0) & __ballot(p < bd.p0)));
+                const uint64_t in = lt1 | (__ballot(k[u] == bd.k1) & __ballot(p < bd.p1));
+                under += __popcll(lt) - __popcll(lt0);
+                mask[u] = ok & in & ~lt;
+                c += __popcll(mask[u]);
+            }
+        }
+        if (lane == 0)
+            sh.run[turn][w] = c;
+        lds_sync();
+        uint32_t at = m;
+#pragma unroll
+        for (int q = 0; q < kPartWaves; ++q) {
+            const uint32_t r = sh.run[turn][q];
+            at += q < w ? r : 0;
+            m += r;
+        }
+        if (c) {                                         // uniform per wavefront
+#pragma unroll
+            for (int u = 0; u < kScan; ++u) {
+                if ((mask[u] >> lane) & 1)
+                    put(at + lanes_below(mask[u]), k[u], i + u * 64);
+                at += __popcll(mask[u]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kScan; ++u)
+            k[u] = next[u];
+    }
+    if (lane == 0)
+        sh.below[w] = under;
+    lds_sync();
+    below = 0;
+#pragma unroll
+    for (int q = 0; q < kPartWaves; ++q)
+        below += sh.below[q];
+    return m;
+}
+
+// The part's records in global memory: sorted keys, then rows, to output positions from `to` on.
+// Sorted records [0, m) come from sh.key / sh.pos.
+__device__ __forceinline__ void emit(const PartShared &sh, const Part &pt, uint64_t kmin, int m,
+                                     int64_t to, const SortOut &o) {
+    for (int i = threadIdx.x; i < m; i += kPartThreads)
+        __builtin_nontemporal_store((int64_t)(sh.key[i] + kmin), o.keys_out + to + i);
+    copy_rows<4, kPartThreads>(m, o, [&](int rec, int64_t &from, int64_t &dst) {
+        from = pt.kb + sh.pos[rec];
+        dst = to + rec;
+    });
+}
+
+// A part of m > kCap records, by digit passes through the workspace's element arrays: the
+// records in input order into a[0, m), then one stable pass per digit between a and b, each a
+// count of the digits and a scatter of chunks of kPartThreads. Called by the whole workgroup; a and b
+// are the part's own slices. Written for few registers: it shares the kernel with the path above.
+__device__ __forceinline__ void big_part(PartShared &sh, const int64_t *__restrict__ keys,
+                                         const Part &pt, const Bounds &bd, uint32_t m, Elem *a,
+                                         Elem *b, int64_t to, const SortOut &o) {
+    const int tid = thread_index(), lane = tid & 63, w = wave_index();
+    int64_t lo = INT64_MAX, hi = INT64_MIN;
+    uint32_t found = 0;
+    for (uint32_t p0 = 0; p0 < pt.n; p0 += kPartThreads) {
+        const uint32_t p = p0 + tid;
+        const int64_t k = keys[pt.kb + min(p, pt.n - 1)];
+        const bool in = p < pt.n && (k > bd.k0 || (k == bd.k0 && p >= bd.p0)) &&
+                        (k < bd.k1 || (k == bd.k1 && p < bd.p1));
+        const uint64_t mask = __ballot(in);
+        if (lane == 0)
+            sh.run[0][w] = __popcll(mask);
+        lds_sync();
+        uint32_t at = found + lanes_below(mask);
+#pragma unroll 1
+        for (int q = 0; q < kPartWaves; ++q) {
+            at += q < w ? sh.run[0][q] : 0;
+            found += sh.run[0][q];
+        }
+        if (in) {
+            lo = min(lo, k);
+            hi = max(hi, k);
+            if (at < m)
+                a[at] = Elem{(uint64_t)k, p};
+        }
+        lds_sync();                                      // run is written again
+    }
+    key_range(sh, lo, hi);
+    const Digits dg = digits_of((uint64_t)hi - (uint64_t)lo);
+    __syncthreads();                                     // the stores, before their readers
+#pragma unroll 1
+    for (int p = 0; p < dg.passes; ++p) {
+        const int shift = p * dg.D;
+        if (tid < kRadix)
+            sh.start[tid] = 0;
+        lds_sync();
+#pragma unroll 1
+        for (uint32_t i = tid; i < m; i += kPartThreads)
+            atomicAdd(&sh.start[(uint32_t)((a[i].key - (uint64_t)lo) >> shift) & dg.mask], 1u);
+        lds_sync();
+        uint32_t run = 0;                                // records before this digit's next one
+        if (tid < kRadix) {
+#pragma unroll 1
+            for (int d = 0; d < tid; ++d)
+                run += sh.start[d];
+        }
+        lds_sync();
+#pragma unroll 1
+        for (uint32_t c0 = 0; c0 < m; c0 += kPartThreads) {
+            const int n = (int)min<uint32_t>(kPartThreads, m - c0);
+            const Elem e = a[c0 + min(tid, n - 1)];
+            const uint64_t key[1] = {e.key - (uint64_t)lo};
+            uint32_t rd[1];
+            rank_rounds(sh, key, 1, w * 64, n, shift, dg.mask, rd);
+            lds_sync();
+            digit_offsets(sh);
+            lds_sync();
+            if (tid < kRadix) {
+                const uint32_t at = sh.start[tid];
+                sh.adj[tid] = run - at;
+                run += (tid + 1 < kRadix ? sh.start[tid + 1] : (uint32_t)n) - at;
+            }
+            lds_sync();
+            const uint32_t d = rd[0] & 0xFFu, dst = sh.adj[d] + sh.cnt[w][d] + (rd[0] >> 8);
+            if (tid < n && dst < m)
+                b[dst] = e;
+            lds_sync();
+        }
+        __syncthreads();                                 // the pass's stores, before its readers
+        Elem *t = a;
+        a = b;
+        b = t;
+    }
+    // One record per wavefront at a time.
+#pragma unroll 1
+    for (uint32_t i = w; i < m; i += kPartWaves) {
+        const Elem e = a[i];
+        const int64_t from = (pt.kb + min<int64_t>((int64_t)e.pos, pt.n - 1)) * o.row_chunks;
+        if (lane == 0)
+            o.keys_out[to + i] = (int64_t)e.key;
+#pragma unroll 1
+        for (int c = lane; c < o.row_chunks; c += 64)
+            o.rows_out[(to + i) * o.row_chunks + c] = o.rows_in[from + c];
+    }
+}
+
+__device__ __forceinline__ void sort_part(PartShared &sh, const int64_t *__restrict__ keys,
+                                          const Part &pt, Elem *buf0, Elem *buf1,
+                                          const SortOut &o) {
+    // Up to two rounds through one copy of the LDS sort: the sample, unless its ranks are counted
+    // or the viewer is one part; then the part. The first turn's keys are on their way meanwhile.
+    const Sample sm(pt);
+    int64_t k0[kScan];
+    const bool whole = pt.G == 1, counted = sm.S <= kSampleCount;
+    if (!whole) {
+        read_keys(keys, pt, 0, k0);
+        if (counted)
+            count_bounds(sh, keys, pt, sm);
+    }
+    int64_t kmin = 0;
+    uint32_t m = 0, below = 0;
+    for (int phase = whole || counted ? 1 : 0; phase < 2; ++phase) {
+        uint64_t key[kEpt];
+        uint32_t pos[kEpt];
+        if (phase == 0 || whole) {
+            m = phase == 0 ? sm.S : pt.n;
+            const Rounds rs((int)m);
+#pragma unroll
+            for (int r = 0; r < kEpt; ++r) {
+                if (r < rs.R) {                          // uniform
+                    const uint32_t i = min((uint32_t)rs.at(r), m - 1);
+                    pos[r] = phase == 0 ? sm.pos(i) : i;
+                    key[r] = (uint64_t)keys[pt.kb + pos[r]];
+                }
+            }
+        } else {
+            if (!counted)
+                pick_bounds(sh, pt, sm.S, kmin);
+            const Bounds bd{sh.bound_key[0], sh.bound_key[1], sh.bound_pos[0], sh.bound_pos[1]};
+            m = scan_viewer(sh, keys, pt, bd, k0, below, [&](uint32_t at, int64_t k, uint32_t p) {
+                if (at < kCap) {
+                    sh.key[at] = (uint64_t)k;
+                    sh.pos[at] = p;
+                }
+            });
+            if (m == 0)
+                return;
+            if (m > kCap)
+                break;
+            const Rounds rs((int)m);
+#pragma unroll
+            for (int r = 0; r < kEpt; ++r) {
+                if (r < rs.R) {
+                    const int i = min(rs.at(r), (int)m - 1);
+                    key[r] = sh.key[i];
+                    pos[r] = sh.pos[i];
+                }
+            }
+        }
+        kmin = sort_lds(sh, Rounds((int)m), key, pos);
+    }
+    const int64_t to = pt.kb + below;
+    if (m <= kCap) {
+        emit(sh, pt, (uint64_t)kmin, (int)m, to, o);
+    } else {
+        const Bounds bd{sh.bound_key[0], sh.bound_key[1], sh.bound_pos[0], sh.bound_pos[1]};
+        big_part(sh, keys, pt, bd, m, buf0 + to, buf1 + to, to, o);
+    }
+}
+
+// Records [base, base + n) go to the output unchanged (keys and rows, in input order).
+__device__ __forceinline__ void copy_slice(const int64_t *__restrict__ keys, int64_t base, int64_t n,
+                                           const SortOut &o) {
+    for (int64_t i = threadIdx.x; i < n; i += kPartThreads)
+        o.keys_out[base + i] = keys[base + i];
+    const int64_t c0 = base * o.row_chunks, c1 = (base + n) * o.row_chunks;
+    for (int64_t c = c0 + threadIdx.x; c < c1; c += kPartThreads)
+        o.rows_out[c] = o.rows_in[c];
+}
+
+// Work items: one per viewer (its part 0), then one per multiple of `part` in [part, total). The
+// multiple a * part that falls strictly inside a viewer is one more part of it, so a viewer's
+// parts are numbered by the multiples it covers and no scan over the viewers is needed.
+__global__ __launch_bounds__(kPartThreads, 4) void part_sort_kernel(const int64_t *__restrict__ keys,
+                                                                const int64_t *off, int32_t B,
+                                                                int32_t part, Elem *buf0, Elem *buf1,
+                                                                SortOut o) {
+    __shared__ PartShared sh;
+    const int64_t it = blockIdx.x;
+    int64_t v, a = 0;
+    if (it < B) {
+        v = it;
+    } else {
+        a = it - B + 1;
+        v = owner<kPartThreads>(off, B, a * part);
+    }
+    int64_t kb, ke;
+    segment(off, o.total, v, kb, ke);
+    const int64_t n = ke - kb;
+    const int64_t first = (uint32_t)kb / (uint32_t)part; // multiples up to kb (offsets < 2^32)
+    const int64_t G = n <= part ? 1 : 1 + (uint32_t)(ke - 1) / (uint32_t)part - first;
+    const int64_t g = it < B ? 0 : a - first;
+    if (n <= 0 || g < 0 || g >= G || (it >= B && g == 0))
+        return;
+    if (n > o.limit || n >= kPartMaxRecords) {        // larger than the caller's bound
+        const int64_t b0 = kb + n * g / G, b1 = kb + n * (g + 1) / G;
+        copy_slice(keys, b0, b1 - b0, o);
+        return;
+    }
+    sort_part(sh, keys, Part{kb, (uint32_t)n, (uint32_t)g, (uint32_t)G}, buf0, buf1, o);
+}
+
+// ---- ranks by comparison: the smallest calls --------------------------------------------------
+//
+// A record's place is the number of records of its viewer that order before it. A workgroup takes
+// `per` consecutive records, holds the viewer's whole key list in registers (kRankEpt keys per
+// lane at a time) and counts for one record after the other: a compare per 64 keys, whose lane
+// mask the scalar unit counts. Quadratic in the list, but the compares of a short list cost less
+// than one dependent step of any other method, and nothing but the key load comes before them.
+// The rows are read meanwhile. The cost is the instructions issued, about 14 + 3 R per record and
+// wavefront that holds R rounds of the list: a list of up to 512 keys is therefore held whole by
+// every wavefront, each with records of its own, and longer ones by groups of 2, 4, 8 or 16.
+constexpr int kRankThreads = 1024;
+constexpr int kRankWaves = kRankThreads / 64;
+constexpr int kRankEpt = 8;
+
+// Groups of 1 << rank_group(n) wavefronts hold a list of n keys.
+__host__ __device__ inline int rank_group(int64_t n) {
+    int gs = 0;
+    while ((kRankWaves >> gs) > 1 && n > (int64_t)(kRankEpt * 64) << gs)
+        ++gs;
+    return gs;
+}
+
+struct RankShared {
+    uint32_t diff[kRankWaves];
+    uint32_t cnt[kRankWaves][64];
+    uint32_t rank[kRankMaxPer];
+};
+
+__device__ __forceinline__ uint64_t lane_value(uint64_t x, int lane) {
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// cnt of lane t < c += keys k[r], r < R, of the wavefront that order before the record whose key
+// lane t holds in x. PACKED: k and x hold (key, position) in one word each. Otherwise k[r]'s
+// position is pos + r * 64 and lane t's record's is p + t.
+template <int R, bool PACKED>
+__device__ __forceinline__ void count_before(const uint64_t (&k)[kRankEpt], uint64_t x, int c,
+                                             uint32_t pos, uint32_t p, uint32_t &cnt) {
+    const int lane = threadIdx.x & 63;
+    for (int t = 0; t < c; ++t) {
+        const uint64_t y = lane_value(x, t);
+        uint32_t n = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            n += __popcll(__ballot(k[r] < y));
+            if (!PACKED)
+                n += __popcll(__ballot(k[r] == y) & __ballot(pos + r * 64 < p + t));
+        }
+        cnt += lane == t ? n : 0;
+    }
+}
+
+template <bool PACKED>
+__device__ __forceinline__ void count_before(int R, const uint64_t (&k)[kRankEpt], uint64_t x, int c,
+                                             uint32_t pos, uint32_t p, uint32_t &cnt) {
+    switch (R) {                                         // uniform
+    case 1: count_before<1, PACKED>(k, x, c, pos, p, cnt); break;
+    case 2: count_before<2, PACKED>(k, x, c, pos, p, cnt); break;
+    case 3: count_before<3, PACKED>(k, x, c, pos, p, cnt); break;
+    case 4: count_before<4, PACKED>(k, x, c, pos, p, cnt); break;
+    case 5: count_before<5, PACKED>(k, x, c, pos, p, cnt); break;
+    case 6: count_before<6, PACKED>(k, x, c, pos, p, cnt); break;
+    case 7: count_before<7, PACKED>(k, x, c, pos, p, cnt); break;
+    default: count_before<8, PACKED>(k, x, c, pos, p, cnt); break;
+    }
+}
+
+// Records [p, p + c) of the viewer with records [kb, kb + n), p relative to kb.
+__device__ __forceinline__ void rank_records(RankShared &sh, const int64_t *__restrict__ keys,
+                                             int64_t kb, uint32_t n, uint32_t p, int c,
+                                             const SortOut &o) {
+    constexpr uint64_t kFlip = (uint64_t)1 << 63;        // signed order as unsigned order
+    const int tid = threadIdx.x, lane = tid & 63, w = wave_index();
+    const int64_t *gk = keys + kb;
+    // Groups of 1 << gs wavefronts hold the list; group `grp` ranks records [t0, t0 + mine).
+    const int gs = rank_group(n);
+    const int in = w & ((1 << gs) - 1), grp = w >> gs;
+    const int share = (c + (kRankWaves >> gs) - 1) / (kRankWaves >> gs);
+    const int t0 = grp * share, mine = max(0, min(share, c - t0));
+    const uint32_t mp = p + min(t0 + lane, c - 1);       // the record whose rank the lane gets
+    const uint64_t key = (uint64_t)gk[mp] ^ kFlip;
+    const uint64_t ref = (uint64_t)gk[p] ^ kFlip;
+    const int64_t out_key = gk[p + min(tid, c - 1)];
+    // The first row chunk of the thread, on its way while the ranks are counted.
+    const int chunks = c * o.row_chunks;
+    const chunk_t *rows = o.rows_in + (kb + p) * o.row_chunks;
+    const chunk_t first = rows[min(tid, chunks - 1)];
+    const int bits = 32 - __clz(n);                      // positions are below 2^bits
+    const uint32_t turn = (uint32_t)(kRankEpt * 64) << gs;
+    uint32_t cnt = 0;
+    for (uint32_t c0 = 0; c0 < n; c0 += turn) {          // uniform
+        const int R = (int)((min(n - c0, turn) + (64u << gs) - 1) >> (6 + gs));
+        const uint32_t pos = c0 + in * R * 64 + lane;    // (wavefront, round, lane)
+        uint64_t k[kRankEpt];
+#pragma unroll
+        for (int r = 0; r < kRankEpt; ++r)
+            if (r < R)                                   // uniform
+                k[r] = (uint64_t)gk[min(pos + r * 64, n - 1)] ^ kFlip;
+        uint64_t diff = key ^ ref;
+#pragma unroll
+        for (int r = 0; r < kRankEpt; ++r)
+            if (r < R)
+                diff |= k[r] ^ ref;
+        // Bits in which keys differ, over the workgroup: below them, room for the position?
+        uint32_t any = (uint32_t)(diff >> 32);
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1)
+            any |= __shfl_xor(any, d);
+        lds_sync();                                      // the last turn's readers are done
+        if (lane == 0)
+            sh.diff[w] = any;
+        lds_sync();
+#pragma unroll
+        for (int q = 0; q < kRankWaves; ++q)
+            any |= sh.diff[q];
+        any = __builtin_amdgcn_readfirstlane(any);
+        const bool packed = __clz(any | 1) >= bits;      // uniform: the top bits are alike
+#pragma unroll
+        for (int r = 0; r < kRankEpt; ++r) {
+            // Past the end: above every packed record; or the largest key, at a position past
+            // every record's.
+            if (r < R)
+                k[r] = pos + r * 64 >= n ? ~(uint64_t)0
+                                         : (packed ? (k[r] << bits) | (pos + r * 64) : k[r]);
+        }
+        if (packed)
+            count_before<true>(R, k, (key << bits) | mp, mine, pos, p + t0, cnt);
+        else
+            count_before<false>(R, k, key, mine, pos, p + t0, cnt);
+    }
+    sh.cnt[w][lane] = cnt;
+    lds_sync();
+    if (tid < c) {
+        const int g = tid / share, t = tid - g * share;
+        uint32_t rank = 0;
+        for (int q = 0; q < 1 << gs; ++q)
+            rank += sh.cnt[(g << gs) + q][t];
+        sh.rank[tid] = rank;
+        o.keys_out[kb + rank] = out_key;
+    }
+    lds_sync();
+    for (int g = tid; g < chunks; g += kRankThreads) {
+        const int rec = g / o.row_chunks;
+        o.rows_out[(kb + sh.rank[rec]) * o.row_chunks + (g - rec * o.row_chunks)] =
+            g < kRankThreads ? first : rows[g];
+    }
+}
+
+// Workgroup b takes the records [b * per, (b + 1) * per) of the call, viewer by viewer.
+__global__ __launch_bounds__(kRankThreads) void rank_sort_kernel(const int64_t *__restrict__ keys,
+                                                                 const int64_t *off, int32_t B,
+                                                                 int32_t per, SortOut o) {
+    __shared__ RankShared sh;
+    int64_t p = (int64_t)blockIdx.x * per;
+    const int64_t end = min(p + per, o.total);
+    while (p < end) {                                    // uniform
+        const int64_t v = owner<kRankThreads>(off, B, p);
+        int64_t kb, ke;
+        segment(off, o.total, v, kb, ke);
+        if (p < kb || p >= ke)
+            break;                                       // offsets that break the rules
+        const int64_t e = min(end, ke);
+        if (ke - kb > o.limit) {                         // larger than the caller's bound
+            for (int64_t i = p + threadIdx.x; i < e; i += kRankThreads)
+                o.keys_out[i] = keys[i];
+            for (int64_t g = p * o.row_chunks + threadIdx.x; g < e * o.row_chunks; g += kRankThreads)
+                o.rows_out[g] = o.rows_in[g];
+        } else {
+            rank_records(sh, keys, kb, (uint32_t)(ke - kb), (uint32_t)(p - kb), (int)(e - p), o);
+        }
+        lds_sync();                                      // sh is reused
+        p = e;
+    }
+}
+
+}  // namespace
+
+hipError_t launch_part_sort(int32_t n_viewers, const int64_t *key_offsets, const int64_t *keys_in,
+                            const void *rows_in, int32_t row_bytes, int64_t total, int64_t limit,
+                            int64_t *keys_out, void *rows_out, void *buf0, void *buf1,
+                            hipStream_t stream) {
+    const SortOut o{limit, total, static_cast<const chunk_t *>(rows_in), row_bytes / 16, keys_out,
+                    static_cast<chunk_t *>(rows_out), nullptr};
+    const int64_t work = total * ((limit + 511) / 512);
+    if ((work <= (limit <= kPartSmall ? kRankWorkShort : kRankWorkLong) ||
+         (limit > kPartSmall && total <= kRankTotal)) &&
+        total >= (int64_t)n_viewers * kRankMinMean) {
+        int32_t per = (int32_t)((total + kRankGrid - 1) / kRankGrid);
+        // A group of wavefronts ranks at most 64 records (one lane each).
+        const int32_t most = min(kRankMaxPer, 64 * (kRankWaves >> rank_group(limit)));
+        if (per > most)
+            per = most;
+        hipLaunchKernelGGL(rank_sort_kernel, dim3((unsigned)((total + per - 1) / per)),
+                           dim3(kRankThreads), 0, stream, keys_in, key_offsets, n_viewers, per, o);
+        return hipGetLastError();
+    }
+    const int32_t part = total <= kPartSmallTotal ? kPartSmall : kPartLarge;
+    hipLaunchKernelGGL(part_sort_kernel, dim3((unsigned)(n_viewers + (total - 1) / part)),
+                       dim3(kPartThreads), 0, stream, keys_in, key_offsets, n_viewers, part,
+                       static_cast<Elem *>(buf0), static_cast<Elem *>(buf1), o);
+    return hipGetLastError();
+}
+
+}  // namespace ccj

@@ -7,8 +7,9 @@
 //   * packed, 8 bytes: ((key - kmin) << pbits) | (position within the viewer), when the span of
 //     the call's keys leaves room for pbits position bits (pbits covers the largest viewer);
 //   * wide, 16 bytes: (key, flat input position), for any keys.
-// Every call starts with the key range (per-workgroup slots, reduced by a plan kernel). Then one
-// of two methods, chosen on the host (by call size, or by the caller):
+// The automatic choice sends calls of moderate lists to the one-launch methods of
+// part_sort_kernels.hip; this file holds the two for the rest (or by the caller's choice). A call
+// starts with the key range (per-workgroup slots, reduced by a plan kernel), then:
 //
 // Merge (calls below kSortRadixMinRecords records): tiles of kTile records per viewer; a block
 // sort per tile (every thread sorts kEpt records in registers with a bitonic network, then
@@ -39,13 +40,12 @@
 #include <hip/hip_runtime.h>
 
 #include "join_internal.h"
+#include "sort_device.h"
 
 namespace ccj {
 namespace {
 
 constexpr int kTile = 4096;                       // records per tile
-constexpr int kThreads = 512;                     // threads per workgroup
-constexpr int kWaves = kThreads / 64;
 constexpr int kEpt = kTile / kThreads;            // records per thread (8)
 constexpr int kLdsElems = kTile + kTile / kEpt;   // padded LDS tile of the small-viewer sort
 constexpr int kDigitBits = 9;                     // widest digit
@@ -53,8 +53,6 @@ constexpr int kRadix = 1 << kDigitBits;           // values of one digit (512 = 
 constexpr int kMaxPasses = 8;                     // 64-bit key spans
 constexpr int kDirectPasses = 3;                  // key spans up to 27 bits
 constexpr unsigned kLoopGrid = 256;               // workgroups of the later passes
-
-typedef unsigned int chunk_t __attribute__((ext_vector_type(4)));
 
 // Shared by every kernel of one call: the key range (written by the plan) and the number of
 // position bits a packed element needs.
@@ -146,23 +144,6 @@ __device__ __forceinline__ Digits digits_of(const Codec &c) {
 
 __device__ __forceinline__ int pidx(int i) { return i + i / kEpt; }
 
-__device__ __forceinline__ void lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-__device__ __forceinline__ int64_t clampk(int64_t v, int64_t hi) {
-    return v < 0 ? 0 : (v > hi ? hi : v);
-}
-
-// Segment [kb, ke) of viewer v, offsets clamped to [0, total] and made non-decreasing.
-__device__ __forceinline__ void segment(const int64_t *off, int64_t total, int64_t v, int64_t &kb,
-                                        int64_t &ke) {
-    kb = clampk(off[v], total);
-    ke = max(kb, clampk(off[v + 1], total));
-}
-
 __device__ __forceinline__ int64_t tiles_of(int64_t n) { return (n + kTile - 1) / kTile; }
 
 __device__ __forceinline__ int rounds_of(int64_t tiles) {
@@ -181,24 +162,6 @@ __device__ __forceinline__ int radix_tile(bool packed) {
 // radix_tile records): none for a viewer that the small-viewer sort takes whole.
 __device__ __forceinline__ int64_t multi_tiles(int64_t n, int tile) {
     return n > kTile ? (n + tile - 1) / tile : 0;
-}
-
-// Largest v in [0, B) with tile_off[v] <= t (tile_off non-decreasing, tile_off[0] = 0), found by
-// the whole workgroup (call it uniformly). Each round every thread probes one of kThreads
-// evenly spaced viewers; the probes at or below t are a prefix, and its length narrows the range
-// kThreads-fold. Up to kThreads viewers take one round of independent loads instead of a chain
-// of ~log2(B) dependent ones.
-__device__ __forceinline__ int64_t owner(const int64_t *tile_off, int64_t B, int64_t t) {
-    int64_t lo = 0, hi = B - 1;                   // tile_off[lo] <= t; the answer is in [lo, hi]
-    while (lo < hi) {
-        const int64_t step = (hi - lo + kThreads) / kThreads;
-        const int64_t v = lo + (int64_t)threadIdx.x * step;
-        const int c = __syncthreads_count(v <= hi && tile_off[v] <= t);   // >= 1 (probe lo)
-        const int64_t nlo = lo + (int64_t)(c - 1) * step;
-        hi = min(hi, nlo + step - 1);
-        lo = nlo;
-    }
-    return lo;
 }
 
 // a goes first in a merge (ties go to the first run).
@@ -280,69 +243,6 @@ __device__ __forceinline__ void store_regs(typename F::T *s, const typename F::T
     for (int m = 0; m < kEpt; ++m)
         if (first + m < n)
             s[pidx(first + m)] = r[m];
-}
-
-struct SortOut {
-    int64_t limit;          // viewers with more records are copied through in input order
-    int64_t total;
-    const chunk_t *rows_in;
-    int32_t row_chunks;
-    int64_t *keys_out;
-    chunk_t *rows_out;
-    uint32_t *perm;         // [total]: input position of the record at each output position
-};
-
-// Copy the feature rows of n sorted records: record i's row goes from flat input position
-// src(i) to flat output position dst(i), skipped where dst(i) < 0. 16-byte chunks in batches of U
-// per thread, two batches in flight: the loads of the next batch are issued before the stores
-// of the current one (vector-memory completions are counted in issue order, stores included, so
-// a load issued after a store could only be waited for together with it). The sorted rows are
-// not read again by this call: non-temporal stores keep them from evicting the lines of rows
-// still to be gathered.
-template <int U, typename Map>
-__device__ __forceinline__ void copy_rows(int n, const SortOut &o, Map map) {
-    const int row_chunks = o.row_chunks;
-    const int n_chunks = n * row_chunks;
-    // Chunk g of the thread's sequence (g = threadIdx.x + j * kThreads) is chunk q of record
-    // rec; both advance by kThreads chunks without a division.
-    const int drec = kThreads / row_chunks, dq = kThreads - drec * row_chunks;
-    int rec = threadIdx.x / row_chunks, q = threadIdx.x - rec * row_chunks;
-    auto load = [&](int g0, chunk_t (&c)[U], int64_t (&to)[U]) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int g = g0 + u * kThreads;
-            to[u] = -1;
-            if (g < n_chunks) {
-                int64_t src, dst;
-                map(rec, src, dst);
-                if (dst >= 0) {
-                    c[u] = o.rows_in[src * row_chunks + q];
-                    to[u] = dst * row_chunks + q;
-                }
-            }
-            rec += drec;
-            q += dq;
-            if (q >= row_chunks) {
-                q -= row_chunks;
-                ++rec;
-            }
-        }
-    };
-    auto store = [&](const chunk_t (&c)[U], const int64_t (&to)[U]) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (to[u] >= 0)
-                __builtin_nontemporal_store(c[u], o.rows_out + to[u]);
-    };
-    chunk_t ca[U], cb[U];
-    int64_t ta[U], tb[U];
-    load(threadIdx.x, ca, ta);
-    for (int g0 = threadIdx.x; g0 < n_chunks; g0 += 2 * U * kThreads) {
-        load(g0 + U * kThreads, cb, tb);
-        store(ca, ta);
-        load(g0 + 2 * U * kThreads, ca, ta);
-        store(cb, tb);
-    }
 }
 
 // Records [base, base + n) go to the output unchanged, in input order (keys now, rows by the
@@ -557,7 +457,7 @@ __global__ __launch_bounds__(kThreads) void small_kernel(const int64_t *__restri
         small_body(Wide{kmin}, dg, lds, keys, off, B, mt, o);
 }
 
-// ---- merge path (calls below kRadixMinRecords records) -------------------------------------
+// ---- merge path (calls below kSortRadixMinRecords records) ---------------------------------
 //
 // Tiles of kTile records per viewer (tile_off: an exclusive scan of ceil(n_v / kTile)); a block
 // sort per tile, then merge rounds within each viewer: runs of kTile << r records are merged
@@ -1330,12 +1230,21 @@ hipError_t launch_sort(int32_t n_viewers, const int64_t *key_offsets, const int6
                        int32_t key_bits, hipStream_t stream) {
     if (total <= 0 || n_viewers <= 0)
         return hipSuccess;
-    if (method == kSortAuto)
-        method = total >= kSortRadixMinRecords ? kSortRadix : kSortMerge;
     uint8_t *w = static_cast<uint8_t *>(workspace);
     const Layout l = layout_of(total, n_viewers);
     void *buf0 = w;
     void *buf1 = w + l.buf;
+    if (method == kSortAuto) {
+        const int64_t limit = max_keys > 0 && max_keys < total ? max_keys : total;
+        int64_t longest = limit;
+        if (max_keys <= 0 && longest > kPartSkew * (total / n_viewers + 1))
+            longest = kPartSkew * (total / n_viewers + 1);
+        if (n_viewers <= kPartMaxViewers && longest <= kPartMaxWork / total &&
+            (max_keys > 0 || total <= kPartUnboundedTotal))
+            return launch_part_sort(n_viewers, key_offsets, keys_in, rows_in, row_bytes, total,
+                                    limit, keys_out, rows_out, buf0, buf1, stream);
+        method = total >= kSortRadixMinRecords ? kSortRadix : kSortMerge;
+    }
     int64_t *mt_off = reinterpret_cast<int64_t *>(w + l.mt_off);   // tile_off on the merge path
     int64_t *range = reinterpret_cast<int64_t *>(w + l.range);
     uint32_t *counters = reinterpret_cast<uint32_t *>(w + l.range + 64);
