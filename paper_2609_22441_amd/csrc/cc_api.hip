@@ -198,6 +198,7 @@ cc_status join_impl(const cc_store *store, int32_t n_viewers, const int64_t *can
     a.out_stride = out_row_stride;
     a.hit = hit_mask;
     a.n_max = n_max;
+    a.valid = valid_mask;
     a.invalid_counter = store->d_invalid;
     a.n_viewers = cand_offsets ? n_viewers : 1;
     a.fence_stride = stride;
@@ -210,11 +211,7 @@ cc_status join_impl(const cc_store *store, int32_t n_viewers, const int64_t *can
     // The LDS table never needs more entries than the largest viewer has keys.
     a.lds_keys = (int32_t)(total_keys < lds_cap ? (total_keys > 0 ? total_keys : 1) : lds_cap);
 
-    hipError_t e = hipSuccess;
-    if (total_cand > 0)
-        e = ccj::launch_join(a, n_lookups, wgs, store->device, stream);
-    if (e == hipSuccess && padded)
-        e = ccj::launch_pad_fill(a, n_lookups, valid_mask, stream);
+    const hipError_t e = ccj::launch_join(a, n_lookups, wgs, store->device, stream);
     if (e != hipSuccess)
         return device_error(e);
     return CC_OK;

@@ -22,6 +22,7 @@ constexpr int64_t kLongListKeys = 4 * (int64_t)kDefaultLdsKeys;
 // Largest row (document, edge or affinity record) in bytes. Copy loops count a tile's row
 // chunks in 32 bits: 256 rows (or 4096 sort records) of this many bytes stay far below 2^31.
 constexpr int32_t kMaxRowBytes = 1 << 20;
+constexpr int64_t kMaxTileStride = 1 << 22;   // a sub-tile of such rows spans 2^30 bytes
 constexpr int kZeroRowBytes = 1024;    // >= the widest row of a compile-time specialisation
 
 struct JoinArgs {
@@ -51,23 +52,21 @@ struct JoinArgs {
     int32_t lds_keys;            // capacity of the dynamic LDS key table
     int32_t fence_stride;        // 0 = chosen per viewer segment
     int32_t fence_budget;        // fences staged per candidate of a segment (automatic stride)
+    int8_t *valid;               // valid mask of the padded layout's slots (n_max > 0)
+    bool wide;                   // rows or strides too long for the pipelined copy; set by launch_join
     bool one_wave;               // automatic grid: one resident wave (long key lists)
     bool lds_auto;               // lds_keys chosen by the library (not by a tuning)
     bool balanced;               // CSR ranges weighted by an estimated cost per candidate
     int32_t n_wg;                // workgroups launched (a multiple of 8); set by launch_join
-    int64_t per_wg;              // candidates per workgroup (multiple of kBlock); set by launch_join
+    int64_t per_wg;              // candidates per workgroup; set by launch_join
 };
 
-// Enqueue the join kernel matching the row widths and lookup count on `device` (current).
+// Enqueue the join kernel matching the row widths and lookup count on `device` (current); in the
+// padded layout it also fills the pad slots and the valid mask.
 // `workgroups` > 0 fixes the grid; 0 sizes it from the kernel's occupancy. Returns the HIP
 // error of the launch.
 hipError_t launch_join(JoinArgs &args, int n_lookups, int32_t workgroups, int device,
                        hipStream_t stream);
-
-// Enqueue the pad fill of the padded layout: valid mask of every slot, zero rows and hit bits
-// for pad slots.
-hipError_t launch_pad_fill(const JoinArgs &args, int n_lookups, int8_t *valid_mask,
-                           hipStream_t stream);
 
 // Workspace bytes of the affinity-record sort for `total` records in `n_viewers` viewers.
 int64_t sort_workspace_bytes(int64_t total, int32_t n_viewers);

@@ -25,9 +25,11 @@
 //            16-byte loads, and count.
 //   hit    : some key equal to x in the inspected window; because keys ascend, the lower
 //            bound is then the leftmost equal key.
+#include <algorithm>
 #include <atomic>
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <utility>
 
 #include "join_internal.h"
@@ -55,6 +57,21 @@ constexpr int kWaitVmcnt0 = (0x7 << 4) | (0xF << 8);
 __device__ __forceinline__ int64_t clamp64(int64_t v, int64_t hi) {
     return v < 0 ? 0 : (v > hi ? hi : v);
 }
+
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ int64_t uniform64(int64_t x) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)x >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// Buffer resource over bytes [p, p + bytes) (raw, 32-bit data format): the memory unit drops a
+// store at an offset past the end, so a partial tile is written by the same unconditional stores
+// as a full one.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(uint8_t *p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)bytes, 0x00020000);
+}
+constexpr int kNonTemporal = 2;      // cache policy of a buffer store (the instruction's nt bit)
 
 // Number of entries of t[0..n) (ascending, n >= 1) that are < x; ceil(log2 n) iterations,
 // trip count independent of x so a wavefront never diverges here.
@@ -342,65 +359,120 @@ __device__ __forceinline__ void balanced_range(const JoinArgs &a, int64_t r, int
     lds_barrier();                                // s is reused by the caller
 }
 
-// Copy a full sub-tile (kBlock rows) whose widths are compile-time chunk counts. Thread tid
-// takes chunks e = i * kBlock + tid of the sub-tile's output, i.e. row e / CH, 16-byte column
-// e % CH, so each wavefront store covers 1 KiB of contiguous output (whole 128-byte lines: a
-// line split between two stores with the streaming hint would be written back twice). Every
-// load and store is unconditional (absent rows are read from the store's zero row), so each
-// thread has all CH loads in flight before its first store. `between()` runs after the loads
-// are issued and before the stores (the caller issues the next sub-tile's dependent loads
-// there). Output rows are written with the non-temporal hint: they are not read again, and
-// keeping them out of the caches leaves room for the author column, keys and edge rows.
-template <int DOC_CH, int EDGE_CH, int NL, typename Between>
-__device__ __forceinline__ void copy_full_tile(const JoinArgs &a, const int64_t *s_src,
-                                               const int64_t (*s_row)[kBlock], int64_t t0,
-                                               const uint8_t *miss_row, Between between) {
+// Address of the source row of each segment of a sub-tile's output rows: the doc row, then the edge
+// row of each lookup (the zero row and the miss row where there is none). Kept as integers and
+// read as global pointers: a pointer fetched from LDS is a generic one, whose loads complete out
+// of order, so that a wait for one of them would be a wait for all.
+template <int NL>
+using Sources = uint64_t[1 + NL][kBlock];
+
+__device__ __forceinline__ chunk_t load_chunk(uint64_t row, int q) {
+    return reinterpret_cast<const __attribute__((address_space(1))) chunk_t *>(row)[q];
+}
+
+// Copy a sub-tile (n <= kBlock rows) whose widths are compile-time chunk counts. Thread tid takes
+// chunks e = i * kBlock + tid of the sub-tile's output, i.e. row e / CH, 16-byte column e % CH, so
+// each wavefront store covers 1 KiB of contiguous output (whole 128-byte lines: a line split
+// between two stores with the streaming hint would be written back twice). Every load is
+// unconditional (rows past n repeat row n - 1) and so is every store (those of rows past n fall
+// outside the buffer and are dropped), so each thread has all CH loads in flight before its first
+// store. `between()` runs after the loads are issued and before the stores (the caller issues
+// the next sub-tile's dependent loads there). Output rows are written with the non-temporal hint:
+// they are not read again, and keeping them out of the caches leaves room for the author column,
+// keys and edge rows. LAST: nothing follows, so chunks wholly past the last row are skipped.
+template <int DOC_CH, int EDGE_CH, int NL, bool LAST, typename Between>
+__device__ __forceinline__ void copy_tile(const JoinArgs &a, const Sources<NL> &s_ptr, int64_t t0,
+                                          int n, Between between) {
     constexpr int CH = DOC_CH + NL * EDGE_CH;
     const int tid = threadIdx.x;
     chunk_t v[CH];
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
+        if (LAST && i * kBlock >= n * CH)                 // uniform
+            break;
         const int e = i * kBlock + tid;
         const int row = e / CH, k = e % CH;
         const bool is_doc = k < DOC_CH;
         const int kk = is_doc ? 0 : k - DOC_CH;
-        const int l = kk / EDGE_CH, q = kk % EDGE_CH;
-        const int64_t d = s_src[row];
-        const int64_t r = s_row[l][row];
-        const uint8_t *pd = d >= 0 ? a.doc + d * (DOC_CH * 16) + k * 16 : a.zero_row + k * 16;
-        const uint8_t *pe = r >= 0 ? a.edge + r * (EDGE_CH * 16) + q * 16 : miss_row + q * 16;
-        v[i] = *reinterpret_cast<const chunk_t *>(is_doc ? pd : pe);
+        const int seg = is_doc ? 0 : 1 + kk / EDGE_CH, q = is_doc ? k : kk % EDGE_CH;
+        v[i] = load_chunk(s_ptr[seg][row], q);
     }
     between();
-    uint8_t *o = a.out + t0 * a.out_stride;
-    if (a.out_stride == CH * 16) {
+    const uint32_t stride = (uint32_t)a.out_stride;
+    const auto o = buffer_of(a.out + t0 * a.out_stride, (uint32_t)n * stride);
+    if (stride == CH * 16) {
         // Packed rows: chunk e sits at byte 16 * e of the sub-tile.
-        chunk_t *po = reinterpret_cast<chunk_t *>(o) + tid;
 #pragma unroll
-        for (int i = 0; i < CH; ++i)
-            __builtin_nontemporal_store(v[i], po + i * kBlock);
+        for (int i = 0; i < CH; ++i) {
+            if (LAST && i * kBlock >= n * CH)
+                break;
+            __builtin_amdgcn_raw_buffer_store_b128(v[i], o, (i * kBlock + tid) * 16, 0, kNonTemporal);
+        }
     } else {
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int e = i * kBlock + tid;
             const int row = e / CH, k = e % CH;
-            __builtin_nontemporal_store(
-                v[i], reinterpret_cast<chunk_t *>(o + row * a.out_stride + k * 16));
+            if (LAST && i * kBlock >= n * CH)
+                break;
+            __builtin_amdgcn_raw_buffer_store_b128(v[i], o, row * stride + k * 16, 0, kNonTemporal);
         }
     }
 }
 
-// Copy the first n rows of a sub-tile (any widths). Used for segments shorter than a sub-tile
-// and for row widths without a compile-time specialisation, so it favours few live registers
-// over loads in flight. DOC_CH / EDGE_CH are row widths in 16-byte chunks (0 = read them from
-// the arguments).
-template <int DOC_CH, int EDGE_CH, int NL>
-__device__ __forceinline__ void copy_rows(const JoinArgs &a, const int64_t *s_src,
-                                          const int64_t (*s_row)[kBlock], int64_t t0, int n) {
+// The same for widths that are only known at run time (rows of at most kZeroRowBytes per
+// segment): batches of kAnyBatch chunks per thread, so rows of up to kAnyBatch chunks have all
+// their loads in flight as above. A thread's row and column advance by kBlock chunks without a
+// division. (300,000 candidates with 128 + 16-byte rows: the division per chunk and four loads in
+// flight of the copy below took 44.5 us, this one 27.)
+constexpr int kAnyBatch = 12;
+
+template <int NL, typename Between>
+__device__ __forceinline__ void copy_tile_any(const JoinArgs &a, const Sources<NL> &s_ptr,
+                                              int64_t t0, int n, Between between) {
     const int tid = threadIdx.x;
-    const int dch = DOC_CH > 0 ? DOC_CH : (a.doc_bytes >> 4);
-    const int ech = EDGE_CH > 0 ? EDGE_CH : (a.edge_bytes >> 4);
-    const int dbytes = dch * 16, ebytes = ech * 16;
+    const int dch = a.doc_bytes >> 4, ech = a.edge_bytes >> 4, ch = dch + NL * ech;
+    const int drow = kBlock / ch, dk = kBlock - drow * ch;
+    int row = tid / ch, k = tid - row * ch;
+    const uint32_t stride = (uint32_t)a.out_stride;
+    const auto o = buffer_of(a.out + t0 * a.out_stride, (uint32_t)n * stride);
+    const int rounds = min(ch, (n * ch + kBlock - 1) / kBlock);   // uniform
+    for (int i0 = 0; i0 < rounds; i0 += kAnyBatch) {
+        chunk_t v[kAnyBatch];
+        uint32_t at[kAnyBatch];
+#pragma unroll
+        for (int u = 0; u < kAnyBatch; ++u) {
+            if (i0 + u < rounds) {                        // uniform
+                const int kk = k - dch;
+                const int l = NL == 2 && kk >= ech ? 1 : 0;
+                const int seg = kk < 0 ? 0 : 1 + l, q = kk < 0 ? k : kk - l * ech;
+                v[u] = load_chunk(s_ptr[seg][row], q);
+                at[u] = row * stride + k * 16;
+                row += drow;
+                k += dk;
+                if (k >= ch) {
+                    k -= ch;
+                    ++row;
+                }
+            }
+        }
+        if (i0 == 0)
+            between();
+#pragma unroll
+        for (int u = 0; u < kAnyBatch; ++u) {
+            if (i0 + u < rounds)
+                __builtin_amdgcn_raw_buffer_store_b128(v[u], o, at[u], 0, kNonTemporal);
+        }
+    }
+}
+
+// Copy the first n rows of a sub-tile of any widths and any stride: for rows longer than the
+// zero row, or strides past a buffer's offsets. A null source reads as zero bytes.
+template <int NL>
+__device__ __forceinline__ void copy_wide_rows(const JoinArgs &a, const Sources<NL> &s_ptr,
+                                               int64_t t0, int n) {
+    const int tid = threadIdx.x;
+    const int dch = a.doc_bytes >> 4, ech = a.edge_bytes >> 4;
     const int ch = dch + NL * ech;
     const int total = n * ch;
     constexpr int U = 4;
@@ -411,31 +483,18 @@ __device__ __forceinline__ void copy_rows(const JoinArgs &a, const int64_t *s_sr
             const int e = base + u * kBlock + tid;
             v[u] = chunk_t{0u, 0u, 0u, 0u};
             if (e < total) {
-                const int row = e / ch, k = e - (e / ch) * ch;
-                const chunk_t *src = nullptr;
-                if (k < dch) {
-                    const int64_t c = s_src[row];
-                    if (c >= 0)
-                        src = reinterpret_cast<const chunk_t *>(a.doc + c * dbytes) + k;
-                } else {
-                    const int kk = k - dch;
-                    const int l = kk / ech;
-                    const int q = kk - l * ech;
-                    const int64_t r = s_row[l][row];
-                    if (r >= 0)
-                        src = reinterpret_cast<const chunk_t *>(a.edge + r * ebytes) + q;
-                    else if (a.def_row)
-                        src = reinterpret_cast<const chunk_t *>(a.def_row) + q;
-                }
+                const int row = e / ch, k = e - row * ch;
+                const int kk = k - dch, l = kk < 0 ? 0 : kk / ech;
+                const uint64_t src = s_ptr[kk < 0 ? 0 : 1 + l][row];
                 if (src)
-                    v[u] = *src;
+                    v[u] = load_chunk(src, kk < 0 ? k : kk - l * ech);
             }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int e = base + u * kBlock + tid;
             if (e < total) {
-                const int row = e / ch, k = e - (e / ch) * ch;
+                const int row = e / ch, k = e - row * ch;
                 reinterpret_cast<chunk_t *>(a.out + (t0 + row) * a.out_stride)[k] = v[u];
             }
         }
@@ -458,58 +517,53 @@ __device__ __forceinline__ void stage_fences(int64_t *s_tab, const int64_t *gk, 
     }
 }
 
-// Resolve one sub-tile starting at candidate tb: per thread, the candidate's position check and
-// search(es). Writes the doc position (or -1) to src[tid] and the global edge row per lookup (or
-// -1) to row[l][tid], stores the hit bytes (output row = candidate + shift), and counts invalid
-// positions of rows tid >= fresh.
+// Resolve one sub-tile of n rows starting at candidate tb: per thread, the candidate's position
+// check and search(es). Writes the source rows to ptr[.][tid] and the hit bytes (output row =
+// candidate + shift; those of rows past n are dropped), and counts invalid positions. `zero` and
+// `miss` stand for absent doc and edge rows.
 template <int NL>
-__device__ __forceinline__ void resolve_tile(const JoinArgs &a, int64_t *src,
-                                             int64_t (*row)[kBlock], unsigned int *s_invalid,
-                                             const int64_t *s_tab, int64_t M, int S,
-                                             const int64_t *gk, int64_t K, int64_t kb, int64_t tb,
-                                             int64_t shift, int fresh, int64_t c, int64_t x0,
-                                             int64_t x1) {
+__device__ __forceinline__ void resolve_tile(const JoinArgs &a, Sources<NL> &ptr,
+                                             unsigned int *s_invalid, const int64_t *s_tab,
+                                             int64_t M, int S, const int64_t *gk, int64_t K,
+                                             int64_t kb, int64_t tb, int n, int64_t shift,
+                                             const uint8_t *zero, const uint8_t *miss, int64_t c,
+                                             int64_t x0, int64_t x1) {
     const int tid = threadIdx.x;
-    const int64_t j = tb + tid + shift;
     const bool valid = c >= 0 && c < a.n_docs;
-    src[tid] = valid ? c : -1;
-    if (!valid && tid >= fresh)
+    ptr[0][tid] = reinterpret_cast<uint64_t>(valid ? a.doc + c * a.doc_bytes : zero);
+    if (!valid && tid < n)
         atomicAdd(s_invalid, 1u);
-    if constexpr (NL == 2) {
-        int64_t r[2];
+    int64_t r[2] = {-1, -1};
+    if constexpr (NL == 2)
         find_key_pair(x0, x1, valid, s_tab, M, S, gk, K, r[0], r[1]);
+    else if (valid)
+        r[0] = find_key(x0, s_tab, M, S, gk, K);
+    const auto hits = buffer_of(reinterpret_cast<uint8_t *>(a.hit) + (tb + shift) * NL, n * NL);
 #pragma unroll
-        for (int l = 0; l < 2; ++l) {
-            row[l][tid] = r[l] >= 0 ? kb + r[l] : -1;
-            a.hit[j * NL + l] = (int8_t)(r[l] >= 0 ? 1 : 0);
-        }
-    } else {
-        int64_t r = -1;
-        if (valid)
-            r = find_key(x0, s_tab, M, S, gk, K);
-        row[0][tid] = r >= 0 ? kb + r : -1;
-        a.hit[j] = (int8_t)(r >= 0 ? 1 : 0);
+    for (int l = 0; l < NL; ++l) {
+        ptr[1 + l][tid] = reinterpret_cast<uint64_t>(
+            r[l] >= 0 ? a.edge + (kb + r[l]) * a.edge_bytes : miss);
+        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(r[l] >= 0 ? 1 : 0), hits, tid * NL + l, 0, 0);
     }
 }
 
-// Process candidates [s0, s1) of one viewer segment (s1 - s0 >= kBlock) in full sub-tiles.
-// Sub-tile k starts at base(k) = min(s0 + k * kBlock, s1 - kBlock): the last one is moved back
-// to end at s1 and overlaps its predecessor (those rows are rewritten with the same bytes, and
-// `fresh` keeps them out of the invalid count).
+// Process candidates [s0, s1) of one viewer segment in sub-tiles of kBlock, the last one partial:
+// its candidates past s1 repeat the last one, and what they would write is dropped.
 //
 // Software pipeline. A thread's dependent chain per candidate is position -> author id ->
 // search -> row copy. Iteration k issues sub-tile k's copy loads, then searches sub-tile k+1
 // into the other half of the double-buffered LDS tables, then issues the loads for later
 // sub-tiles (positions of k+3, author ids of k+2), then stores sub-tile k. Vector-memory
 // completions are counted in issue order, so a search's key-window loads, issued after the
-// copy loads, never wait for stores younger than the previous iteration's. The last iteration
-// searches its own sub-tile once more (identical hit bytes; `fresh` = kBlock counts nothing)
-// so that the loop body has no branch. All loads are unconditional from clamped indices: a
+// copy loads, never wait for stores younger than the previous iteration's. The last sub-tile is
+// copied after the loop, with nothing between. All loads are unconditional from clamped indices: a
 // load under a branch, or a second path into the loop latch, would leave the compiler unable
 // to count outstanding loads, and it would then wait for every store of a sub-tile first.
+// (A last sub-tile moved back to end at s1 instead, its rows written twice, and searched once more
+// inside the loop, took 41.5 us against 37.5 for 8 requests of 50,000 candidates, where a range is
+// 6.1 sub-tiles.)
 template <int DOC_CH, int EDGE_CH, int NL, bool A32, typename Stage>
-__device__ __forceinline__ void full_tiles(const JoinArgs &a, int64_t (*s_src)[kBlock],
-                                           int64_t (*s_row)[NL][kBlock],
+__device__ __forceinline__ void full_tiles(const JoinArgs &a, Sources<NL> *s_ptr,
                                            unsigned int *s_invalid, const int64_t *s_tab,
                                            int64_t M, int S, const int64_t *gk, int64_t K,
                                            int64_t kb, int64_t s0, int64_t s1, int64_t shift,
@@ -517,46 +571,101 @@ __device__ __forceinline__ void full_tiles(const JoinArgs &a, int64_t (*s_src)[k
     const int tid = threadIdx.x;
     const int64_t last_doc = a.n_docs > 0 ? a.n_docs - 1 : 0;
     const int64_t ntiles = (s1 - s0 + kBlock - 1) / kBlock;
-    auto base = [&](int64_t k) { return min(s0 + k * kBlock, s1 - kBlock); };
-    auto fresh = [&](int64_t k) { return (int)min<int64_t>(s0 + k * kBlock - base(k), kBlock); };
+    auto base = [&](int64_t k) { return s0 + k * kBlock; };
+    auto at = [&](int64_t k) { return min(base(k) + tid, s1 - 1); };
+    auto rows = [&](int64_t k) { return (int)min<int64_t>(kBlock, s1 - base(k)); };
     auto extra = [&](int64_t k) -> int64_t {
         if constexpr (NL == 2)
-            return a.extra[base(k) + tid];
+            return a.extra[at(k)];
         return 0;
     };
-    int64_t c1 = a.cand_idx[base(1) + tid];
-    int64_t c2 = a.cand_idx[base(2) + tid];
+    auto resolve = [&](int64_t k, int64_t c, int64_t x, int64_t e) {
+        resolve_tile<NL>(a, s_ptr[k & 1], s_invalid, s_tab, M, S, gk, K, kb, base(k), rows(k), shift,
+                         a.zero_row, miss_row, c, x, e);
+    };
+    auto copy = [&](int64_t k, auto last, auto between) {
+        if constexpr (DOC_CH > 0)
+            copy_tile<DOC_CH, EDGE_CH, NL, decltype(last)::value>(a, s_ptr[k & 1], base(k) + shift,
+                                                                  rows(k), between);
+        else
+            copy_tile_any<NL>(a, s_ptr[k & 1], base(k) + shift, rows(k), between);
+    };
+    int64_t c1 = a.cand_idx[at(1)];
+    int64_t c2 = a.cand_idx[at(2)];
     int64_t e1 = extra(1);
     int64_t x1;
     {
-        const int64_t c0 = a.cand_idx[base(0) + tid];
+        const int64_t c0 = a.cand_idx[at(0)];
         const int64_t e0 = extra(0);
-        const int64_t x0 = author_of<A32>(a, clamp64(c0, last_doc), base(0) + tid);
-        x1 = author_of<A32>(a, clamp64(c1, last_doc), base(1) + tid);
+        const int64_t x0 = author_of<A32>(a, clamp64(c0, last_doc), at(0));
+        x1 = author_of<A32>(a, clamp64(c1, last_doc), at(1));
         stage();
-        resolve_tile<NL>(a, s_src[0], s_row[0], s_invalid, s_tab, M, S, gk, K, kb, base(0),
-                         shift, fresh(0), c0, x0, e0);
+        resolve(0, c0, x0, e0);
     }
     // Let the prologue loads land here (once per segment). Otherwise, where the loop entry and
     // the back edge meet, the compiler keeps the prologue's short distances and waits for the
     // previous sub-tile's stores before every search.
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     lds_barrier();
-    for (int64_t k = 0; k < ntiles; ++k) {
-        const int p = (int)(k & 1);
-        copy_full_tile<DOC_CH, EDGE_CH, NL>(
-            a, s_src[p], s_row[p], base(k) + shift, miss_row, [&]() {
-                resolve_tile<NL>(a, s_src[p ^ 1], s_row[p ^ 1], s_invalid, s_tab, M, S, gk, K,
-                                 kb, base(k + 1), shift, fresh(k + 1), c1, x1, e1);
-                const int64_t c3 = a.cand_idx[base(k + 3) + tid];
-                const int64_t e2 = extra(k + 2);
-                const int64_t x2 = author_of<A32>(a, clamp64(c2, last_doc), base(k + 2) + tid);
-                c1 = c2;
-                c2 = c3;
-                x1 = x2;
-                e1 = e2;
-            });
+    for (int64_t k = 0; k + 1 < ntiles; ++k) {
+        copy(k, std::false_type{}, [&]() {
+            resolve(k + 1, c1, x1, e1);
+            const int64_t c3 = a.cand_idx[at(k + 3)];
+            const int64_t e2 = extra(k + 2);
+            const int64_t x2 = author_of<A32>(a, clamp64(c2, last_doc), at(k + 2));
+            c1 = c2;
+            c2 = c3;
+            x1 = x2;
+            e1 = e2;
+        });
         lds_barrier();
+    }
+    copy(ntiles - 1, std::true_type{}, []() {});
+    lds_barrier();
+}
+
+// Pad slots of the padded layout (slot i of viewer v with i >= min(n_v, n_max)): zero bytes over
+// the row width, hit 0; and the valid mask of every slot. In blocks of 64 slots of one viewer,
+// wavefront after wavefront over the whole launch; a lane finds one block's viewer and size, so
+// the offsets of 64 blocks are read together. The chunks of a block's pad rows are written in
+// order. (A launch of its own with one thread per slot, row after row of 128 bytes per thread, took
+// 12.8 us after the join's 35.7 for 12 viewers of 41,003 slots, 57% of them pads; one launch 30.3.)
+template <int NL>
+__device__ __forceinline__ void fill_pads(const JoinArgs &a) {
+    const int lane = threadIdx.x & 63;
+    const int64_t wave = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    const int64_t waves = (int64_t)gridDim.x * (kBlock / 64);
+    const int64_t per_viewer = (a.n_max + 63) / 64;
+    const int64_t blocks = (int64_t)a.n_viewers * per_viewer;
+    const int wch = (a.doc_bytes + NL * a.edge_bytes) >> 4;
+    for (int64_t b0 = wave; b0 < blocks; b0 += 64 * waves) {
+        const int64_t mine = min(b0 + lane * waves, blocks - 1);
+        const int64_t mv = mine / per_viewer, mi = (mine - mv * per_viewer) * 64;
+        const int64_t nv = clamp64(a.cand_offsets[mv + 1], a.total_cand) -
+                           clamp64(a.cand_offsets[mv], a.total_cand);
+        const int64_t m_slot = mv * a.n_max + mi;
+        const int m_count = (int)min<int64_t>(64, a.n_max - mi);
+        const int m_used = (int)clamp64(nv - mi, m_count);
+        for (int l = 0; l < 64 && b0 + l * waves < blocks; ++l) {
+            const int count = __builtin_amdgcn_readlane(m_count, l);
+            const int used = __builtin_amdgcn_readlane(m_used, l);
+            const int64_t slot =
+                (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(m_slot >> 32), l) << 32) |
+                          (uint32_t)__builtin_amdgcn_readlane((int)m_slot, l));
+            if (lane < count)
+                a.valid[slot + lane] = lane < used ? 1 : 0;
+            if (lane >= used && lane < count)
+                for (int q = 0; q < NL; ++q)
+                    a.hit[(slot + lane) * NL + q] = 0;
+            const int chunks = (count - used) * wch;
+            uint8_t *o = a.out + (slot + used) * a.out_stride;
+            for (int c = lane; c < chunks; c += 64) {
+                const int row = c / wch;
+                const int64_t at = row * a.out_stride + (c - row * wch) * 16;
+                __builtin_nontemporal_store(chunk_t{0u, 0u, 0u, 0u},
+                                            reinterpret_cast<chunk_t *>(o + at));
+            }
+        }
     }
 }
 
@@ -565,10 +674,9 @@ __device__ __forceinline__ void full_tiles(const JoinArgs &a, int64_t (*s_src)[k
 template <int DOC_CH, int EDGE_CH, int NL, bool BATCHED, bool A32>
 __global__ __launch_bounds__(kBlock) void join_kernel(JoinArgs a) {
     extern __shared__ int64_t s_tab[];            // fence table, a.lds_keys entries
-    __shared__ int64_t s_src[2][kBlock];          // doc position of each sub-tile row, or -1
-    __shared__ int64_t s_row[2][NL][kBlock];      // global edge row per lookup, or -1
-                                                  // (two buffers: sub-tiles k and k+1)
+    __shared__ Sources<NL> s_ptr[2];              // source rows of sub-tiles k and k+1
     __shared__ unsigned int s_invalid;
+    static_assert(sizeof(Sources<NL>) >= kBlock * sizeof(int64_t), "balanced_range's scratch");
 
     const int tid = threadIdx.x;
     constexpr bool batched = BATCHED;
@@ -577,7 +685,7 @@ __global__ __launch_bounds__(kBlock) void join_kernel(JoinArgs a) {
     int64_t begin, end;
     int32_t v = 0;                                // first viewer that may hold `begin`
     if (batched && a.balanced) {
-        balanced_range(a, rng, gridDim.x, s_src[0], begin, end, v);
+        balanced_range(a, rng, gridDim.x, reinterpret_cast<int64_t *>(&s_ptr[0]), begin, end, v);
     } else {
         begin = rng * a.per_wg;
         end = min(begin + a.per_wg, a.total_cand);
@@ -594,8 +702,6 @@ __global__ __launch_bounds__(kBlock) void join_kernel(JoinArgs a) {
             v = lo;
         }
     }
-    if (begin >= end)
-        return;
     if (tid == 0)
         s_invalid = 0;
     const uint8_t *miss_row = a.def_row ? a.def_row : a.zero_row;
@@ -610,58 +716,62 @@ __global__ __launch_bounds__(kBlock) void join_kernel(JoinArgs a) {
             ke = max(kb, clamp64(a.key_offsets[v + 1], a.total_keys));
             if (a.n_max > 0) {                    // padded layout: first n_max candidates
                 ve = min(ve, vb + a.n_max);
-                shift = (int64_t)v * a.n_max - vb;
+                shift = uniform64((int64_t)v * a.n_max - vb);
             }
         }
-        const int64_t s0 = max(begin, vb);
-        const int64_t s1 = min(end, ve);
+        const int64_t s0 = uniform64(max(begin, vb));
+        const int64_t s1 = uniform64(min(end, ve));
         if (s1 <= s0)
             continue;
         begin = s1;
 
-        const int64_t K = ke - kb;
+        const int64_t K = uniform64(ke - kb);
         const int64_t *gk = a.keys + kb;
         const int S = choose_stride(K, s1 - s0, a.lds_keys, a.fence_stride, a.fence_budget);
         const int64_t M = (K + S - 1) / S;
-        // Stage the fences into LDS (after the previous segment's readers are done). Full
-        // segments stage after issuing their first loads, so the two latencies overlap.
+        // Stage the fences into LDS (after the previous segment's readers are done), after the
+        // segment's first loads are issued, so the two latencies overlap.
         auto stage = [&]() {
             lds_barrier();
             stage_fences(s_tab, gk, M, S);
             lds_barrier();
         };
-        const int64_t seg = s1 - s0;
-        if constexpr (DOC_CH > 0) {
-            if (seg >= kBlock) {
-                full_tiles<DOC_CH, EDGE_CH, NL, A32>(a, s_src, s_row, &s_invalid, s_tab, M, S, gk, K,
-                                                kb, s0, s1, shift, miss_row, stage);
-                continue;
-            }
+        if (DOC_CH > 0 || !a.wide) {
+            full_tiles<DOC_CH, EDGE_CH, NL, A32>(a, s_ptr, &s_invalid, s_tab, M, S, gk, K, kb, s0, s1,
+                                                 shift, miss_row, stage);
+            continue;
         }
-        // A segment shorter than a sub-tile (or widths without a specialisation): guarded
-        // sub-tiles, one candidate per thread.
-        stage();
-        for (int64_t t0 = s0; t0 < s1; t0 += kBlock) {
-            const int n = (int)min<int64_t>(kBlock, s1 - t0);
-            if (tid < n) {
-                const int64_t c = a.cand_idx[t0 + tid];
-                const bool ok = c >= 0 && c < a.n_docs;
-                const int64_t x0 = ok ? author_of<A32>(a, c, t0 + tid) : 0;
-                const int64_t x1 = NL == 2 ? a.extra[t0 + tid] : 0;
-                resolve_tile<NL>(a, s_src[0], s_row[0], &s_invalid, s_tab, M, S, gk, K, kb, t0,
-                                 shift, 0, c, x0, x1);
+        if constexpr (DOC_CH == 0) {
+            // Rows or strides too long for the pipeline: one sub-tile after the other.
+            stage();
+            for (int64_t t0 = s0; t0 < s1; t0 += kBlock) {
+                const int n = (int)min<int64_t>(kBlock, s1 - t0);
+                if (tid < n) {
+                    const int64_t c = a.cand_idx[t0 + tid];
+                    const bool ok = c >= 0 && c < a.n_docs;
+                    const int64_t x0 = ok ? author_of<A32>(a, c, t0 + tid) : 0;
+                    const int64_t x1 = NL == 2 ? a.extra[t0 + tid] : 0;
+                    resolve_tile<NL>(a, s_ptr[0], &s_invalid, s_tab, M, S, gk, K, kb, t0, n, shift,
+                                     nullptr, a.def_row, c, x0, x1);
+                }
+                lds_barrier();
+                copy_wide_rows<NL>(a, s_ptr[0], t0 + shift, n);
+                lds_barrier();
             }
-            lds_barrier();
-            copy_rows<DOC_CH, EDGE_CH, NL>(a, s_src[0], s_row[0], t0 + shift, n);
-            lds_barrier();
         }
     }
     lds_barrier();
     if (tid == 0 && s_invalid)
         atomicAdd(a.invalid_counter, (unsigned long long)s_invalid);
+    if constexpr (BATCHED) {
+        if (a.n_max > 0)
+            fill_pads<NL>(a);
+    }
 }
 
 constexpr int kMaxDevices = 64;
+constexpr int64_t kMinRange = 32;      // fewest candidates that a workgroup is launched for ...
+constexpr int64_t kMinShare = 64;      // ... and that the automatic grid gives one
 
 // Multiprocessor count per device (cached; devices are few).
 int cu_count(int device) {
@@ -699,15 +809,18 @@ int resident_per_cu(const void *fn, size_t lds) {
 template <int D, int E, int L, bool BATCHED, bool A32>
 hipError_t launch_one(JoinArgs &a, int32_t workgroups, int device, hipStream_t stream) {
     // The largest LDS table plus the kernel's static tables must fit a workgroup's 160 KiB.
-    static_assert(kMaxLdsKeys * sizeof(int64_t) + (2 + 2 * L) * kBlock * sizeof(int64_t) +
+    static_assert(kMaxLdsKeys * sizeof(int64_t) + 2 * sizeof(Sources<L>) +
                           sizeof(unsigned int) <= 160 * 1024,
                   "LDS budget exceeded");
     const void *fn = reinterpret_cast<const void *>(&join_kernel<D, E, L, BATCHED, A32>);
     const int64_t tiles = (a.total_cand + kBlock - 1) / kBlock;
     const int64_t cus = cu_count(device);
-    // One workgroup per CU (below): the LDS table may then hold up to kWideLdsKeys keys at no
-    // cost in occupancy, so that longer lists are staged whole.
-    if (a.lds_auto && workgroups <= 0 && L == 1 && tiles >= 2 * cus)
+    // One workgroup per CU (below), or more for smaller launches. Lists that do not fit the default
+    // table keep one: its table may then hold up to kWideLdsKeys keys at no cost in occupancy, so
+    // that longer lists are staged whole.
+    const bool long_lists = a.total_keys > (int64_t)a.n_viewers * kDefaultLdsKeys;
+    const bool one_per_cu = tiles >= 4 * cus || (tiles >= 2 * cus && long_lists);
+    if (a.lds_auto && workgroups <= 0 && L == 1 && one_per_cu)
         a.lds_keys = (int32_t)(a.total_keys < kWideLdsKeys ? (a.total_keys > 0 ? a.total_keys : 1)
                                                           : kWideLdsKeys);
     const size_t lds = (size_t)max(1, a.lds_keys) * sizeof(int64_t);
@@ -722,32 +835,40 @@ hipError_t launch_one(JoinArgs &a, int32_t workgroups, int device, hipStream_t s
     });
     if (err != hipSuccess)
         return err;
-    // Grid: each workgroup owns a contiguous range of whole sub-tiles; the count is rounded to
-    // a multiple of 8 so that each XCD gets an equal share.
+    // Grid: each workgroup owns a contiguous range; the count is rounded to a multiple of 8 so that
+    // each XCD gets an equal share.
     //   * Long key lists: one resident wave (the whole LDS table allows one workgroup per CU).
-    //   * At least two sub-tiles per CU: one workgroup per CU. Fewer, longer ranges pay the
-    //     fence staging and the pipeline's fill and drain once per CU; on launches of 300k to
-    //     3.2M candidates this beat every larger grid, by up to 17% at 400k. Two lookups per
-    //     candidate double the dependent search chain per sub-tile: two workgroups per CU then
-    //     hide it better (64 requests of 100,000 candidates: 9% faster than one).
-    //   * Smaller launches: about 1.5 resident waves, at most one workgroup per sub-tile.
+    //   * At least four sub-tiles per CU: one workgroup per CU. Fewer, longer ranges pay the
+    //     fence staging and the pipeline's fill and drain once per CU (8 requests of 50,000: 37.2
+    //     us on 256 workgroups, 37.5 on 512, 41.5 on 768). Two lookups per candidate double the
+    //     dependent search chain per sub-tile: two workgroups per CU then hide it better (64
+    //     requests of 100,000 candidates: 9% faster than one).
+    //   * More than one sub-tile per CU: two workgroups per CU, each with an equal share of one or
+    //     two sub-tiles (100,000 candidates: 12.3 us on 512 workgroups, 13.9 on 200 of two
+    //     sub-tiles, 15.4 on 768; 4 requests of 50,000: 20.4 on 512, 22.0 on 256).
+    //   * Smaller launches: an equal share for every CU, of at least kMinShare candidates (50,000
+    //     candidates: 8.8 us on 256 workgroups, 11.3 on 196 whole sub-tiles; 10,000: 6.1 on 128,
+    //     6.5 on 256, 7.4 on 320).
     int64_t n_wg = workgroups;
     if (n_wg <= 0) {
+        const int resident = resident_per_cu(fn, lds);
         if (a.one_wave)
-            n_wg = cus * resident_per_cu(fn, lds);
-        else if (tiles >= 2 * cus)
-            n_wg = cus * (L == 2 ? min(2, resident_per_cu(fn, lds)) : 1);
+            n_wg = cus * resident;
+        else if (one_per_cu)
+            n_wg = cus * (L == 2 ? std::min(2, resident) : 1);
+        else if (tiles > cus)
+            n_wg = cus * std::min(2, resident);
         else
-            n_wg = cus * resident_per_cu(fn, lds) * 3 / 2;
+            n_wg = std::min(cus, (a.total_cand + kMinShare - 1) / kMinShare);
     }
-    if (n_wg > tiles)
-        n_wg = tiles;
-    if (n_wg < 1)
-        n_wg = 1;
-    const int64_t tiles_per_wg = (tiles + n_wg - 1) / n_wg;
-    a.per_wg = tiles_per_wg * kBlock;
-    if (!a.balanced)                      // equal ranges of whole sub-tiles, none left empty
-        n_wg = (a.total_cand + a.per_wg - 1) / a.per_wg;
+    // The padded layout's slots are filled by the same launch: 8 blocks of 64 per wavefront.
+    const int64_t fill = a.n_max > 0 ? (int64_t)a.n_viewers * ((a.n_max + 63) / 64) / 32 : 0;
+    const int64_t least = std::max<int64_t>(1, std::min(cus, fill));
+    const int64_t most = (a.total_cand + kMinRange - 1) / kMinRange;
+    n_wg = std::max(least, std::min(n_wg, most));
+    a.per_wg = (a.total_cand + n_wg - 1) / n_wg;
+    if (!a.balanced && a.per_wg > 0)      // none left empty
+        n_wg = std::max(least, (a.total_cand + a.per_wg - 1) / a.per_wg);
     n_wg = (n_wg + 7) & ~int64_t(7);
     a.n_wg = (int32_t)n_wg;
     hipLaunchKernelGGL((join_kernel<D, E, L, BATCHED, A32>), dim3(a.n_wg), dim3(kBlock), lds, stream,
@@ -767,31 +888,14 @@ hipError_t launch_form(JoinArgs &a, int32_t wgs, int device, hipStream_t stream)
 template <int L>
 hipError_t dispatch_widths(JoinArgs &a, int32_t wgs, int device, hipStream_t stream) {
     const int d = a.doc_bytes >> 4, e = a.edge_bytes >> 4;
+    // A sub-tile's output offsets fit a buffer's 32 bits, and absent rows the zero row.
+    const bool far = a.out_stride > kMaxTileStride;
+    a.wide = far || a.doc_bytes > kZeroRowBytes || a.edge_bytes > kZeroRowBytes;
+    if (far) return launch_form<0, 0, L>(a, wgs, device, stream);
     if (d == 4 && e == 2) return launch_form<4, 2, L>(a, wgs, device, stream);
     if (d == 8 && e == 4) return launch_form<8, 4, L>(a, wgs, device, stream);
     if (d == 8 && e == 8) return launch_form<8, 8, L>(a, wgs, device, stream);
     return launch_form<0, 0, L>(a, wgs, device, stream);
-}
-
-// Padded layout: slot r = v * n_max + i is a candidate's slot when i < min(n_v, n_max). Writes
-// the valid mask of every slot; a pad slot also gets zero bytes over the row width and hit 0.
-__global__ void pad_fill_kernel(JoinArgs a, int NL, int width_chunks, int8_t *valid) {
-    const int64_t slots = (int64_t)a.n_viewers * a.n_max;
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < slots;
-         r += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t v = r / a.n_max, i = r - v * a.n_max;
-        const int64_t nv = clamp64(a.cand_offsets[v + 1], a.total_cand) -
-                           clamp64(a.cand_offsets[v], a.total_cand);
-        const bool used = i < nv;
-        valid[r] = used ? 1 : 0;
-        if (!used) {
-            for (int l = 0; l < NL; ++l)
-                a.hit[r * NL + l] = 0;
-            chunk_t *o = reinterpret_cast<chunk_t *>(a.out + r * a.out_stride);
-            for (int q = 0; q < width_chunks; ++q)
-                o[q] = chunk_t{0u, 0u, 0u, 0u};
-        }
-    }
 }
 
 __global__ void validate_keys_kernel(const int64_t *key_offsets, const int64_t *keys,
@@ -814,19 +918,6 @@ hipError_t launch_join(JoinArgs &a, int n_lookups, int32_t workgroups, int devic
                        hipStream_t stream) {
     return n_lookups == 2 ? dispatch_widths<2>(a, workgroups, device, stream)
                           : dispatch_widths<1>(a, workgroups, device, stream);
-}
-
-hipError_t launch_pad_fill(const JoinArgs &a, int n_lookups, int8_t *valid_mask,
-                           hipStream_t stream) {
-    const int64_t slots = (int64_t)a.n_viewers * a.n_max;
-    if (slots <= 0)
-        return hipSuccess;
-    const int64_t blocks = (slots + 255) / 256;
-    const int grid = (int)(blocks < 8192 ? blocks : 8192);
-    const int width_chunks = (a.doc_bytes + n_lookups * a.edge_bytes) / 16;
-    hipLaunchKernelGGL(pad_fill_kernel, dim3(grid), dim3(256), 0, stream, a, n_lookups,
-                       width_chunks, valid_mask);
-    return hipGetLastError();
 }
 
 hipError_t launch_validate_keys(const int64_t *key_offsets, const int64_t *keys,
