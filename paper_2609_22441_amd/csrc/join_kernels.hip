@@ -217,10 +217,15 @@ __device__ __forceinline__ void find_key_pair(int64_t x0, int64_t x1, bool valid
 }
 
 // Fence stride for one segment: the smallest power of two whose fence count fits the LDS
-// table and is not much larger than the number of candidates that will use it.
+// table and is not much larger than the number of candidates that will use it. A segment of any
+// size may have kStageBatch fences: they are staged by one round of loads. (17,187 candidates in
+// shares of 67, two lookups into 68,767 keys: 22.2 us with at least 512 fences, 17.1 with 4,096.)
+constexpr int kStageUnroll = 16;
+constexpr int64_t kStageBatch = kStageUnroll * kBlock;
+
 __device__ __forceinline__ int choose_stride(int64_t K, int64_t seg_len, int32_t cap,
                                              int32_t forced, int32_t per_cand) {
-    int64_t budget = forced > 0 ? cap : min<int64_t>(cap, max<int64_t>(512, per_cand * seg_len));
+    int64_t budget = forced > 0 ? cap : min<int64_t>(cap, max<int64_t>(kStageBatch, per_cand * seg_len));
     int S = forced > 0 ? forced : 1;
     while ((K + S - 1) / S > budget)
         S <<= 1;
@@ -505,7 +510,7 @@ __device__ __forceinline__ void copy_wide_rows(const JoinArgs &a, const Sources<
 // clamped to M - 1; the repeated writes of the last fence store the same value).
 __device__ __forceinline__ void stage_fences(int64_t *s_tab, const int64_t *gk, int64_t M, int S) {
     const int tid = threadIdx.x;
-    constexpr int U = 16;
+    constexpr int U = kStageUnroll;
     for (int64_t i0 = 0; i0 < M; i0 += U * kBlock) {
         int64_t f[U];
 #pragma unroll
@@ -848,18 +853,22 @@ hipError_t launch_one(JoinArgs &a, int32_t workgroups, int device, hipStream_t s
     //     sub-tiles, 15.4 on 768; 4 requests of 50,000: 20.4 on 512, 22.0 on 256).
     //   * Smaller launches: an equal share for every CU, of at least kMinShare candidates (50,000
     //     candidates: 8.8 us on 256 workgroups, 11.3 on 196 whole sub-tiles; 10,000: 6.1 on 128,
-    //     6.5 on 256, 7.4 on 320).
+    //     6.5 on 256, 7.4 on 320), or of one per 128 keys up to a sub-tile: every share stages its
+    //     viewer's fences, a line each (17,187 candidates, two lookups into 68,767 keys: 17.3 us
+    //     in sub-tiles, 22.6 in shares of 67).
     int64_t n_wg = workgroups;
     if (n_wg <= 0) {
         const int resident = resident_per_cu(fn, lds);
+        const int64_t share = std::min<int64_t>(
+            kBlock, std::max<int64_t>(kMinShare, a.total_keys / std::max(1, a.n_viewers) / 128));
         if (a.one_wave)
-            n_wg = cus * resident;
+            n_wg = std::min(cus * resident, (a.total_cand + share - 1) / share);
         else if (one_per_cu)
             n_wg = cus * (L == 2 ? std::min(2, resident) : 1);
         else if (tiles > cus)
             n_wg = cus * std::min(2, resident);
         else
-            n_wg = std::min(cus, (a.total_cand + kMinShare - 1) / kMinShare);
+            n_wg = std::min(cus, (a.total_cand + share - 1) / share);
     }
     // The padded layout's slots are filled by the same launch: 8 blocks of 64 per wavefront.
     const int64_t fill = a.n_max > 0 ? (int64_t)a.n_viewers * ((a.n_max + 63) / 64) / 32 : 0;
