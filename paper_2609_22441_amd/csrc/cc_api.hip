@@ -442,6 +442,8 @@ cc_status cc_store_upsert(cc_store *store, int64_t n_records, const int64_t *doc
     DeviceGuard guard(store->device);
     if (guard.error() != hipSuccess)
         return device_error(guard.error());
+    volatile int64_t *counts = store->h_counts;   // pinned: written by the batch's last kernel
+    counts[3] = 0;
     hipError_t e = ccj::launch_upsert_claim(store->d_map, store->map_groups, doc_ids, n_records,
                                             workspace,
                                             g_wait_polls.load(std::memory_order_relaxed), stream);
@@ -449,11 +451,7 @@ cc_status cc_store_upsert(cc_store *store, int64_t n_records, const int64_t *doc
         e = ccj::launch_upsert_finish(store->d_map, n_records, workspace, store->n_docs,
                                       store->capacity, author_ids, doc_rows,
                                       store->doc_row_bytes, store->d_author, store->d_author32,
-                                      store->d_rows, stream);
-    int64_t *counts = store->h_counts;        // pinned: the read-back is one small DMA
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(counts, ccj::upsert_counts(workspace, n_records),
-                           ccj::kUpsertCounts * sizeof(int64_t), hipMemcpyDeviceToHost, stream);
+                                      store->d_rows, store->compact, store->h_counts, stream);
     if (e == hipSuccess)
         e = hipStreamSynchronize(stream);
     if (e != hipSuccess)

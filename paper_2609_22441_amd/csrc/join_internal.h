@@ -167,21 +167,22 @@ hipError_t launch_map_init(MapEntry *map, int64_t n_groups, hipStream_t stream);
 hipError_t launch_resolve(const MapEntry *map, int64_t n_groups, const int64_t *ids, int64_t n,
                           int64_t *pos, hipStream_t stream);
 
-// Ingestion batch in two launches: claim (map entries for every id, first/last occurrence,
-// ranks of the new ids, and kUpsertCounts counts at upsert_counts(ws, n): n_new, n_rejected,
-// n_unplaced, n_wide_authors, the scan's tile counter, waits that reached their bound),
-// then finish: when the batch fits (nothing unplaced, no bounded wait given up and
-// n_old + n_new <= capacity) scatter the rows and commit the map, otherwise roll the claim
-// back. The decision is taken on the device from the counts.
+// Ingestion batch in two steps: claim (map entries for every id, first/last occurrence, ranks of
+// the new ids, and the counts n_new, n_rejected, n_unplaced, -, the scan's tile counter, waits that
+// reached their bound), then finish: when the batch fits (nothing unplaced, no bounded wait given
+// up and n_old + n_new <= capacity) scatter the rows and commit the map, otherwise roll the claim
+// back. The decision is taken on the device from the counts. The finish writes the counts to
+// host_counts (pinned, kUpsertCounts entries); host_counts[3] becomes 1, from the caller's 0, when
+// `compact` and an author id wider than 32 bits was stored.
 constexpr int kUpsertCounts = 6;
 constexpr int32_t kDefaultWaitPolls = 1 << 16;   // bound on each device-side wait of a batch
 int64_t upsert_workspace_bytes(int64_t n);
-int64_t *upsert_counts(void *workspace, int64_t n);
 hipError_t launch_upsert_claim(MapEntry *map, int64_t n_groups, const int64_t *ids, int64_t n,
                                void *workspace, int32_t max_polls, hipStream_t stream);
 hipError_t launch_upsert_finish(MapEntry *map, int64_t n, void *workspace, int64_t n_old,
                                 int64_t capacity, const int64_t *author_in, const void *rows_in,
                                 int32_t row_bytes, int64_t *author, int32_t *author32,
-                                uint8_t *rows, hipStream_t stream);
+                                uint8_t *rows, bool compact, int64_t *host_counts,
+                                hipStream_t stream);
 
 }  // namespace ccj

@@ -23,12 +23,10 @@
 //            (one pass, tiles chained by decoupled look-back) gives each new id its rank, in
 //            batch order.
 //   apply:   the last occurrence of every id copies its row and author id to the stored
-//            position or to n_old + rank; then the first occurrence commits pos and every
-//            record clears aux.
-//   rollback (batch does not fit): pending entries are freed again, aux is cleared.
+//            position or to n_old + rank; the first occurrence commits pos, the last clears aux;
+//            or (batch does not fit) pending entries are freed again, aux is cleared.
 // Whether the batch fits (every id placed, n_old + n_new <= capacity) is decided on the device
-// from the claim's counts: apply and rollback are both enqueued and each does nothing unless
-// it is the one that applies, so a batch needs a single synchronisation at its end.
+// from the claim's counts, so a batch needs a single synchronisation at its end.
 #include <stdint.h>
 
 #include <hip/hip_runtime.h>
@@ -48,9 +46,11 @@ __host__ __device__ inline int scan_per(int64_t n) {
     return n >= kScanLargeFrom ? kScanPerLarge : kScanPerSmall;
 }
 constexpr uint64_t kMaxProbeGroups = 64;
-// counts[]: new ids, rejected records, unplaced ids, author ids wider than 32 bits, the scan's
-// tile counter, waits (of the claim or the scan) that reached their bound of max_polls polls.
+// counts[]: new ids, rejected records, unplaced ids, (host copy only) whether an author id wider
+// than 32 bits was stored, the scan's tile counter, waits (of the claim or the scan) that reached
+// their bound of max_polls polls.
 constexpr int kCounts = kUpsertCounts;
+constexpr int kWideCount = 3;
 static_assert(kCounts * 8 <= 256, "the counts live in the workspace's last 256 bytes");
 
 typedef unsigned int chunk_t __attribute__((ext_vector_type(4)));
@@ -331,11 +331,6 @@ __global__ __launch_bounds__(kThreads) void claim_kernel(MapEntry *map, uint64_t
     }
 }
 
-// Record i is the first occurrence of an id that is new in this batch (posv already read).
-__device__ __forceinline__ int32_t first_new(const Ws &w, int64_t i) {
-    return w.posv[i] == -(3 + (int32_t)i) ? 1 : 0;
-}
-
 // Look-back word of one scan tile: flag in the top two bits (0 = not yet published, kAgg = the
 // tile's own count of new ids, kInc = the count over this and every earlier tile), the count
 // below them.
@@ -518,38 +513,60 @@ __device__ __forceinline__ bool batch_fits(const Ws &w, int64_t n_old, int64_t c
     return w.counts[2] == 0 && w.counts[5] == 0 && n_old + w.counts[0] <= capacity;
 }
 
-__global__ void rollback_kernel(MapEntry *map, int64_t n, Ws w, int64_t n_old, int64_t capacity) {
-    if (batch_fits(w, n_old, capacity))
-        return;
-    for (int64_t i = global_id(); i < n; i += grid_stride()) {
-        const int64_t s = w.slot[i];
-        if (s < 0)
-            continue;
-        if (map[s].pos < 0) {                     // pending: claimed by this batch
-            map[s].key = kEmptyKey;
-            map[s].pos = kNoPos;
-        }
-        map[s].aux = -1;
-    }
+// The batch's last launch, which also hands the counts to the host (its stores reach the pinned
+// array by the end of the kernel, so the caller's synchronisation needs no copy behind it).
+//
+// When the batch fits: the last occurrence of each id writes its row and author id, at the stored
+// position or at n_old + the rank of the id's first record, and the map changes: the first record
+// of a new id stores its position, the last record of every id clears the entry's pending mark. A
+// thread takes kScatterPer 16-byte chunks of its grid-stride sequence at a time and issues their
+// loads in three rounds (last marks; position fields, row chunks, author ids and map slots;
+// ranks of new ids), so that each round trip serves kScatterPer chunks; a chunk's record and
+// column advance by the stride without a division. The thread of a record's column 0 changes the
+// map after its chunk; no reader may overlap a batch, so the order across threads is free.
+// Otherwise the claim is rolled back: pending entries are freed, aux is cleared.
+//
+// Scatter, commit and rollback as launches of their own took 29.0 + 6.9 + 4.9 us for a batch of
+// 300,000 records (most of the last two their launch and drain), one launch 32.5. COMMIT = false
+// leaves the map's update to commit_kernel: from kCommitApartFrom records on, where the launch no
+// longer counts, the map's random writes cost more between the row writes (10M records in one
+// launch 1,065 us, in two 551 + 316).
+constexpr int kScatterPer = 4;
+constexpr int64_t kCommitApartFrom = 1 << 21;     // records
+
+__device__ __forceinline__ void put_host(int64_t *p, int64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// The last occurrence of each id writes its row and author id, at the stored position or at
-// n_old + the rank of the id's first record. A thread takes kScatterPer 16-byte chunks of its
-// grid-stride sequence at a time and issues their loads in three rounds (last marks; position
-// fields, row chunks and author ids; ranks of new ids), so that each round trip serves
-// kScatterPer chunks; a chunk's record and column advance by the stride without a division.
-constexpr int kScatterPer = 4;
-
-__global__ __launch_bounds__(kThreads) void scatter_kernel(int64_t n, Ws w,
-                                                           int64_t n_old, int64_t capacity,
-                                                           const int64_t *__restrict__ author_in,
-                                                           const chunk_t *__restrict__ rows_in,
-                                                           int32_t chunks,
-                                                           int64_t *__restrict__ author,
-                                                           int32_t *__restrict__ author32,
-                                                           chunk_t *__restrict__ rows) {
-    if (!batch_fits(w, n_old, capacity))
+template <bool COMMIT>
+__global__ __launch_bounds__(kThreads) void apply_kernel(MapEntry *map, int64_t n, Ws w,
+                                                         int64_t n_old, int64_t capacity,
+                                                         const int64_t *__restrict__ author_in,
+                                                         const chunk_t *__restrict__ rows_in,
+                                                         int32_t chunks,
+                                                         int64_t *__restrict__ author,
+                                                         int32_t *__restrict__ author32,
+                                                         chunk_t *__restrict__ rows,
+                                                         bool compact, int64_t *host_counts) {
+    __shared__ int s_wide;                        // an author id wider than 32 bits was stored
+    if (threadIdx.x == 0)
+        s_wide = 0;
+    if (blockIdx.x == 0 && threadIdx.x < kCounts && threadIdx.x != kWideCount)
+        put_host(host_counts + threadIdx.x, w.counts[threadIdx.x]);
+    __syncthreads();
+    if (!batch_fits(w, n_old, capacity)) {
+        for (int64_t i = global_id(); i < n; i += grid_stride()) {
+            const int64_t s = w.slot[i];
+            if (s < 0)
+                continue;
+            if (map[s].pos < 0) {                 // pending: claimed by this batch
+                map[s].key = kEmptyKey;
+                map[s].pos = kNoPos;
+            }
+            map[s].aux = -1;
+        }
         return;
+    }
     constexpr int U = kScatterPer;
     const int64_t total = n * chunks;
     const int64_t stride = grid_stride();
@@ -573,47 +590,63 @@ __global__ __launch_bounds__(kThreads) void scatter_kernel(int64_t n, Ws w,
                 ++i;
             }
         }
-        bool carry[U];
+        bool last[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            carry[u] = in[u] && w.last[rec[u]];   // a later record carries this id's row
+            last[u] = in[u] && w.last[rec[u]];    // else a later record carries this id's row
         int32_t pv[U];
         chunk_t c[U];
-        int64_t x[U];
+        int64_t x[U], slot[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             pv[u] = 0;
-            x[u] = 0;
-            if (carry[u]) {
-                pv[u] = w.posv[rec[u]];
+            slot[u] = -1;
+            if (last[u])
                 c[u] = rows_in[rec[u] * chunks + col[u]];
-                if (col[u] == 0)
-                    x[u] = author_in[rec[u]];
-            }
+            const bool head = in[u] && col[u] == 0;   // the thread that changes the map
+            if (last[u] || (COMMIT && head))
+                pv[u] = w.posv[rec[u]];
+            if (last[u] && head)
+                x[u] = author_in[rec[u]];
+            if (COMMIT && head)
+                slot[u] = w.slot[rec[u]];
         }
         int64_t target[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            target[u] = !carry[u] || pv[u] >= 0 ? (int64_t)pv[u]
-                                                : n_old + w.rank[-(int64_t)pv[u] - 3];
+            target[u] = pv[u] >= 0 || pv[u] == kNoPos ? (int64_t)pv[u]
+                                                      : n_old + w.rank[-(int64_t)pv[u] - 3];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (!carry[u])
-                continue;
-            rows[target[u] * chunks + col[u]] = c[u];
-            if (col[u] == 0) {
+            if (last[u])
+                rows[target[u] * chunks + col[u]] = c[u];
+            if (last[u] && col[u] == 0) {
                 author[target[u]] = x[u];
                 author32[target[u]] = (int32_t)x[u];
-                if (x[u] < INT32_MIN || x[u] > INT32_MAX)
-                    atomicAdd(reinterpret_cast<unsigned long long *>(&w.counts[3]), 1ULL);
+                if (compact && (x[u] < INT32_MIN || x[u] > INT32_MAX))
+                    s_wide = 1;
+            }
+            if (!COMMIT || slot[u] < 0)           // another column, or a record without an entry
+                continue;
+            const bool first = pv[u] == -(3 + (int32_t)rec[u]);
+            MapEntry *e = map + slot[u];
+            if (first && last[u]) {
+                typedef int pair_t __attribute__((ext_vector_type(2)));
+                *reinterpret_cast<pair_t *>(&e->pos) = pair_t{(int32_t)target[u], -1};
+            } else if (first) {
+                e->pos = (int32_t)target[u];
+            } else if (last[u]) {
+                e->aux = -1;
             }
         }
     }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_wide)
+        put_host(host_counts + kWideCount, 1);
 }
 
-// The map changes only now, after the rows are written: the first record of a new id stores
-// its position, the last record of every id clears the entry's pending mark. Nothing is read
-// from the map.
+// The map's update for large batches: the first record of a new id stores its position, the last
+// record of every id clears the entry's pending mark. Nothing is read from the map.
 __global__ void commit_kernel(MapEntry *map, int64_t n, Ws w, int64_t n_old, int64_t capacity) {
     if (!batch_fits(w, n_old, capacity))
         return;
@@ -621,7 +654,7 @@ __global__ void commit_kernel(MapEntry *map, int64_t n, Ws w, int64_t n_old, int
         const int64_t s = w.slot[i];
         if (s < 0)
             continue;
-        const bool first = first_new(w, i) != 0, last = w.last[i] != 0;
+        const bool first = w.posv[i] == -(3 + (int32_t)i), last = w.last[i] != 0;
         const int32_t pos = (int32_t)(n_old + w.rank[i]);
         if (first && last) {
             typedef int pair_t __attribute__((ext_vector_type(2)));
@@ -707,8 +740,6 @@ int64_t upsert_workspace_bytes(int64_t n) {
     return round_up(n * 8) + 2 * round_up(n * 4) + 2 * round_up(n) + round_up(blocks * 8) + 256;
 }
 
-int64_t *upsert_counts(void *workspace, int64_t n) { return carve(workspace, n).counts; }
-
 hipError_t launch_upsert_claim(MapEntry *map, int64_t n_groups, const int64_t *ids, int64_t n,
                                void *workspace, int32_t max_polls, hipStream_t stream) {
     const Ws w = carve(workspace, n);
@@ -734,27 +765,23 @@ hipError_t launch_upsert_claim(MapEntry *map, int64_t n_groups, const int64_t *i
 hipError_t launch_upsert_finish(MapEntry *map, int64_t n, void *workspace, int64_t n_old,
                                 int64_t capacity, const int64_t *author_in, const void *rows_in,
                                 int32_t row_bytes, int64_t *author, int32_t *author32,
-                                uint8_t *rows, hipStream_t stream) {
+                                uint8_t *rows, bool compact, int64_t *host_counts,
+                                hipStream_t stream) {
     if (n <= 0)
         return hipSuccess;
     const Ws w = carve(workspace, n);
     const int32_t chunks = row_bytes / 16;
-    hipLaunchKernelGGL(scatter_kernel, dim3(grid_for(n * chunks, kThreads * kScatterPer)),
-                       dim3(kThreads), 0,
-                       stream, n, w, n_old, capacity, author_in,
+    const bool apart = n >= kCommitApartFrom;
+    hipLaunchKernelGGL(apart ? apply_kernel<false> : apply_kernel<true>,
+                       dim3(grid_for(n * chunks, kThreads * kScatterPer)), dim3(kThreads), 0,
+                       stream, map, n, w, n_old, capacity, author_in,
                        static_cast<const chunk_t *>(rows_in), chunks, author, author32,
-                       reinterpret_cast<chunk_t *>(rows));
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
+                       reinterpret_cast<chunk_t *>(rows), compact, host_counts);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !apart)
         return e;
     hipLaunchKernelGGL(commit_kernel, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, stream, map,
                        n, w, n_old, capacity);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
-    // The rollback runs only for a batch that does not fit; otherwise every workgroup returns at
-    // once, so a small grid (grid-stride over the records) keeps that no-op launch short.
-    hipLaunchKernelGGL(rollback_kernel, dim3(grid_for(n, kThreads * 64)), dim3(kThreads), 0, stream,
-                       map, n, w, n_old, capacity);
     return hipGetLastError();
 }
 

@@ -556,3 +556,92 @@ def test_probe_limit_refuses_the_batch_and_keeps_the_store():
     assert (fresh.resolve(ids, "refused first batch") == -1).all()
     idx.close()
     fresh.close()
+
+
+def test_batch_that_commits_apart_from_its_rows():
+    """2^21 + 3 records (the map's update is a launch of its own from 2^21 on): stored, new and
+    repeated ids and a reserved one, checked in full against a replay; then one that does not fit
+    leaves the store as it was."""
+    n, base = (1 << 21) + 3, 100_000
+    note(f"ingestion: {n} records, the map updated by a launch of its own")
+    g = torch.Generator(device=DEV).manual_seed(5)
+    store = P.cc_store_create_indexed(base + n, 16)
+    try:
+        ws = torch.empty(P.cc_upsert_workspace_bytes(2 * n), dtype=torch.uint8, device=DEV)
+
+        def upsert(items):
+            ids = items * 7_919 + 13
+            ids = torch.where(items < 0, torch.full_like(ids, -(1 << 63)), ids)
+            auth = torch.randint(0, 1 << 30, (items.numel(),), device=DEV, generator=g)
+            rows = torch.randint(0, 1 << 60, (items.numel(), 2), device=DEV, generator=g)
+            return auth, rows, P.cc_store_upsert(store, ids, auth, rows, ws)
+
+        a0, r0, got = upsert(torch.arange(base, device=DEV))
+        assert got == (base, 0)
+        items = torch.randint(0, base + n // 2, (n,), device=DEV, generator=g)
+        items[n // 3] = -1                       # the reserved id
+        a1, r1, (n_new, n_rej) = upsert(items)
+        it, first = np.unique(items.cpu().numpy(), return_index=True)
+        keep = it >= base
+        assert (n_new, n_rej) == (int(keep.sum()), 1)
+        order = it[keep][np.argsort(first[keep], kind="stable")]       # by first record
+        pos = {}
+        want_a, want_r = torch.cat([a0.cpu(), torch.zeros(n_new, dtype=torch.int64)]), \
+            torch.cat([r0.cpu(), torch.zeros(n_new, 2, dtype=torch.int64)])
+        rank = np.full(base + n, -1, np.int64)
+        rank[:base] = np.arange(base)
+        rank[order] = base + np.arange(n_new)
+        src = items.cpu().numpy()
+        ok = src >= 0
+        target = rank[src[ok]]
+        last = np.full(base + n_new, -1, np.int64)
+        np.maximum.at(last, target, np.flatnonzero(ok))                # the last record wins
+        hit = torch.from_numpy(last >= 0)
+        want_a[hit] = a1.cpu()[torch.from_numpy(last[last >= 0])]
+        want_r[hit] = r1.cpu()[torch.from_numpy(last[last >= 0])]
+
+        def read():
+            m = P.cc_store_info(store)[0]
+            a = torch.empty(m, dtype=torch.int64, device=DEV)
+            r = torch.empty(m, 2, dtype=torch.int64, device=DEV)
+            P.cc_store_read(store, 0, m, a, r)
+            q = torch.arange(base + n, device=DEV) * 7_919 + 13
+            p = torch.empty_like(q)
+            P.cc_resolve_ids(store, q, p)
+            return a.cpu(), r.cpu(), p.cpu().numpy()
+
+        a, r, p = read()
+        assert torch.equal(a, want_a) and torch.equal(r, want_r)
+        assert np.array_equal(p, rank)
+        with pytest.raises(P.CCError) as e:
+            upsert(torch.arange(base + n, base + 3 * n, device=DEV))
+        assert e.value.status == P.CC_ERR_STORE_FULL
+        a2, r2, p2 = read()
+        assert torch.equal(a2, want_a) and torch.equal(r2, want_r) and np.array_equal(p2, rank)
+    finally:
+        P.cc_store_destroy(store)
+
+
+@pytest.mark.parametrize("n", [1, 300_000])
+def test_wide_author_ids_are_noticed_once_stored(n):
+    """An author id wider than 32 bits in one record of a batch turns the joins to the 64-bit
+    column; one in a record that a later record of the same id replaces does not."""
+    note(f"ingestion: wide author id, {n} records")
+    store = P.cc_store_create_indexed(2 * n + 2, 16)
+    try:
+        ws = torch.empty(P.cc_upsert_workspace_bytes(n + 1), dtype=torch.uint8, device=DEV)
+        ids = torch.arange(n + 1, device=DEV)
+        ids[n] = 0                               # repeats record 0
+        auth = torch.arange(n + 1, device=DEV)
+        auth[0] = 1 << 40                        # replaced by record n
+        rows = torch.zeros(n + 1, 16, dtype=torch.uint8, device=DEV)
+        P.cc_store_upsert(store, ids, auth, rows, ws)
+        assert P.cc_store_layout(store)[0] == 4
+        auth[n] = -(1 << 40)
+        P.cc_store_upsert(store, ids, auth, rows, ws)
+        assert P.cc_store_layout(store)[0] == 8
+        out = torch.empty(1, dtype=torch.int64, device=DEV)
+        P.cc_store_read(store, 0, 1, out)
+        assert int(out[0]) == -(1 << 40)
+    finally:
+        P.cc_store_destroy(store)
