@@ -54,6 +54,10 @@ _lib = None
 
 def lib():
     """Load libccjoin.so (no fallback: raises if it has not been built)."""
+    return _lib or _load()
+
+
+def _load():
     global _lib
     if _lib is None:
         if not LIB_PATH.exists():
@@ -101,8 +105,25 @@ def lib():
         L.cc_sort_workspace_bytes.restype = i64
         L.cc_upsert_workspace_bytes.argtypes = [i64]
         L.cc_upsert_workspace_bytes.restype = i64
+        # Native marshalling of the hot entry points (csrc/marshal.c) takes function addresses.
+        L.marshal = _load_marshal()
+        for name in ("cc_store_info", "cc_join", "cc_join_batched", "cc_join_batched_authors",
+                     "cc_join_batched_padded", "cc_resolve_ids", "cc_sort_affinity_method",
+                     "cc_store_upsert"):
+            setattr(L, "at_" + name, ctypes.cast(getattr(L, name), vp).value)
         _lib = L
     return _lib
+
+
+def _load_marshal():
+    import torch
+    try:
+        from . import _marshal
+    except ImportError as e:
+        raise RuntimeError("the package's _marshal module is not built; run "
+                           "__graft_entry__.build() first") from e
+    _marshal.init(torch.Tensor, torch.int64, torch.int8, _current_stream)
+    return _marshal
 
 
 def cc_status_string(status: int) -> str:
@@ -126,10 +147,11 @@ def _current_stream() -> int:
     a tenth of building a Stream object (about 0.3 us against 3 us per call); the public call
     is the fallback where the query is missing."""
     global _RAW_STREAM
-    import torch
     if _RAW_STREAM is None:
+        import torch
         raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        _RAW_STREAM = (lambda: raw(torch.cuda.current_device())) if raw is not None else \
+        device = torch.cuda.current_device
+        _RAW_STREAM = (lambda: raw(device())) if raw is not None else \
             (lambda: torch.cuda.current_stream().cuda_stream)
     return _RAW_STREAM()
 
@@ -154,7 +176,8 @@ def _prod(xs):
 # with it, or a strided view would reach a kernel as an out-of-bounds or unmapped access, so
 # every tensor argument is checked here before the call: element type, dense layout, length
 # and GPU residency. Offsets and keys held in device memory are not read here; the kernels
-# clamp them.
+# clamp them. The hot entry points first try the same checks in native code (L.marshal), which
+# answers None for anything but plain tensors that pass them; the checks here then decide.
 
 def _fail(name: str, what: str, exc=ValueError):
     raise exc(f"{name}: {what}")
@@ -313,6 +336,12 @@ def cc_store_upsert(store: int, doc_ids, author_ids, doc_rows, workspace, stream
     """Apply one ingestion batch (§6.2); returns (n_new, n_rejected). Synchronises the stream.
     Raises CCError with status CC_ERR_STORE_FULL (store unchanged) when the batch does not fit,
     CC_ERR_TIMEOUT (store unchanged) when a bounded device-side wait gave up."""
+    L = _lib or _load()
+    done = L.marshal.upsert(L.at_cc_store_upsert, L.at_cc_store_info, store, doc_ids, author_ids,
+                            doc_rows, workspace, stream)
+    if done is not None:
+        _check(done[0], "cc_store_upsert")
+        return done[1], done[2]
     n = doc_ids.numel()
     pi = _arr(doc_ids, "doc_ids", _i64())
     pa = _arr(author_ids, "author_ids", _i64(), n)
@@ -337,6 +366,10 @@ def cc_store_read(store: int, first: int, count: int, author_out=None, rows_out=
 
 def cc_resolve_ids(store: int, doc_ids, positions, stream=None) -> None:
     """Eq. 6 (§6.3.1): positions[i] = store position of doc_ids[i], or -1."""
+    L = _lib or _load()
+    st = L.marshal.resolve(L.at_cc_resolve_ids, store, doc_ids, positions, stream)
+    if st is not None:
+        return _check(st, "cc_resolve_ids")
     n = doc_ids.numel()
     pi = _arr(doc_ids, "doc_ids", _i64())
     pp = _arr(positions, "positions", _i64(), n)
@@ -384,6 +417,11 @@ def _edge_args(edge_keys, edge_feats, tk: int, default_row):
 def cc_join(store: int, cand_idx, edge_keys, edge_feats, out, hit_mask, default_row=None,
             stream=None) -> None:
     """One viewer (see include/cc_join.h). out is [n_cand, >= doc+edge bytes] (any dtype)."""
+    L = _lib or _load()
+    st = L.marshal.join(L.at_cc_join, L.at_cc_store_info, store, cand_idx, edge_keys, edge_feats,
+                        out, hit_mask, default_row, stream)
+    if st is not None:
+        return _check(st, "cc_join")
     n = cand_idx.numel()
     pc = _arr(cand_idx, "cand_idx", _i64())
     pk, pf, pd, ew = _edge_args(edge_keys, edge_feats, edge_keys.numel(), default_row)
@@ -504,6 +542,17 @@ def cc_join_batched(store: int, cand_offsets, cand_idx, key_offsets, edge_keys, 
     """B viewers in CSR form, 1 + len(extra_keys) lookups (see include/cc_join.h). With
     `author_ids` ([total_cand] int64), lookup 0 searches the caller's author id of each
     candidate instead of the store's (cc_join_batched_authors)."""
+    if total_cand is None and total_keys is None and tuning is None and (
+            not extra_keys or len(extra_keys) == 1):
+        L = _lib or _load()
+        st = L.marshal.batched(L.at_cc_join_batched, L.at_cc_join_batched_authors,
+                               L.at_cc_store_info, store, cand_offsets, cand_idx, key_offsets,
+                               edge_keys, edge_feats, default_row,
+                               extra_keys[0] if extra_keys else None, stream, out, hit_mask,
+                               author_ids)
+        if st is not None:
+            return _check(st, "cc_join_batched" if author_ids is None
+                          else "cc_join_batched_authors")
     B, L, tc, tk, pco, pc, pko, pk, pf, pd, ex, ew = _batched_args(
         store, cand_offsets, cand_idx, key_offsets, edge_keys, edge_feats, default_row,
         extra_keys, total_cand, total_keys)
@@ -532,6 +581,14 @@ def cc_join_batched_padded(store: int, cand_offsets, cand_idx, key_offsets, edge
                            stream=None) -> None:
     """B viewers written into the padded [B, n_max] layout (see include/cc_join.h). out is
     [B, n_max, >= row bytes] or [B * n_max, >= row bytes]."""
+    if total_cand is None and total_keys is None and (not extra_keys or len(extra_keys) == 1):
+        L = _lib or _load()
+        st = L.marshal.padded(L.at_cc_join_batched_padded, L.at_cc_store_info, store, cand_offsets,
+                              cand_idx, key_offsets, edge_keys, edge_feats, default_row,
+                              extra_keys[0] if extra_keys else None, stream, n_max, out, hit_mask,
+                              valid_mask)
+        if st is not None:
+            return _check(st, "cc_join_batched_padded")
     B, L, tc, tk, pco, pc, pko, pk, pf, pd, ex, ew = _batched_args(
         store, cand_offsets, cand_idx, key_offsets, edge_keys, edge_feats, default_row,
         extra_keys, total_cand, total_keys)
@@ -559,6 +616,13 @@ def cc_sort_affinity(key_offsets, keys_in, rows_in, keys_out, rows_out, workspac
     """Stable per-viewer sort of affinity records (Alg. 1 Step 1; see include/cc_join.h).
     With the defaults this is cc_sort_affinity; a `method` (CC_SORT_MERGE, CC_SORT_RADIX) or a
     `key_bits` bound on the keys' span calls cc_sort_affinity_method."""
+    if total_keys is None:
+        L = _lib or _load()
+        st = L.marshal.sort(L.at_cc_sort_affinity_method, method, key_bits, key_offsets, keys_in,
+                            rows_in, keys_out, rows_out, workspace, max_keys, stream)
+        if st is not None:
+            return _check(st, "cc_sort_affinity" if method == SORT_AUTO and key_bits == 0
+                          else "cc_sort_affinity_method")
     B = key_offsets.numel() - 1
     tk = keys_in.numel() if total_keys is None else int(total_keys)
     rb = _row_bytes(rows_in)

@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 from pathlib import Path
 
@@ -11,6 +12,7 @@ PKG = Path(__file__).resolve().parent
 ROOT = PKG.parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libccjoin.so"
+MARSHAL = PKG / "_marshal.so"
 SOURCES = [CSRC / "cc_api.hip", CSRC / "join_kernels.hip", CSRC / "sort_kernels.hip",
            CSRC / "part_sort_kernels.hip", CSRC / "map_kernels.hip"]
 
@@ -53,5 +55,20 @@ def build(out: Path = LIB, extra_flags=()) -> Path:
     return out
 
 
+def build_marshal(out: Path = MARSHAL) -> Path:
+    """Compile the binding's native argument marshalling (a CPython extension, no GPU code)."""
+    out = Path(out)
+    tmp = out.with_name(out.name + ".tmp")
+    r = subprocess.run([os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC",
+                        f"-I{sysconfig.get_paths()['include']}", str(CSRC / "marshal.c"),
+                        "-o", str(tmp)], capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(r.stdout + r.stderr)
+        raise RuntimeError("compiling marshal.c failed")
+    tmp.replace(out)
+    return out
+
+
 if __name__ == "__main__":
     print(build())
+    print(build_marshal())
