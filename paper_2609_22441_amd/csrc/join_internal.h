@@ -115,6 +115,15 @@ constexpr int32_t kPartSmall = 1024;
 constexpr int32_t kPartLarge = 1280;
 constexpr int64_t kPartSmallTotal = (int64_t)1 << 18;
 
+// Two launches, the first of which puts long viewers' records in order of their parts: taken where
+// viewers have at most kSplitMax records (256 parts, of whose number two go to the ends) and by the
+// caller's bound (their mean, without one) may have more than kSplitMin. Measured against the
+// partition in one launch or radix, us: 64 x 5,000 33 / 30, 30 x 10,000 31 / 31, 100 x 10,000 60 /
+// 66, 1 x 20,000 22 / 28, 6 x 100,000 45 / 86, 32 x 100,000 222 / 261.
+constexpr int32_t kPartSplit = 640;
+constexpr int64_t kSplitMin = 8192;
+constexpr int64_t kSplitMax = (256 - 2) * (int64_t)kPartSplit;
+
 // Ranks by comparison (the same file): calls with few enough compares, total * ceil(longest / 512),
 // in viewers of kRankMinMean records or more on average. kRankGrid workgroups, of at most
 // kRankMaxPer records each. They take 8.5 to 9 us up to 5,000 records in one viewer (partition: 11
@@ -128,12 +137,14 @@ constexpr int64_t kRankMinMean = 128;
 constexpr int32_t kRankMaxPer = 256;
 constexpr int32_t kRankGrid = 256;
 
-// Enqueue the partition method, or ranks by comparison where they are faster: viewers of at most min(limit, kPartMaxRecords - 1) records are sorted, longer
-// ones copied through. buf0 and buf1: element arrays of 16 bytes per record.
+// Enqueue the partition method (in two launches if `split`, for limits up to kSplitMax), or ranks
+// by comparison where they are faster: viewers of at most min(limit, kPartMaxRecords - 1) records
+// are sorted, longer ones copied through. buf0 and buf1: element arrays of 16 bytes per record.
+// chunks: 12.5 bytes per record and 2 KiB, 8-byte aligned.
 hipError_t launch_part_sort(int32_t n_viewers, const int64_t *key_offsets, const int64_t *keys_in,
                             const void *rows_in, int32_t row_bytes, int64_t total, int64_t limit,
                             int64_t *keys_out, void *rows_out, void *buf0, void *buf1,
-                            hipStream_t stream);
+                            void *chunks, bool split, hipStream_t stream);
 
 // Enqueue a kernel that sets *counter (device) to zero.
 hipError_t launch_clear_counter(unsigned long long *counter, hipStream_t stream);

@@ -1189,6 +1189,11 @@ constexpr Layout layout_of(int64_t total, int64_t n_viewers) {
     l.bytes = l.perm + round_up(total * 4);
     return l;
 }
+// The partition method's chunks share the space from the histograms on: 8 + 4 + 4 bytes per record
+// and more than 16 KiB.
+static_assert(layout_of(1, 1).bytes - layout_of(1, 1).hist > 16384 &&
+                  2 * kMaxPasses * kRadix * 4 >= 8 * kTile && 4 * kRadix * 8 >= 4 * kTile,
+              "room for 12.5 bytes per record and 2 KiB");
 
 // Fixed device scratch of the allocation-free sort (cc_sort_affinity_noalloc): the workspace of
 // the largest call it accepts. One copy per device, resolved once per device below; in host
@@ -1239,10 +1244,13 @@ hipError_t launch_sort(int32_t n_viewers, const int64_t *key_offsets, const int6
         int64_t longest = limit;
         if (max_keys <= 0 && longest > kPartSkew * (total / n_viewers + 1))
             longest = kPartSkew * (total / n_viewers + 1);
-        if (n_viewers <= kPartMaxViewers && longest <= kPartMaxWork / total &&
+        const bool split = (max_keys > 0 ? limit : total / n_viewers) > kSplitMin &&
+                           limit <= kSplitMax;
+        if (n_viewers <= kPartMaxViewers && (split || longest <= kPartMaxWork / total) &&
             (max_keys > 0 || total <= kPartUnboundedTotal))
             return launch_part_sort(n_viewers, key_offsets, keys_in, rows_in, row_bytes, total,
-                                    limit, keys_out, rows_out, buf0, buf1, stream);
+                                    limit, keys_out, rows_out, buf0, buf1, w + l.hist, split,
+                                    stream);
         method = total >= kSortRadixMinRecords ? kSortRadix : kSortMerge;
     }
     int64_t *mt_off = reinterpret_cast<int64_t *>(w + l.mt_off);   // tile_off on the merge path

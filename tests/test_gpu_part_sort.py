@@ -1,6 +1,7 @@
 """GPU parity of the partition sort (cc_sort_affinity's choice for viewers of moderate length)
 against the oracle's stable sort: sizes around a part, the LDS tile and the sample; key
-distributions that break the sample's estimate; bounds; malformed offsets."""
+distributions that break the sample's estimate; bounds; malformed offsets; and the same of the split
+method that calls with long viewers take."""
 from __future__ import annotations
 
 import numpy as np
@@ -117,9 +118,9 @@ def test_above_the_radix_threshold_with_a_bound():
     _check([60_000] * 18, _keys("ids", 18 * 60_000, 4), "18 x 60,000", max_keys=60_000)
 
 
-def _sample_positions(n, parts):
+def _sample_positions(n, parts, per=10, most=4096):
     """The kernel's sample: one hashed position per stratum."""
-    s = min(4096 if parts > 409 else max(64, parts * 10), n)
+    s = min(most if parts > most // per else max(64, parts * per), n)
     i = np.arange(s, dtype=np.uint64)
     step = np.uint64((n << 12) // s)
     a, b = (i * step) >> np.uint64(12), ((i + np.uint64(1)) * step) >> np.uint64(12)
@@ -181,3 +182,96 @@ def test_malformed_offsets_stay_inside_the_buffers():
         wrote = (got != 0xCD).any(dim=1)
         src = got[wrote].contiguous().view(torch.int64)[:, 0]
         assert bool(((src >= 0) & (src < n)).all())
+
+
+# ---- calls with viewers of more than 8,192 records, at most 162,560: split by chunks beforehand ----
+
+SPLIT, CHUNK, WHOLE, LONGEST = 640, 3072, 2048, 254 * 640
+
+
+@pytest.mark.parametrize("kind", ["ids", "few", "equal", "ascending", "descending", "wide"])
+@pytest.mark.parametrize("lead", [0, 1, WHOLE, CHUNK - 1])
+def test_split_sizes(lead, kind):
+    """Viewers around the largest one that is sorted whole, one chunk and several, at offsets that
+    put the multiples of a part and a chunk anywhere."""
+    sizes = [lead, WHOLE, WHOLE + 1, CHUNK, CHUNK + 1, 0, 20_000, 2 * CHUNK, 1, 16 * SPLIT + 1, 8193]
+    _check(sizes, _keys(kind, sum(sizes), lead + 1), f"split, {kind} after {lead}", max_keys=20_000)
+
+
+@pytest.mark.parametrize("kind", ["ids", "few", "wide"])
+@pytest.mark.parametrize("n", [8_193, LONGEST, LONGEST + 1])
+def test_split_range_of_lengths(n, kind):
+    _check([777, n, 5_000], _keys(kind, n + 5_777, 3), f"{kind}, longest {n}", max_keys=n)
+    _check([n], _keys(kind, n, 4), f"{kind}, one viewer of {n}")
+
+
+@pytest.mark.parametrize("dup", [1, 300, 3_000])
+def test_split_keys_that_crowd(dup):
+    """Most keys in a sliver of the span (the histogram of the sample can't tell them apart), a few
+    far away, some repeated `dup` times."""
+    n = 60_000
+    keys = torch.arange(n) // dup
+    keys[::1000] = (1 << 62) - torch.arange(60)
+    keys[7::1000] = -(1 << 62) + torch.arange(60)
+    keys = keys[torch.randperm(n, generator=W.gen("cpu", dup, 1))]
+    _check([n, 9_000], torch.cat([keys, _keys("ids", 9_000, 2)]), f"crowded, {dup}", max_keys=n)
+
+
+@pytest.mark.parametrize("lead", [0, 777])
+def test_split_part_that_the_sample_misjudged(lead):
+    n = 33_333
+    parts = 1 + (lead + n - 1) // SPLIT - lead // SPLIT
+    keys = 500_000_000 + torch.randint(0, 700, (n,), generator=W.gen("cpu", n, 7))
+    at = torch.from_numpy(_sample_positions(n, parts, 12, WHOLE))
+    keys[at] = torch.randint(0, 1_000_000_000, (at.numel(),), generator=W.gen("cpu", n, 8))
+    assert int(((keys >= 500_000_000) & (keys < 500_000_700)).sum()) > 2 * WHOLE
+    _check([lead, n], torch.cat([_keys("ids", lead, 1), keys]), f"split, misjudged after {lead}",
+           max_keys=n)
+
+
+def test_part_of_a_short_viewer_that_the_sample_misjudged():
+    n, lead = 8_000, 6_000                       # viewers of at most 8,192 records: not split
+    parts = 1 + (lead + n - 1) // PART - lead // PART
+    keys = 500_000_000 + torch.randint(0, 700, (n,), generator=W.gen("cpu", n, 7))
+    at = torch.from_numpy(_sample_positions(n, parts))
+    keys[at] = torch.randint(0, 1_000_000_000, (at.numel(),), generator=W.gen("cpu", n, 8))
+    _check([lead, n], torch.cat([_keys("ids", lead, 1), keys]), "misjudged, 8,000", max_keys=n)
+
+
+def test_split_viewers_above_the_bound_are_copied_through():
+    sizes = [30_000, 9_000, 300, 50_000, 8_200]
+    ko = torch.tensor([0] + np.cumsum(sizes).tolist(), dtype=torch.int64)
+    n = int(ko[-1])
+    keys = _keys("few", n, 1)
+    rows = torch.arange(n, dtype=torch.int64).repeat_interleave(2).view(torch.uint8).reshape(n, 16)
+    note("split sort: bound 9,000")
+    gk, gr = _sort(ko, keys, rows, 9_000)
+    wk, wr = oracle.sort_affinity(ko, keys, rows)
+    for v, size in enumerate(sizes):
+        sl = slice(int(ko[v]), int(ko[v + 1]))
+        want = (keys.numpy()[sl], rows.numpy()[sl]) if size > 9_000 else (wk[sl], wr[sl])
+        assert np.array_equal(gk[sl], want[0]) and np.array_equal(gr[sl], want[1]), f"viewer {v}"
+
+
+@pytest.mark.parametrize("off", [[0, 40_000, 10_000, 50_000], [-5, 1 << 40, 3, 50_000],
+                                 [30_000, 20_000, 10_000, 0], [0, 20_000, 7, 30_000]])
+def test_split_malformed_offsets_stay_inside_the_buffers(off):
+    """Viewers that overlap write each other's chunk tables; whatever they hold, what is read and
+    written stays inside the call's buffers."""
+    note("split sort: malformed offsets")
+    n, pad = 50_000, 4_096
+    keys = _keys("ids", n, 2)
+    rows = torch.arange(n).repeat_interleave(2).view(torch.uint8).reshape(n, 16)
+    k_all = torch.full((n + 2 * pad,), -7, dtype=torch.int64, device=DEV)
+    r_all = torch.full((n + 2 * pad, 16), 0xCD, dtype=torch.uint8, device=DEV)
+    size = P.cc_sort_workspace_bytes(n, 3)
+    ws = torch.full((size + pad,), 0xEE, dtype=torch.uint8, device=DEV)
+    P.cc_sort_affinity(torch.tensor(off).to(DEV), keys.to(DEV), rows.to(DEV), k_all[pad:pad + n],
+                       r_all[pad:pad + n], ws[:size], max_keys=50_000)
+    torch.cuda.synchronize()
+    assert bool((k_all[:pad] == -7).all()) and bool((k_all[pad + n:] == -7).all())
+    assert bool((r_all[:pad] == 0xCD).all()) and bool((r_all[pad + n:] == 0xCD).all())
+    assert bool((ws[size:] == 0xEE).all())
+    got = r_all[pad:pad + n].cpu()
+    src = got[(got != 0xCD).any(dim=1)].contiguous().view(torch.int64)[:, 0]
+    assert bool(((src >= 0) & (src < n)).all())
