@@ -237,7 +237,7 @@ def sort_entry(torch, P, b, we, dev, tag, n_authors):
                                                         max_keys=mk, key_bits=kb), 30)
     alg = nk * (16 + 2 * we)
     return {"entry": "cc_sort_affinity_method", "workload": tag, "viewers": ko.numel() - 1,
-            "method": "radix" if nk >= P.SORT_RADIX_MIN_RECORDS else "merge", "key_bits": kb,
+            "method": "auto", "key_bits": kb,
             "records": nk, "row_bytes": we, "ms_median": t["median"], "ms_mean": t["mean"],
             "records_per_s": nk / (t["median"] / 1e3), "algorithmic_bytes": alg,
             "hbm_gbps": alg / (t["median"] / 1e3) / 1e9,

@@ -417,11 +417,11 @@ CC_API cc_status cc_sort_affinity(int32_t n_viewers, const int64_t *key_offsets,
  * method gives the same output; they differ in speed:
  *   CC_SORT_MERGE  per-tile sorts in LDS, then merge rounds within each viewer (a number of
  *                  kernels that grows with log2 of the largest viewer); the last round writes
- *                  the keys and copies the rows. Fewer launches: the faster method for small
- *                  calls.
+ *                  the keys and copies the rows. Fewer launches: the faster of the two for
+ *                  small calls.
  *   CC_SORT_RADIX  least-significant-digit radix passes of up to 9 bits over the span of the
  *                  call's keys (decoupled look-back between a viewer's tiles), then one gather
- *                  of the rows. Moves fewer bytes per record: the faster method for large calls.
+ *                  of the rows. Moves fewer bytes per record: the faster of the two for large ones.
  *                  A tile waits only for earlier tiles held by running workgroups, with a bound
  *                  of 8,192 polls so that every wave exits; a wait that reached it (not
  *                  expected) would leave the call's output undefined, every output row still a
@@ -429,8 +429,10 @@ CC_API cc_status cc_sort_affinity(int32_t n_viewers, const int64_t *key_offsets,
  *   CC_SORT_AUTO   one launch where the lists are short enough for it (their number times the
  *                  longest's length, or its estimate where max_keys is 0, decides): every
  *                  workgroup finds and sorts one part of a viewer in key order, or, in the smallest
- *                  calls, counts its records' places by comparison. Otherwise CC_SORT_RADIX from
- *                  CC_SORT_RADIX_MIN_RECORDS records on, else CC_SORT_MERGE.
+ *                  calls, counts its records' places by comparison. Two launches for lists of
+ *                  8,193 to 162,560 records, which are put in order of the parts beforehand.
+ *                  Otherwise CC_SORT_RADIX from CC_SORT_RADIX_MIN_RECORDS records on, else
+ *                  CC_SORT_MERGE.
  *   key_bits       0, or an upper bound on the bit length of (largest key - smallest key) over
  *                  the call (at most 64): the radix method then launches only the passes such a
  *                  span needs (ceil(key_bits / 9), e.g. 3 for author ids below 2^27), where it
