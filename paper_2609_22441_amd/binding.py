@@ -535,6 +535,13 @@ def _batched_args(store, cand_offsets, cand_idx, key_offsets, edge_keys, edge_fe
     return B, n_lookups, tc, tk, pco, pc, pko, pk, pf, pd, ex, ew
 
 
+def _at_most_one_extra(extra_keys) -> bool:
+    """No second lookup, or its keys in a list or tuple: what the native path takes. It reads None
+    as no second lookup, so a None among the keys is left to the checks, which refuse it."""
+    return not extra_keys or (isinstance(extra_keys, (list, tuple)) and len(extra_keys) == 1
+                              and extra_keys[0] is not None)
+
+
 def cc_join_batched(store: int, cand_offsets, cand_idx, key_offsets, edge_keys, edge_feats, out,
                     hit_mask, default_row=None, extra_keys: Optional[Sequence] = None,
                     total_cand: Optional[int] = None, total_keys: Optional[int] = None,
@@ -542,8 +549,8 @@ def cc_join_batched(store: int, cand_offsets, cand_idx, key_offsets, edge_keys, 
     """B viewers in CSR form, 1 + len(extra_keys) lookups (see include/cc_join.h). With
     `author_ids` ([total_cand] int64), lookup 0 searches the caller's author id of each
     candidate instead of the store's (cc_join_batched_authors)."""
-    if total_cand is None and total_keys is None and tuning is None and (
-            not extra_keys or len(extra_keys) == 1):
+    if (total_cand is None and total_keys is None and tuning is None
+            and _at_most_one_extra(extra_keys)):
         L = _lib or _load()
         st = L.marshal.batched(L.at_cc_join_batched, L.at_cc_join_batched_authors,
                                L.at_cc_store_info, store, cand_offsets, cand_idx, key_offsets,
@@ -581,7 +588,7 @@ def cc_join_batched_padded(store: int, cand_offsets, cand_idx, key_offsets, edge
                            stream=None) -> None:
     """B viewers written into the padded [B, n_max] layout (see include/cc_join.h). out is
     [B, n_max, >= row bytes] or [B * n_max, >= row bytes]."""
-    if total_cand is None and total_keys is None and (not extra_keys or len(extra_keys) == 1):
+    if total_cand is None and total_keys is None and _at_most_one_extra(extra_keys):
         L = _lib or _load()
         st = L.marshal.padded(L.at_cc_join_batched_padded, L.at_cc_store_info, store, cand_offsets,
                               cand_idx, key_offsets, edge_keys, edge_feats, default_row,

@@ -1,0 +1,146 @@
+"""The binding's native marshalling (csrc/marshal.c) on the CPU: host tensors that report GPU
+residency, and C functions that record their arguments, stand in for the tensors and the library. Every
+call is made once with the native path in front and once through binding.py's checks alone; both
+must reach the same C function with the same arguments, or raise the same error."""
+import ctypes
+
+import pytest
+import torch
+
+import paper_2609_22441_amd.binding as B
+
+DOC, EDGE = 32, 16
+HOT = ("cc_join", "cc_join_batched", "cc_join_batched_authors", "cc_join_batched_padded",
+       "cc_resolve_ids", "cc_sort_affinity", "cc_sort_affinity_method", "cc_store_upsert")
+
+
+class OnGpu:
+    """A host tensor that reports GPU residency."""
+    is_cuda = True
+
+    def __init__(self, t):
+        self.t = t
+
+    def __getattr__(self, k):
+        return getattr(self.t, k)
+
+
+class Off:
+    """A marshal module that answers None to everything."""
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+class Recorder:
+    """Functions with the library's signatures that record (name, arguments) and return 0; as
+    attributes for ctypes callers, and their addresses (at_*) for the native path."""
+
+    def __init__(self, real, marshal):
+        self.calls, self.keep = [], []
+        self.marshal = marshal
+        for name in HOT + ("cc_store_info",):
+            f = ctypes.CFUNCTYPE(ctypes.c_int, *getattr(real, name).argtypes)(
+                self._info if name == "cc_store_info" else self._record(name))
+            self.keep.append(f)
+            setattr(self, name, f)
+            setattr(self, "at_" + name, ctypes.cast(f, ctypes.c_void_p).value)
+
+    def _info(self, store, n, width):
+        if width:
+            width[0] = DOC
+        return 0
+
+    def _record(self, name):
+        def call(*args):
+            # Pointers to pointers: the pointers themselves; pointers to results: left out.
+            self.calls.append((name, [(a[0] if a else None) if isinstance(a, ctypes.POINTER(ctypes.c_void_p))
+                                      else a for a in args if not isinstance(a, ctypes.POINTER(ctypes.c_int64))]))
+            return 0
+        return call
+
+
+@pytest.fixture
+def both(monkeypatch):
+    """both(call) runs call(binding) on each path and returns the two outcomes."""
+    from paper_2609_22441_amd import _marshal
+    real = B.lib()
+    _marshal.init(OnGpu, torch.int64, torch.int8, lambda: 7)
+    monkeypatch.setattr(B, "_current_stream", lambda: 7)
+
+    def run(call):
+        got = []
+        for marshal in (_marshal, Off()):
+            rec = Recorder(real, marshal)
+            monkeypatch.setattr(B, "_lib", rec)
+            try:
+                call()
+                got.append(rec.calls)
+            except Exception as e:
+                got.append((type(e), str(e), rec.calls))
+        return got
+
+    yield run
+    _marshal.init(torch.Tensor, torch.int64, torch.int8, B._current_stream)
+
+
+def g(*shape, dtype=torch.int64):
+    return OnGpu(torch.zeros(*shape, dtype=dtype))
+
+
+N, K, V = 10, 6, 2
+
+
+def batch(L=2):
+    return dict(cand_offsets=g(V + 1), cand_idx=g(N), key_offsets=g(V + 1), edge_keys=g(K),
+                edge_feats=g(K, EDGE, dtype=torch.uint8),
+                out=g(N, DOC + L * EDGE, dtype=torch.uint8), hit_mask=g(N, L, dtype=torch.int8))
+
+
+def padded(L=2, n_max=5):
+    s = V * n_max
+    return dict(batch(L), out=g(s, DOC + L * EDGE, dtype=torch.uint8),
+                hit_mask=g(s, L, dtype=torch.int8), valid_mask=g(s, dtype=torch.int8), n_max=n_max)
+
+
+def same(got):
+    assert got[0] == got[1]
+    return got[0]
+
+
+# What may stand for the second lookup's keys. None in a list is no list of keys: it raises, and is
+# not taken for a call with one lookup.
+EXTRA = {"one": lambda: [g(N)], "tuple": lambda: (g(N),), "set": lambda: {g(N)}, "none": lambda: None,
+         "empty": lambda: [], "a list of None": lambda: [None], "a tuple of None": lambda: (None,),
+         "two": lambda: [g(N), g(N)], "short": lambda: [g(N - 1)], "32 bits": lambda: [g(N, dtype=torch.int32)]}
+
+
+@pytest.mark.parametrize("kind", EXTRA)
+def test_second_lookup(both, kind):
+    extra = EXTRA[kind]()
+    L = 1 + (len(extra) if extra else 0)
+    for form, args in ((B.cc_join_batched, batch(max(L, 2))), (B.cc_join_batched_padded, padded(max(L, 2)))):
+        got = same(both(lambda: form(1, extra_keys=extra, stream=0, **args)))
+        if kind in ("a list of None", "a tuple of None"):
+            assert got[0] is ValueError and got[2] == []
+        elif kind in ("short", "32 bits"):
+            assert got[0] in (ValueError, TypeError) and got[2] == []
+        else:
+            assert len(got) == 1 and (L if L < 3 else 3) in got[0][1]
+
+
+def test_plain_calls(both):
+    """The other entry points and their options."""
+    cand, ids, pos, ws, rows = g(N), g(N), g(N), g(64), g(N, DOC, dtype=torch.uint8)
+    one = dict(edge_keys=g(K), edge_feats=g(K, EDGE, dtype=torch.uint8),
+               out=g(N, DOC + EDGE + 8, dtype=torch.uint8), hit_mask=g(N, dtype=torch.int8))
+    row, many = g(EDGE, dtype=torch.uint8), batch(1)
+    sort = (g(V + 1), g(K), g(K, EDGE, dtype=torch.uint8), g(K), g(K, EDGE, dtype=torch.uint8), ws)
+    for name, call in (("cc_join", lambda: B.cc_join(1, cand, **one)),
+                       ("cc_join", lambda: B.cc_join(1, cand, default_row=row, stream=3, **one)),
+                       ("cc_join_batched_authors", lambda: B.cc_join_batched(1, author_ids=ids, **many)),
+                       ("cc_resolve_ids", lambda: B.cc_resolve_ids(1, ids, pos)),
+                       ("cc_store_upsert", lambda: B.cc_store_upsert(1, ids, pos, rows, ws)),
+                       ("cc_sort_affinity_method",
+                        lambda: B.cc_sort_affinity(*sort, max_keys=5, method=2, key_bits=9))):
+        got = same(both(call))
+        assert len(got) == 1 and got[0][0] == name
