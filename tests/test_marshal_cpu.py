@@ -144,3 +144,44 @@ def test_plain_calls(both):
                         lambda: B.cc_sort_affinity(*sort, max_keys=5, method=2, key_bits=9))):
         got = same(both(call))
         assert len(got) == 1 and got[0][0] == name
+
+
+@pytest.mark.parametrize("error", [KeyboardInterrupt, MemoryError, RuntimeError])
+def test_an_exception_on_the_way_is_raised(both, monkeypatch, error):
+    """An interrupt while the native path asks for the current stream is not lost, and nothing is
+    called."""
+    from paper_2609_22441_amd import _marshal
+    raised = []
+
+    def once():
+        if not raised:
+            raised.append(1)
+            raise error("once")
+        return 7
+
+    _marshal.init(OnGpu, torch.int64, torch.int8, once)
+    rec = Recorder(B.lib(), _marshal)
+    monkeypatch.setattr(B, "_lib", rec)
+    with pytest.raises(error, match="once"):
+        B.cc_resolve_ids(1, g(N), g(N))
+    assert rec.calls == []
+    B.cc_resolve_ids(1, g(N), g(N))
+    assert len(rec.calls) == 1
+
+
+@pytest.mark.parametrize("error", [AttributeError, TypeError, OverflowError])
+@pytest.mark.parametrize("name", ["numel", "is_contiguous", "data_ptr"])
+def test_an_argument_without_a_tensors_methods_is_not_plain(both, name, error):
+    class Odd(OnGpu):
+        pass
+
+    def fail(self):
+        raise error("odd")
+
+    from paper_2609_22441_amd import _marshal
+    _marshal.init(Odd, torch.int64, torch.int8, lambda: 7)
+    rec = Recorder(B.lib(), _marshal)
+    x = Odd(torch.zeros(N, dtype=torch.int64))
+    assert _marshal.resolve(rec.at_cc_resolve_ids, 1, x, x, 0) == 0 and len(rec.calls) == 1
+    setattr(Odd, name, fail)
+    assert _marshal.resolve(rec.at_cc_resolve_ids, 1, x, x, 0) is None and len(rec.calls) == 1
