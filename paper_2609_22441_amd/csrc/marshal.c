@@ -8,7 +8,8 @@
  * plain"; any other exception (a KeyboardInterrupt, a MemoryError) is the caller's and is raised.
  *
  * A cc_join through binding.py's checks costs the host about 8 us, more than the kernel of a
- * request of 10,000 candidates takes (5.6 us): such requests in a row took 9.1 us each, through this module 6.3.
+ * request of 10,000 candidates takes (5.6 us): such requests in a row took 9.1 us each, through
+ * this module 6.2.
  */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -187,7 +188,8 @@ static int stream_of(PyObject *x, void **p) {
     return ok;
 }
 
-/* Asked after every tensor has passed: the library itself only compares handles against 0. */
+/* Reads the store, which the library itself only compares against 0: asked when every argument has
+ * passed that needs no row width, so a call that is refused for one of them reads no handle. */
 static int doc_row_bytes(PyObject *info, const cc_store *s, int64_t *bytes) {
     void *f;
     int32_t w = 0;
@@ -211,8 +213,9 @@ static PyObject *m_join(PyObject *self, PyObject *const *a, Py_ssize_t n_args) {
     int64_t n, k, ew, stride, dw;
     if (n_args != 10 || !address(a[0], &fn) || !address(a[2], &store) ||
         !array_of(a[3], t_i64, 0, &cand, &n) || !array_of(a[4], t_i64, 0, &keys, &k) ||
-        !rows_of(a[5], k, &feats, &ew) || !doc_row_bytes(a[1], store, &dw) || !out_of(a[6], n, dw + ew, &out, &stride) || !array_of(a[7], t_i8, n, &hit, NULL) ||
-        !bytes_of(a[8], ew, &def, NULL) || !stream_of(a[9], &stream))
+        !rows_of(a[5], k, &feats, &ew) || !array_of(a[7], t_i8, n, &hit, NULL) ||
+        !bytes_of(a[8], ew, &def, NULL) || !stream_of(a[9], &stream) ||
+        !doc_row_bytes(a[1], store, &dw) || !out_of(a[6], n, dw + ew, &out, &stride))
         return no_call();
     CALL(((join_fn)fn)(store, cand, n, keys, k, feats, (int32_t)ew, def, out, stride, hit, stream));
 }
@@ -220,34 +223,33 @@ static PyObject *m_join(PyObject *self, PyObject *const *a, Py_ssize_t n_args) {
 /* Inputs that the batched forms share. */
 typedef struct {
     void *store, *co, *cand, *ko, *keys, *feats, *def, *extra[1], *stream;
-    int64_t B, tc, tk, ew, dw, L;
+    int64_t B, tc, tk, ew, L;
 } Batch;
 
-/* a: info, store, cand_offsets, cand_idx, key_offsets, keys, feats, default_row, extra, stream
+/* a: store, cand_offsets, cand_idx, key_offsets, keys, feats, default_row, extra, stream
  * (extra: None, or the second lookup's keys). */
 static int batch_of(PyObject *const *a, Batch *b) {
     int64_t nb;
-    if (!address(a[1], &b->store) || !array_of(a[2], t_i64, 1, &b->co, &nb) || nb - 1 > INT32_MAX || !array_of(a[3], t_i64, 0, &b->cand, &b->tc) ||
-        !array_of(a[4], t_i64, nb, &b->ko, NULL) || !array_of(a[5], t_i64, 0, &b->keys, &b->tk) ||
-        !rows_of(a[6], b->tk, &b->feats, &b->ew) || !bytes_of(a[7], b->ew, &b->def, NULL) ||
-        !doc_row_bytes(a[0], b->store, &b->dw))
+    if (!address(a[0], &b->store) || !array_of(a[1], t_i64, 1, &b->co, &nb) || nb - 1 > INT32_MAX ||
+        !array_of(a[2], t_i64, 0, &b->cand, &b->tc) || !array_of(a[3], t_i64, nb, &b->ko, NULL) ||
+        !array_of(a[4], t_i64, 0, &b->keys, &b->tk) || !rows_of(a[5], b->tk, &b->feats, &b->ew) ||
+        !bytes_of(a[6], b->ew, &b->def, NULL) || !stream_of(a[8], &b->stream))
         return 0;
     b->B = nb - 1;
-    b->L = a[8] == Py_None ? 1 : 2;
-    return b->L == 1 || array_of(a[8], t_i64, b->tc, &b->extra[0], NULL);
+    b->L = a[7] == Py_None ? 1 : 2;
+    return b->L == 1 || array_of(a[7], t_i64, b->tc, &b->extra[0], NULL);
 }
 
-/* batched(cc_join_batched, cc_join_batched_authors, <batch>, out, hit, author_ids) */
+/* batched(cc_join_batched, cc_join_batched_authors, cc_store_info, <batch>, out, hit, author_ids) */
 static PyObject *m_batched(PyObject *self, PyObject *const *a, Py_ssize_t n_args) {
     (void)self;
     Batch b;
     void *fn, *fn_authors, *out, *hit, *authors = NULL;
-    int64_t stride;
-    if (n_args != 15 || !address(a[0], &fn) || !address(a[1], &fn_authors) || !batch_of(a + 2, &b) ||
-        !out_of(a[12], b.tc, b.dw + b.L * b.ew, &out, &stride) ||
+    int64_t stride, dw;
+    if (n_args != 15 || !address(a[0], &fn) || !address(a[1], &fn_authors) || !batch_of(a + 3, &b) ||
         !array_of(a[13], t_i8, b.tc * b.L, &hit, NULL) ||
         (a[14] != Py_None && !array_of(a[14], t_i64, b.tc, &authors, NULL)) ||
-        !stream_of(a[11], &b.stream))
+        !doc_row_bytes(a[2], b.store, &dw) || !out_of(a[12], b.tc, dw + b.L * b.ew, &out, &stride))
         return no_call();
     const int64_t *const *ex = b.L == 2 ? (const int64_t *const *)b.extra : NULL;
     if (a[14] != Py_None) {
@@ -259,17 +261,16 @@ static PyObject *m_batched(PyObject *self, PyObject *const *a, Py_ssize_t n_args
                           (int32_t)b.ew, b.def, (int32_t)b.L, ex, out, stride, hit, b.stream));
 }
 
-/* padded(cc_join_batched_padded, <batch>, n_max, out, hit, valid) */
+/* padded(cc_join_batched_padded, cc_store_info, <batch>, n_max, out, hit, valid) */
 static PyObject *m_padded(PyObject *self, PyObject *const *a, Py_ssize_t n_args) {
     (void)self;
     Batch b;
     void *fn, *out, *hit, *valid;
-    int64_t n_max, stride;
-    if (n_args != 15 || !address(a[0], &fn) || !batch_of(a + 1, &b) || !number(a[11], &n_max) ||
-        n_max < 1 || n_max > INT32_MAX ||
-        !out_of(a[12], b.B * n_max, b.dw + b.L * b.ew, &out, &stride) ||
-        !array_of(a[13], t_i8, b.B * n_max * b.L, &hit, NULL) ||
-        !array_of(a[14], t_i8, b.B * n_max, &valid, NULL) || !stream_of(a[10], &b.stream))
+    int64_t n_max, stride, dw;
+    if (n_args != 15 || !address(a[0], &fn) || !batch_of(a + 2, &b) || !number(a[11], &n_max) ||
+        n_max < 1 || n_max > INT32_MAX || !array_of(a[13], t_i8, b.B * n_max * b.L, &hit, NULL) ||
+        !array_of(a[14], t_i8, b.B * n_max, &valid, NULL) || !doc_row_bytes(a[1], b.store, &dw) ||
+        !out_of(a[12], b.B * n_max, dw + b.L * b.ew, &out, &stride))
         return no_call();
     const int64_t *const *ex = b.L == 2 ? (const int64_t *const *)b.extra : NULL;
     CALL(((padded_fn)fn)(b.store, (int32_t)b.B, b.co, b.cand, b.tc, b.ko, b.keys, b.tk, b.feats,
@@ -297,8 +298,8 @@ static PyObject *m_upsert(PyObject *self, PyObject *const *a, Py_ssize_t n_args)
     int64_t n, dw, rb, ws_bytes, n_new = 0, n_rejected = 0;
     if (n_args != 8 || !address(a[0], &fn) || !address(a[2], &store) ||
         !array_of(a[3], t_i64, 0, &ids, &n) || !array_of(a[4], t_i64, n, &authors, NULL) ||
-        !rows_of(a[5], n, &rows, &rb) || !doc_row_bytes(a[1], store, &dw) || rb != dw ||
-        a[6] == Py_None || !bytes_of(a[6], 0, &ws, &ws_bytes) || !stream_of(a[7], &stream))
+        !rows_of(a[5], n, &rows, &rb) || a[6] == Py_None || !bytes_of(a[6], 0, &ws, &ws_bytes) ||
+        !stream_of(a[7], &stream) || !doc_row_bytes(a[1], store, &dw) || rb != dw)
         return no_call();
     int st;
     Py_BEGIN_ALLOW_THREADS

@@ -36,7 +36,7 @@ class Recorder:
     attributes for ctypes callers, and their addresses (at_*) for the native path."""
 
     def __init__(self, real, marshal):
-        self.calls, self.keep = [], []
+        self.calls, self.keep, self.asked = [], [], 0
         self.marshal = marshal
         for name in HOT + ("cc_store_info",):
             f = ctypes.CFUNCTYPE(ctypes.c_int, *getattr(real, name).argtypes)(
@@ -46,6 +46,7 @@ class Recorder:
             setattr(self, "at_" + name, ctypes.cast(f, ctypes.c_void_p).value)
 
     def _info(self, store, n, width):
+        self.asked += 1
         if width:
             width[0] = DOC
         return 0
@@ -185,3 +186,31 @@ def test_an_argument_without_a_tensors_methods_is_not_plain(both, name, error):
     assert _marshal.resolve(rec.at_cc_resolve_ids, 1, x, x, 0) == 0 and len(rec.calls) == 1
     setattr(Odd, name, fail)
     assert _marshal.resolve(rec.at_cc_resolve_ids, 1, x, x, 0) is None and len(rec.calls) == 1
+
+
+def test_a_refused_call_reads_no_store_handle(both):
+    """The row width is asked of the store only when every argument that does not need it has passed:
+    with one of those missing, the native path answers None without reading the handle."""
+    from paper_2609_22441_amd import _marshal
+    rec = Recorder(B.lib(), _marshal)
+    info, b, p = rec.at_cc_store_info, batch(), padded()
+    row = g(EDGE, dtype=torch.uint8)
+    head = [b[k] for k in ("cand_offsets", "cand_idx", "key_offsets", "edge_keys", "edge_feats")]
+    # (function, arguments, place of the output rows: the one argument checked against the width)
+    calls = [
+        (_marshal.join, [rec.at_cc_join, info, 1, g(N), g(K), b["edge_feats"],
+                         g(N, DOC + EDGE, dtype=torch.uint8), g(N, dtype=torch.int8), row, 0], 6),
+        (_marshal.batched, [rec.at_cc_join_batched, rec.at_cc_join_batched_authors, info, 1, *head,
+                            row, g(N), 0, b["out"], b["hit_mask"], g(N)], 12),
+        (_marshal.padded, [rec.at_cc_join_batched_padded, info, 1, *head, row, g(N), 0, p["n_max"],
+                           p["out"], p["hit_mask"], p["valid_mask"]], 12),
+        (_marshal.upsert, [rec.at_cc_store_upsert, info, 1, g(N), g(N), g(N, DOC, dtype=torch.uint8),
+                           g(64), 0], None)]
+    for call, args, out in calls:
+        for i in range(args.index(1) + 1, len(args)):
+            if i != out:
+                assert call(*args[:i], "odd", *args[i + 1:]) is None
+                assert rec.asked == 0 and rec.calls == [], (call.__name__, i)
+        assert call(*args) in (0, (0, 0, 0)) and rec.asked == 1 and len(rec.calls) == 1
+        rec.calls.clear()
+        rec.asked = 0
