@@ -9,6 +9,7 @@ The stream defaults to torch's current stream on the current device.
 from __future__ import annotations
 
 import ctypes
+import warnings
 from pathlib import Path
 from typing import Optional, Sequence
 
@@ -106,7 +107,7 @@ def _load():
         L.cc_upsert_workspace_bytes.argtypes = [i64]
         L.cc_upsert_workspace_bytes.restype = i64
         # Native marshalling of the hot entry points (csrc/marshal.c) takes function addresses.
-        L.marshal = _load_marshal()
+        L.marshal = _Unloaded()
         for name in ("cc_store_info", "cc_join", "cc_join_batched", "cc_join_batched_authors",
                      "cc_join_batched_padded", "cc_resolve_ids", "cc_sort_affinity_method",
                      "cc_store_upsert"):
@@ -115,13 +116,31 @@ def _load():
     return _lib
 
 
+class _Unloaded:
+    """In the place of the native marshalling until a call needs it: loading the library takes
+    neither torch nor the _marshal module."""
+
+    def __getattr__(self, name):
+        _lib.marshal = _load_marshal()
+        return getattr(_lib.marshal, name)
+
+
+class _ChecksOnly:
+    """In its place where it is not built: no call is plain, so binding.py's checks make it."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_marshal():
     import torch
     try:
         from . import _marshal
-    except ImportError as e:
-        raise RuntimeError("the package's _marshal module is not built; run "
-                           "__graft_entry__.build() first") from e
+    except ImportError:
+        warnings.warn("the package's _marshal module is not built (__graft_entry__.build() does): "
+                      "calls are checked in Python, about 8 us of host time each", RuntimeWarning,
+                      stacklevel=4)
+        return _ChecksOnly()
     _marshal.init(torch.Tensor, torch.int64, torch.int8, _current_stream)
     return _marshal
 

@@ -3,6 +3,9 @@ residency, and C functions that record their arguments, stand in for the tensors
 call is made once with the native path in front and once through binding.py's checks alone; both
 must reach the same C function with the same arguments, or raise the same error."""
 import ctypes
+import subprocess
+import sys
+import textwrap
 
 import pytest
 import torch
@@ -214,3 +217,37 @@ def test_a_refused_call_reads_no_store_handle(both):
         assert call(*args) in (0, (0, 0, 0)) and rec.asked == 1 and len(rec.calls) == 1
         rec.calls.clear()
         rec.asked = 0
+
+
+def _python(code):
+    r = subprocess.run([sys.executable, "-c", textwrap.dedent(code)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return r.stderr
+
+
+def test_the_library_loads_without_torch_and_without_the_native_path():
+    _python("""
+        import sys
+        sys.modules["torch"] = None
+        sys.modules["paper_2609_22441_amd._marshal"] = None
+        import paper_2609_22441_amd as P
+        assert P.cc_sort_workspace_bytes(1000, 2) > 0 and P.cc_status_string(0)
+        """)
+
+
+def test_calls_without_the_native_path_are_checked_in_python():
+    err = _python("""
+        import sys
+        sys.modules["paper_2609_22441_amd._marshal"] = None
+        import torch
+        import paper_2609_22441_amd as P
+        x = torch.zeros(4, dtype=torch.int64)
+        for n in (1, 2):
+            try:
+                P.cc_resolve_ids(1, x, x)
+            except ValueError as e:
+                assert "GPU memory" in str(e)
+            else:
+                raise SystemExit("no error")
+        """)
+    assert err.count("not built") == 1
