@@ -426,13 +426,15 @@ CC_API cc_status cc_sort_affinity(int32_t n_viewers, const int64_t *key_offsets,
  *                  of 8,192 polls so that every wave exits; a wait that reached it (not
  *                  expected) would leave the call's output undefined, every output row still a
  *                  copy of one of the call's input rows (memory-safe).
- *   CC_SORT_AUTO   one launch where the lists are short enough for it (their number times the
- *                  longest's length, or its estimate where max_keys is 0, decides): every
- *                  workgroup finds and sorts one part of a viewer in key order, or, in the smallest
- *                  calls, counts its records' places by comparison. Two launches for lists of
- *                  8,193 to 162,560 records, which are put in order of the parts beforehand.
- *                  Otherwise CC_SORT_RADIX from CC_SORT_RADIX_MIN_RECORDS records on, else
- *                  CC_SORT_MERGE.
+ *   CC_SORT_AUTO   by the call's records, its number of viewers and max_keys. The smallest calls
+ *                  take one launch that counts every record's place by comparison. Calls whose
+ *                  max_keys (the mean list, where it is 0) is above 8,192, and whose lists cannot
+ *                  exceed 162,560 records, take two launches: records are put in order of the
+ *                  parts of their viewer's key order first. Calls whose records times longest list
+ *                  (max_keys, or all records where it is 0) are few enough take one launch, in which
+ *                  every workgroup finds and sorts one part. The rest take CC_SORT_RADIX from
+ *                  CC_SORT_RADIX_MIN_RECORDS records on, else CC_SORT_MERGE. A call that names
+ *                  its longest list as max_keys is therefore often the faster one.
  *   key_bits       0, or an upper bound on the bit length of (largest key - smallest key) over
  *                  the call (at most 64): the radix method then launches only the passes such a
  *                  span needs (ceil(key_bits / 9), e.g. 3 for author ids below 2^27), where it

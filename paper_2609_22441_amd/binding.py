@@ -633,7 +633,7 @@ def cc_sort_workspace_bytes(total_keys: int, n_viewers: int) -> int:
 
 
 SORT_AUTO, SORT_MERGE, SORT_RADIX = 0, 1, 2
-SORT_RADIX_MIN_RECORDS = 1 << 20       # above short lists, CC_SORT_AUTO takes the radix method from here
+SORT_RADIX_MIN_RECORDS = 1 << 20       # CC_SORT_AUTO's line between the merge and the radix method
 
 
 def cc_sort_affinity(key_offsets, keys_in, rows_in, keys_out, rows_out, workspace,

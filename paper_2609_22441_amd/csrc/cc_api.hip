@@ -11,6 +11,7 @@
 
 #include "cc_join.h"
 #include "join_internal.h"
+#include "sort_choice.h"
 
 static_assert(CC_SORT_AUTO == ccj::kSortAuto && CC_SORT_MERGE == ccj::kSortMerge &&
                   CC_SORT_RADIX == ccj::kSortRadix &&

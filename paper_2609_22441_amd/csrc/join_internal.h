@@ -81,70 +81,22 @@ constexpr int kMaxScratchDevices = 64;
 // current device. Resolved on the first call per device, then cached.
 hipError_t sort_scratch(int device, void **ptr);
 
-// Sort methods (the values of CC_SORT_AUTO, CC_SORT_MERGE, CC_SORT_RADIX) and the call size
-// from which the automatic choice takes the radix method.
-constexpr int32_t kSortAuto = 0;
-constexpr int32_t kSortMerge = 1;
-constexpr int32_t kSortRadix = 2;
-constexpr int64_t kSortRadixMinRecords = (int64_t)1 << 20;
-
 // Enqueue the per-viewer stable sort of affinity records (keys + rows) into keys_out/rows_out
-// with `method` (kSortAuto: by call size). max_keys > 0 bounds the records of any one viewer;
+// with `method` (kSortAuto: by sort_choice). max_keys > 0 bounds the records of any one viewer;
 // key_bits > 0 bounds the bit length of (largest key - smallest key); 0 = unknown.
 hipError_t launch_sort(int32_t n_viewers, const int64_t *key_offsets, const int64_t *keys_in,
                        const void *rows_in, int32_t row_bytes, int64_t total, int64_t max_keys,
                        int64_t *keys_out, void *rows_out, void *workspace, int32_t method,
                        int32_t key_bits, hipStream_t stream);
 
-// Partition method (part_sort_kernels.hip): the automatic choice for calls whose key reads, about
-// total * longest / part, stay below those of a few passes over the call. Measured, 64-byte rows
-// (partition against merge or radix, us): 64 x 5,000 records 30 / 56, 30 x 20,000 44 / 82, 100 x
-// 20,000 116 / 153, 6 x 100,000 88 / 106, 1 x 200,000 92 / 96; past the line 50 x 40,000 145 / 141,
-// 10 x 100,000 130 / 123, 32 x 100,000 323 / 200, 1 x 500,000 245 / 118.
-constexpr int64_t kPartMaxWork = (int64_t)1 << 36;       // total * longest
-// A caller that gives no bound on its viewers is taken to have none longer than kPartSkew times
-// the mean, in calls of up to kPartUnboundedTotal records (where being wrong costs least).
-constexpr int64_t kPartSkew = 16;
-constexpr int64_t kPartUnboundedTotal = (int64_t)1 << 19;
-constexpr int64_t kPartMaxRecords = (int64_t)1 << 20;    // per viewer, exclusive (32-bit sample)
-constexpr int32_t kPartMaxViewers = 1 << 21;     // one workgroup each: the grid stays launchable
-// Records per part in calls of up to kPartSmallTotal records (the chip is not full, so short parts
-// end sooner: 1 x 20,000 27 us against 30 with 2,048) and in larger ones (fewer reads of the key
-// lists: 30 x 20,000 44 us against 57 with 1,024, 45 with 2,048).
-constexpr int32_t kPartSmall = 1024;
-constexpr int32_t kPartLarge = 1280;
-constexpr int64_t kPartSmallTotal = (int64_t)1 << 18;
-
-// Two launches, the first of which puts long viewers' records in order of their parts: taken where
-// viewers have at most kSplitMax records (256 parts, of whose number two go to the ends) and by the
-// caller's bound (their mean, without one) may have more than kSplitMin. Measured against the
-// partition in one launch or radix, us: 64 x 5,000 33 / 30, 30 x 10,000 31 / 31, 100 x 10,000 60 /
-// 66, 1 x 20,000 22 / 28, 6 x 100,000 45 / 86, 32 x 100,000 222 / 261.
-constexpr int32_t kPartSplit = 640;
-constexpr int64_t kSplitMin = 8192;
-constexpr int64_t kSplitMax = (256 - 2) * (int64_t)kPartSplit;
-
-// Ranks by comparison (the same file): calls with few enough compares, total * ceil(longest / 512),
-// in viewers of kRankMinMean records or more on average. kRankGrid workgroups, of at most
-// kRankMaxPer records each. They take 8.5 to 9 us up to 5,000 records in one viewer (partition: 11
-// for viewers of one part, 20 for longer ones), 12 us at 100,000 units of work and 28 at 200,000 (4 x
-// 5,000, where the partition takes 20); viewers of one part 9 us at 19,200 units and 12.6 at 128,000
-// (64 x 1,000, partition 11.4).
-constexpr int64_t kRankWorkShort = 40000;
-constexpr int64_t kRankWorkLong = 130000;
-constexpr int64_t kRankTotal = 10240;             // 1 x 10,000: 18.5 us, partition 23
-constexpr int64_t kRankMinMean = 128;
-constexpr int32_t kRankMaxPer = 256;
-constexpr int32_t kRankGrid = 256;
-
-// Enqueue the partition method (in two launches if `split`, for limits up to kSplitMax), or ranks
-// by comparison where they are faster: viewers of at most min(limit, kPartMaxRecords - 1) records
-// are sorted, longer ones copied through. buf0 and buf1: element arrays of 16 bytes per record.
-// chunks: 12.5 bytes per record and 2 KiB, 8-byte aligned.
+// Enqueue one of the three methods of part_sort_kernels.hip (kSortRank, kSortPart, kSortSplit), as
+// sort_choice names it for this total and limit: viewers of at most min(limit, kPartMaxRecords - 1)
+// records are sorted, longer ones copied through. buf0 and buf1: element arrays of 16 bytes per
+// record. chunks: 12.5 bytes per record and 2 KiB, 8-byte aligned.
 hipError_t launch_part_sort(int32_t n_viewers, const int64_t *key_offsets, const int64_t *keys_in,
                             const void *rows_in, int32_t row_bytes, int64_t total, int64_t limit,
                             int64_t *keys_out, void *rows_out, void *buf0, void *buf1,
-                            void *chunks, bool split, hipStream_t stream);
+                            void *chunks, int32_t method, hipStream_t stream);
 
 // Enqueue a kernel that sets *counter (device) to zero.
 hipError_t launch_clear_counter(unsigned long long *counter, hipStream_t stream);

@@ -29,6 +29,7 @@
 // sample has kPerPart records per part: a part of more than kCap / kPartLarge = 3.2 times its
 // share is a 2e-6 event in key orders that know nothing of the sample.
 #include "join_internal.h"
+#include "sort_choice.h"
 #include "sort_device.h"
 
 namespace ccj {
@@ -1078,6 +1079,8 @@ __global__ __launch_bounds__(kPartThreads, 8) void split_kernel(
 constexpr int kRankThreads = 1024;
 constexpr int kRankWaves = kRankThreads / 64;
 constexpr int kRankEpt = 8;
+constexpr int kRankGrid = 256;                 // workgroups, of at most kRankMaxPer records each
+constexpr int kRankMaxPer = 256;
 
 // Groups of 1 << rank_group(n) wavefronts hold a list of n keys.
 __host__ __device__ inline int rank_group(int64_t n) {
@@ -1247,13 +1250,10 @@ __global__ __launch_bounds__(kRankThreads) void rank_sort_kernel(const int64_t *
 hipError_t launch_part_sort(int32_t n_viewers, const int64_t *key_offsets, const int64_t *keys_in,
                             const void *rows_in, int32_t row_bytes, int64_t total, int64_t limit,
                             int64_t *keys_out, void *rows_out, void *buf0, void *buf1,
-                            void *chunks, bool split, hipStream_t stream) {
+                            void *chunks, int32_t method, hipStream_t stream) {
     const SortOut o{limit, total, static_cast<const chunk_t *>(rows_in), row_bytes / 16, keys_out,
                     static_cast<chunk_t *>(rows_out), nullptr};
-    const int64_t work = total * ((limit + 511) / 512);
-    if ((work <= (limit <= kPartSmall ? kRankWorkShort : kRankWorkLong) ||
-         (limit > kPartSmall && total <= kRankTotal)) &&
-        total >= (int64_t)n_viewers * kRankMinMean) {
+    if (method == kSortRank) {
         int32_t per = (int32_t)((total + kRankGrid - 1) / kRankGrid);
         // A group of wavefronts ranks at most 64 records (one lane each).
         const int32_t most = min(kRankMaxPer, 64 * (kRankWaves >> rank_group(limit)));
@@ -1264,7 +1264,7 @@ hipError_t launch_part_sort(int32_t n_viewers, const int64_t *key_offsets, const
         return hipGetLastError();
     }
     Elem *b0 = static_cast<Elem *>(buf0), *b1 = static_cast<Elem *>(buf1);
-    if (split) {
+    if (method == kSortSplit) {
         Split sp{static_cast<int64_t *>(chunks), nullptr, nullptr, (uint32_t)(total / kChunk) + 1};
         sp.pos = reinterpret_cast<uint32_t *>(sp.key + total);
         sp.start = reinterpret_cast<uint16_t *>(sp.pos + total);

@@ -1,0 +1,87 @@
+// Which kernels sort a call: the automatic choice of the affinity-record sort (CC_SORT_AUTO), from the
+// call's sizes alone. Host code without HIP, so that tests can ask it which kernels a call takes.
+//
+// Times below are in us, 16-byte rows and 24-bit ids unless a width is named, as a / b: the method in
+// question against the one the call takes otherwise (merge below kSortRadixMinRecords, else radix).
+#pragma once
+
+#include <stdint.h>
+
+namespace ccj {
+
+// Sort methods (the values of CC_SORT_AUTO, CC_SORT_MERGE, CC_SORT_RADIX), the call size from which
+// the automatic choice prefers radix to merge, and the three methods of part_sort_kernels.hip,
+// which only the automatic choice takes.
+constexpr int32_t kSortAuto = 0;
+constexpr int32_t kSortMerge = 1;
+constexpr int32_t kSortRadix = 2;
+constexpr int64_t kSortRadixMinRecords = (int64_t)1 << 20;
+constexpr int32_t kSortRank = 3;       // ranks by comparison, one launch
+constexpr int32_t kSortPart = 4;       // partition, one launch
+constexpr int32_t kSortSplit = 5;      // partition of long lists, split by part beforehand: two
+
+// Ranks by comparison: calls with few enough compares, total * ceil(longest / 512), in viewers of
+// kRankMinMean records or more on average. They take 8.5 to 9 us up to 5,000 records in one viewer
+// (partition: 11 for viewers of one part, 20 for longer ones), 12 us at 100,000 units of work and
+// 28 at 200,000 (4 x 5,000, where the partition takes 20); viewers of one part 9 us at 19,200 units
+// and 12.6 at 128,000 (64 x 1,000, partition 11.4).
+constexpr int64_t kRankWorkShort = 40000;         // viewers of one part
+constexpr int64_t kRankWorkLong = 130000;
+constexpr int64_t kRankTotal = 10240;             // 1 x 10,000: 18.5 us, partition 23
+constexpr int64_t kRankMinMean = 128;
+
+// Records per part in calls of up to kPartSmallTotal records (the chip is not full, so short parts
+// end sooner: 1 x 20,000 27 us against 30 with 2,048) and in larger ones (fewer reads of the key
+// lists: 30 x 20,000 44 us against 57 with 1,024, 45 with 2,048).
+constexpr int32_t kPartSmall = 1024;
+constexpr int32_t kPartLarge = 1280;
+constexpr int64_t kPartSmallTotal = (int64_t)1 << 18;
+constexpr int64_t kPartMaxRecords = (int64_t)1 << 20;    // per viewer, exclusive (32-bit sample)
+constexpr int32_t kPartMaxViewers = 1 << 21;     // one workgroup each: the grid stays launchable
+
+// Partition: calls whose key reads, about total * longest / part, stay below those of a few passes
+// over the call. 64 x 5,000 records of 64 bytes 29 / 53, 230 x 5,000 58 / 85, 300 x 8,000 100 / 131,
+// 20,000 x 1,000 456 / 1,131.
+constexpr int64_t kPartMaxWork = (int64_t)1 << 36;       // total * longest
+
+// A call without a bound on its viewers (max_keys = 0) is taken to hold one viewer of all its records:
+// 1,000 viewers of 20 records and one of 130,000 90 / 90, of 300,000 158 / 116, of 500,000
+// 257 / 126. (Taking none to be longer than 16 times the mean cost such calls up to twice the time;
+// without it 64 x 5,000 records take 70 us instead of 29 where the caller names no bound.) Except up
+// to kPartUnboundedTotal records in viewers of at most kPartUnboundedMean on average, where the
+// merge's time per viewer covers a long one: 20,000 x 10 286 / 888, and 8,000 viewers of 4 with
+// one of 500,000 466 / 466.
+constexpr int64_t kPartUnboundedTotal = (int64_t)1 << 19;
+constexpr int64_t kPartUnboundedMean = 64;
+
+// Two launches, the first of which puts long viewers' records in order of their parts: taken where
+// viewers have at most kSplitMax records (256 parts, of whose number two go to the ends) and by the
+// caller's bound (their mean, without one) may have more than kSplitMin. 1 x 160,000 27 / 84,
+// 130 x 8,500 52 / 107, 3,000 x 8,500 958 / 1,116, 40 x 130,000 175 / 225, 100 x 160,000 547 / 569;
+// against the partition in one launch: 64 x 5,000 33 / 30, 30 x 10,000 31 / 31, 100 x 10,000 60 / 66.
+constexpr int32_t kPartSplit = 640;              // records per part
+constexpr int64_t kSplitMin = 8192;
+constexpr int64_t kSplitMax = (256 - 2) * (int64_t)kPartSplit;
+
+// The method of a call of total records (1 to 2^32 - 1) in n_viewers viewers (at least 1), none
+// longer than max_keys if that is positive.
+inline int32_t sort_choice(int64_t total, int64_t n_viewers, int64_t max_keys) {
+    const int64_t limit = max_keys > 0 && max_keys < total ? max_keys : total;
+    const int64_t compares = total * ((limit + 511) / 512);
+    if (total >= n_viewers * kRankMinMean &&
+        (limit <= kPartSmall ? compares <= kRankWorkShort
+                             : compares <= kRankWorkLong || total <= kRankTotal))
+        return kSortRank;
+    if (n_viewers <= kPartMaxViewers) {
+        if ((max_keys > 0 ? limit : total / n_viewers) > kSplitMin && limit <= kSplitMax)
+            return kSortSplit;
+        if (max_keys > 0 || total <= kPartUnboundedTotal) {
+            const bool tiny = max_keys <= 0 && total <= n_viewers * kPartUnboundedMean;
+            if (tiny || limit <= kPartMaxWork / total)
+                return kSortPart;
+        }
+    }
+    return total >= kSortRadixMinRecords ? kSortRadix : kSortMerge;
+}
+
+}  // namespace ccj

@@ -40,6 +40,7 @@
 #include <hip/hip_runtime.h>
 
 #include "join_internal.h"
+#include "sort_choice.h"
 #include "sort_device.h"
 
 namespace ccj {
@@ -1239,25 +1240,16 @@ hipError_t launch_sort(int32_t n_viewers, const int64_t *key_offsets, const int6
     const Layout l = layout_of(total, n_viewers);
     void *buf0 = w;
     void *buf1 = w + l.buf;
-    if (method == kSortAuto) {
-        const int64_t limit = max_keys > 0 && max_keys < total ? max_keys : total;
-        int64_t longest = limit;
-        if (max_keys <= 0 && longest > kPartSkew * (total / n_viewers + 1))
-            longest = kPartSkew * (total / n_viewers + 1);
-        const bool split = (max_keys > 0 ? limit : total / n_viewers) > kSplitMin &&
-                           limit <= kSplitMax;
-        if (n_viewers <= kPartMaxViewers && (split || longest <= kPartMaxWork / total) &&
-            (max_keys > 0 || total <= kPartUnboundedTotal))
-            return launch_part_sort(n_viewers, key_offsets, keys_in, rows_in, row_bytes, total,
-                                    limit, keys_out, rows_out, buf0, buf1, w + l.hist, split,
-                                    stream);
-        method = total >= kSortRadixMinRecords ? kSortRadix : kSortMerge;
-    }
+    const int64_t largest = max_keys > 0 && max_keys < total ? max_keys : total;
+    if (method == kSortAuto)
+        method = sort_choice(total, n_viewers, max_keys);
+    if (method != kSortMerge && method != kSortRadix)
+        return launch_part_sort(n_viewers, key_offsets, keys_in, rows_in, row_bytes, total, largest,
+                                keys_out, rows_out, buf0, buf1, w + l.hist, method, stream);
     int64_t *mt_off = reinterpret_cast<int64_t *>(w + l.mt_off);   // tile_off on the merge path
     int64_t *range = reinterpret_cast<int64_t *>(w + l.range);
     uint32_t *counters = reinterpret_cast<uint32_t *>(w + l.range + 64);
     int64_t *slots = reinterpret_cast<int64_t *>(w + l.slots);
-    const int64_t largest = max_keys > 0 ? (max_keys < total ? max_keys : total) : total;
     // Position bits of a packed element: enough for the largest viewer.
     int32_t pbits = 1;
     while (((int64_t)1 << pbits) < largest)

@@ -1,0 +1,28 @@
+"""The sort's automatic choice on the CPU: which kernels a call of given sizes takes (the rules'
+measured reasons stand in csrc/sort_choice.h)."""
+import pytest
+
+from sort_route import MERGE, PART, RADIX, RANK, SPLIT, choice
+
+
+@pytest.mark.parametrize("sizes,max_keys,want", [
+    ([5_000], 0, RANK), ([10_240], 0, RANK), ([10_241], 0, SPLIT), ([500] * 80, 500, RANK),
+    ([500] * 81, 500, PART), ([5_000] * 4, 5_000, PART), ([100] * 90, 100, PART),
+    ([5_000] * 64, 5_000, PART), ([5_000] * 64, 8_192, PART), ([5_000] * 64, 8_193, SPLIT),
+    ([30_000] * 64, 30_000, SPLIT), ([254 * 640] * 20, 254 * 640, SPLIT), ([100_000], 0, SPLIT),
+    ([400_000] * 3, 400_000, RADIX), ([400_000], 400_000, MERGE),
+    ([9_000] * 300, 0, RADIX), ([1_000] * 20_000, 1_000, PART)])
+def test_methods(sizes, max_keys, want):
+    assert choice(sizes, max_keys) == want
+
+
+@pytest.mark.parametrize("longest", [300_000, 400_000, 495_000])
+def test_a_call_without_a_bound_may_hold_one_long_viewer(longest):
+    """One viewer of nearly all records among 1,000: 158 to 257 us (500,000) in one launch, where merge takes 116
+    to 126. With a bound on its viewers, or lists so short that merge pays more for their number, the
+    one launch is the faster one."""
+    sizes = [longest] + [20] * 1_000
+    assert choice(sizes) == MERGE
+    assert choice([5_000] * 64) == MERGE and choice([5_000] * 64, 5_000) == PART
+    assert choice([longest] + [2] * 8_000) == PART
+    assert choice([10] * 20_000) == PART
