@@ -44,7 +44,7 @@ constexpr int kRadix = 1 << kBits;
 constexpr int kSampleMin = 64;
 constexpr int kPerPart = 10;                   // sample records per part
 constexpr int kSampleCount = 256;              // samples up to this size are ranked by counting
-static_assert(kPartUnboundedTotal < kPartMaxRecords &&
+static_assert(kPartUnboundedTotal < kPartMaxRecords && kPartLarge < kPartMaxRecords &&
                   kPartMaxWork <= (kPartMaxRecords - 1) * (kPartMaxRecords - 1),
               "every viewer of a call that the automatic choice sends here can be sorted");
 

@@ -40,9 +40,13 @@ constexpr int64_t kPartMaxRecords = (int64_t)1 << 20;    // per viewer, exclusiv
 constexpr int32_t kPartMaxViewers = 1 << 21;     // one workgroup each: the grid stays launchable
 
 // Partition: calls whose key reads, about total * longest / part, stay below those of a few passes
-// over the call. 64 x 5,000 records of 64 bytes 29 / 53, 230 x 5,000 58 / 85, 300 x 8,000 100 / 131,
-// 20,000 x 1,000 456 / 1,131.
-constexpr int64_t kPartMaxWork = (int64_t)1 << 36;       // total * longest
+// over the call: 64 x 5,000 records of 64 bytes 29 / 53, 230 x 5,000 58 / 85, 300 x 8,000 100 / 131,
+// 1,000 x 5,000 202 / 205. Past the line 2,000 x 5,000 392 / 385 and 2,700 x 5,000 549 / 506 (10 us
+// more of a gap where the caller names the key span), 900 x 8,000 of 64 bytes 371 / 357, 2 x 180,000
+// 111 / 99, 1 x 262,000 112 / 91. Viewers of one part each read their keys once, whatever their
+// number: 60,000 x 1,000 1,374 / 3,354.
+constexpr int64_t kPartMaxWork = 5 * ((int64_t)1 << 32);     // total * longest
+constexpr int64_t kPartMaxWorkWhole = (int64_t)1 << 36;      // ... of viewers of one part
 
 // A call without a bound on its viewers (max_keys = 0) is taken to hold one viewer of all its records:
 // 1,000 viewers of 20 records and one of 130,000 90 / 90, of 300,000 158 / 116, of 500,000
@@ -77,7 +81,7 @@ inline int32_t sort_choice(int64_t total, int64_t n_viewers, int64_t max_keys) {
             return kSortSplit;
         if (max_keys > 0 || total <= kPartUnboundedTotal) {
             const bool tiny = max_keys <= 0 && total <= n_viewers * kPartUnboundedMean;
-            if (tiny || limit <= kPartMaxWork / total)
+            if (tiny || limit <= (limit <= kPartLarge ? kPartMaxWorkWhole : kPartMaxWork) / total)
                 return kSortPart;
         }
     }

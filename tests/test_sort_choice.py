@@ -10,7 +10,7 @@ from sort_route import MERGE, PART, RADIX, RANK, SPLIT, choice
     ([500] * 81, 500, PART), ([5_000] * 4, 5_000, PART), ([100] * 90, 100, PART),
     ([5_000] * 64, 5_000, PART), ([5_000] * 64, 8_192, PART), ([5_000] * 64, 8_193, SPLIT),
     ([30_000] * 64, 30_000, SPLIT), ([254 * 640] * 20, 254 * 640, SPLIT), ([100_000], 0, SPLIT),
-    ([400_000] * 3, 400_000, RADIX), ([400_000], 400_000, MERGE),
+    ([254 * 640 + 1], 0, MERGE), ([400_000] * 3, 400_000, RADIX), ([400_000], 400_000, MERGE),
     ([9_000] * 300, 0, RADIX), ([1_000] * 20_000, 1_000, PART)])
 def test_methods(sizes, max_keys, want):
     assert choice(sizes, max_keys) == want
@@ -26,3 +26,12 @@ def test_a_call_without_a_bound_may_hold_one_long_viewer(longest):
     assert choice([5_000] * 64) == MERGE and choice([5_000] * 64, 5_000) == PART
     assert choice([longest] + [2] * 8_000) == PART
     assert choice([10] * 20_000) == PART
+
+
+@pytest.mark.parametrize("sizes,want", [
+    ([180_000] * 2, MERGE), ([262_000], MERGE), ([5_000] * 2_000, RADIX), ([5_000] * 2_700, RADIX),
+    ([8_000] * 900, RADIX), ([8_000] * 300, PART), ([5_000] * 500, PART), ([2_000] * 2_000, PART),
+    ([1_280] * 40_000, PART), ([1_281] * 40_000, RADIX)])
+def test_the_partitions_key_reads_have_a_limit(sizes, want):
+    """Past it the other methods are faster, by 2 to 22%; viewers of one part read no key twice."""
+    assert choice(sizes, max(sizes)) == want
