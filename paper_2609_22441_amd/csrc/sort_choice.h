@@ -48,6 +48,11 @@ constexpr int32_t kPartMaxViewers = 1 << 21;     // one workgroup each: the grid
 constexpr int64_t kPartMaxWork = 5 * ((int64_t)1 << 32);     // total * longest
 constexpr int64_t kPartMaxWorkWhole = (int64_t)1 << 36;      // ... of viewers of one part
 
+// In calls that radix would take instead, viewers of fewer records than this on average: a workgroup
+// of the partition takes 14.6 ns per viewer, one of radix (several viewers each) 10 to 13. 1,200,000
+// x 8 17,460 / 12,306, 600,000 x 16 8,757 / 7,915, 600,000 x 24 8,831 / 10,540.
+constexpr int64_t kPartMinMean = 20;
+
 // A call without a bound on its viewers (max_keys = 0) is taken to hold one viewer of all its records:
 // 1,000 viewers of 20 records and one of 130,000 90 / 90, of 300,000 158 / 116, of 500,000
 // 257 / 126. (Taking none to be longer than 16 times the mean cost such calls up to twice the time;
@@ -79,7 +84,8 @@ inline int32_t sort_choice(int64_t total, int64_t n_viewers, int64_t max_keys) {
     if (n_viewers <= kPartMaxViewers) {
         if ((max_keys > 0 ? limit : total / n_viewers) > kSplitMin && limit <= kSplitMax)
             return kSortSplit;
-        if (max_keys > 0 || total <= kPartUnboundedTotal) {
+        const bool short_lists = total >= kSortRadixMinRecords && total < n_viewers * kPartMinMean;
+        if (!short_lists && (max_keys > 0 || total <= kPartUnboundedTotal)) {
             const bool tiny = max_keys <= 0 && total <= n_viewers * kPartUnboundedMean;
             if (tiny || limit <= (limit <= kPartLarge ? kPartMaxWorkWhole : kPartMaxWork) / total)
                 return kSortPart;

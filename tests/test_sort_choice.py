@@ -35,3 +35,9 @@ def test_a_call_without_a_bound_may_hold_one_long_viewer(longest):
 def test_the_partitions_key_reads_have_a_limit(sizes, want):
     """Past it the other methods are faster, by 2 to 22%; viewers of one part read no key twice."""
     assert choice(sizes, max(sizes)) == want
+
+
+def test_very_many_very_short_lists():
+    """8 records each: 12.3 ms with radix, 17.5 in one launch."""
+    assert choice([8] * 1_200_000, 16) == RADIX and choice([16] * 600_000, 16) == RADIX
+    assert choice([24] * 600_000, 24) == PART and choice([8] * 100_000, 16) == PART
