@@ -31,6 +31,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "ingest_choice.h"
 #include "join_internal.h"
 
 namespace ccj {
@@ -528,11 +529,10 @@ __device__ __forceinline__ bool batch_fits(const Ws &w, int64_t n_old, int64_t c
 //
 // Scatter, commit and rollback as launches of their own took 29.0 + 6.9 + 4.9 us for a batch of
 // 300,000 records (most of the last two their launch and drain), one launch 32.5. COMMIT = false
-// leaves the map's update to commit_kernel: from kCommitApartFrom records on, where the launch no
-// longer counts, the map's random writes cost more between the row writes (10M records in one
-// launch 1,065 us, in two 551 + 316).
+// leaves the map's update to commit_kernel: batches for which commit_apart says that the launch no
+// longer counts beside the map's random writes between the row writes (10M records in one launch
+// 1,065 us, in two 551 + 316).
 constexpr int kScatterPer = 4;
-constexpr int64_t kCommitApartFrom = 1 << 21;     // records
 
 __device__ __forceinline__ void put_host(int64_t *p, int64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -771,7 +771,7 @@ hipError_t launch_upsert_finish(MapEntry *map, int64_t n, void *workspace, int64
         return hipSuccess;
     const Ws w = carve(workspace, n);
     const int32_t chunks = row_bytes / 16;
-    const bool apart = n >= kCommitApartFrom;
+    const bool apart = commit_apart(n, row_bytes);
     hipLaunchKernelGGL(apart ? apply_kernel<false> : apply_kernel<true>,
                        dim3(grid_for(n * chunks, kThreads * kScatterPer)), dim3(kThreads), 0,
                        stream, map, n, w, n_old, capacity, author_in,

@@ -1,5 +1,5 @@
-"""The sort's automatic choice (csrc/sort_choice.h) for a call's sizes: the header itself, compiled
-for the host."""
+"""The kernels that a call's sizes lead to: the sort's automatic choice (csrc/sort_choice.h) and the
+ingestion's (csrc/ingest_choice.h), the headers themselves, compiled for the host."""
 from __future__ import annotations
 
 import ctypes
@@ -11,9 +11,13 @@ from pathlib import Path
 CSRC = Path(__file__).resolve().parent.parent / "paper_2609_22441_amd" / "csrc"
 MERGE, RADIX, RANK, PART, SPLIT = 1, 2, 3, 4, 5
 
-SHIM = """#include "sort_choice.h"
+SHIM = """#include "ingest_choice.h"
+#include "sort_choice.h"
 extern "C" int choice(int64_t total, int64_t n_viewers, int64_t max_keys) {
     return ccj::sort_choice(total, n_viewers, max_keys);
+}
+extern "C" int apart(int64_t n_records, int64_t row_bytes) {
+    return ccj::commit_apart(n_records, row_bytes);
 }
 """
 
@@ -25,11 +29,16 @@ def _shim():
         src.write_text(SHIM)
         subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", f"-I{CSRC}",
                         str(src), "-o", str(out)], check=True)
-        f = ctypes.CDLL(str(out)).choice
-    f.argtypes = [ctypes.c_int64] * 3
-    return f
+        lib = ctypes.CDLL(str(out))
+    lib.choice.argtypes = [ctypes.c_int64] * 3
+    lib.apart.argtypes = [ctypes.c_int64] * 2
+    return lib
 
 
 def choice(sizes, max_keys=0) -> int:
     """The method of a call with viewers of these sizes."""
-    return _shim()(int(sum(sizes)), len(sizes), max_keys)
+    return _shim().choice(int(sum(sizes)), len(sizes), max_keys)
+
+
+def commit_apart(n_records, row_bytes) -> bool:
+    return bool(_shim().apart(n_records, row_bytes))

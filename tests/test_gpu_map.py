@@ -13,6 +13,7 @@ import oracle
 import paper_2609_22441_amd as P
 import workload as W
 from gpu_common import FILL, gpu_join, note, oracle_join
+from kernel_choice import commit_apart
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -558,14 +559,16 @@ def test_probe_limit_refuses_the_batch_and_keeps_the_store():
     fresh.close()
 
 
-def test_batch_that_commits_apart_from_its_rows():
-    """2^21 + 3 records (the map's update is a launch of its own from 2^21 on): stored, new and
-    repeated ids and a reserved one, checked in full against a replay; then one that does not fit
-    leaves the store as it was."""
-    n, base = (1 << 21) + 3, 100_000
-    note(f"ingestion: {n} records, the map updated by a launch of its own")
+@pytest.mark.parametrize("n,row", [((1 << 21) + 3, 16), (100_663, 4_000), (100_665, 4_000)])
+def test_batch_that_commits_apart_from_its_rows(n, row):
+    """2^21 + 3 records, and both sides of the line in row bytes past which the map's update is a
+    launch of its own: stored, new and repeated ids and a reserved one, checked in full against a
+    replay; then one that does not fit leaves the store as it was."""
+    base = 100_000 if row == 16 else 20_000
+    assert commit_apart(n, row) == (n != 100_663)
+    note(f"ingestion: {n} records of {row} bytes, the map updated by a launch of its own or not")
     g = torch.Generator(device=DEV).manual_seed(5)
-    store = P.cc_store_create_indexed(base + n, 16)
+    store = P.cc_store_create_indexed(base + n, row)
     try:
         ws = torch.empty(P.cc_upsert_workspace_bytes(2 * n), dtype=torch.uint8, device=DEV)
 
@@ -573,7 +576,7 @@ def test_batch_that_commits_apart_from_its_rows():
             ids = items * 7_919 + 13
             ids = torch.where(items < 0, torch.full_like(ids, -(1 << 63)), ids)
             auth = torch.randint(0, 1 << 30, (items.numel(),), device=DEV, generator=g)
-            rows = torch.randint(0, 1 << 60, (items.numel(), 2), device=DEV, generator=g)
+            rows = torch.randint(0, 1 << 60, (items.numel(), row // 8), device=DEV, generator=g)
             return auth, rows, P.cc_store_upsert(store, ids, auth, rows, ws)
 
         a0, r0, got = upsert(torch.arange(base, device=DEV))
@@ -587,7 +590,7 @@ def test_batch_that_commits_apart_from_its_rows():
         order = it[keep][np.argsort(first[keep], kind="stable")]       # by first record
         pos = {}
         want_a, want_r = torch.cat([a0.cpu(), torch.zeros(n_new, dtype=torch.int64)]), \
-            torch.cat([r0.cpu(), torch.zeros(n_new, 2, dtype=torch.int64)])
+            torch.cat([r0.cpu(), torch.zeros(n_new, row // 8, dtype=torch.int64)])
         rank = np.full(base + n, -1, np.int64)
         rank[:base] = np.arange(base)
         rank[order] = base + np.arange(n_new)
@@ -603,7 +606,7 @@ def test_batch_that_commits_apart_from_its_rows():
         def read():
             m = P.cc_store_info(store)[0]
             a = torch.empty(m, dtype=torch.int64, device=DEV)
-            r = torch.empty(m, 2, dtype=torch.int64, device=DEV)
+            r = torch.empty(m, row // 8, dtype=torch.int64, device=DEV)
             P.cc_store_read(store, 0, m, a, r)
             q = torch.arange(base + n, device=DEV) * 7_919 + 13
             p = torch.empty_like(q)

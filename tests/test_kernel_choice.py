@@ -1,8 +1,8 @@
-"""The sort's automatic choice on the CPU: which kernels a call of given sizes takes (the rules'
-measured reasons stand in csrc/sort_choice.h)."""
+"""Which kernels a call of given sizes takes, on the CPU (the rules' measured reasons stand in
+csrc/sort_choice.h and csrc/ingest_choice.h)."""
 import pytest
 
-from sort_route import MERGE, PART, RADIX, RANK, SPLIT, choice
+from kernel_choice import MERGE, PART, RADIX, RANK, SPLIT, choice, commit_apart
 
 
 @pytest.mark.parametrize("sizes,max_keys,want", [
@@ -41,3 +41,12 @@ def test_very_many_very_short_lists():
     """8 records each: 12.3 ms with radix, 17.5 in one launch."""
     assert choice([8] * 1_200_000, 16) == RADIX and choice([16] * 600_000, 16) == RADIX
     assert choice([24] * 600_000, 24) == PART and choice([8] * 100_000, 16) == PART
+
+
+@pytest.mark.parametrize("n,row,want", [
+    (300_000, 128, False), (2_000_000, 128, False), (1_000_000, 256, False), (100_000, 2_048, False),
+    (600_000, 1_024, True), (1_000_000, 512, True), (2_000_000, 256, True), (1_500_000, 1_024, True),
+    (1 << 21, 16, True)])
+def test_batches_of_many_row_bytes_update_the_map_apart(n, row, want):
+    """1,500,000 records of 1,024 bytes: 862 us in one launch, 781 in two."""
+    assert commit_apart(n, row) == want
