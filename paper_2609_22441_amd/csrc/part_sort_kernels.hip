@@ -837,8 +837,8 @@ __device__ __forceinline__ bool part_of(const int64_t *off, int32_t B, int64_t t
     return true;
 }
 
-// SPLIT: split_kernel has gone through the viewers of more than kChunk records; shorter ones are one
-// part.
+// SPLIT: split_kernel has gone through the viewers of more than kSplitCap records; shorter ones are
+// one part.
 template <bool SPLIT>
 __global__ __launch_bounds__(kPartThreads, SPLIT ? 8 : 4) void part_sort_kernel(
     const int64_t *__restrict__ keys, const int64_t *off, int32_t B, int32_t part, Split sp,
@@ -863,21 +863,25 @@ __global__ __launch_bounds__(kPartThreads, SPLIT ? 8 : 4) void part_sort_kernel(
 //
 // Step 2 above reads a viewer once per part, which for long viewers costs more than all else, and
 // the radix method's nine launches keep the rows waiting for six passes over the keys. Here
-// every workgroup takes one chunk of kChunk records of a viewer of more than kChunk, finds the
+// every workgroup takes one chunk of at most kChunk records of a viewer of more than kSplitCap, finds the
 // bounds of all the viewer's parts from the same sample, and writes the chunk's keys and positions
 // ordered by part (stably, one digit pass in LDS) with the first index of every part. Nothing is
 // counted over chunks: a part's workgroup in the next launch adds up the chunks' entries. Two
-// launches against radix (or the scan above): 32 x 100,000 records of 128 bytes 262 -> 222 us, 64
-// viewers of 100 to 30,000 of 64 bytes 42.9 -> 35.4, 1 x 100,000 58.6 -> 27.7.
+// launches against radix (or the scan above): 32 x 100,000 records of 128 bytes 262 -> 224 us, 64
+// viewers of 100 to 30,000 of 64 bytes 42.6 -> 33, 1 x 100,000 58.6 -> 27.7.
 //
 // The bounds come from a histogram of the sample over kBins equal shares of its key span, a part
 // starting as far into the share that holds its first sample record as that record is among the
-// share's: any bounds will do that every chunk finds alike. Where a share holds more than kShareMost sample records (keys that crowd or repeat),
-// the sample is sorted instead, and the bounds are its records by key and position.
-// A part of more than kSplitCap records, 3.2 times its share, is a 1e-7 event in key orders that
-// know nothing of the sample (with 10 sample records and 3 times, 5e-6, one of 8,000 parts was, and
-// took 300 us). Half of the keys in a tenth of the span, parts that start at their share's edge: the
-// largest of 47,000 parts had 2,027 records; as far into it as above, 1,714 of 63,000.
+// share's: any bounds will do that every chunk finds alike and that ascend. Where a share holds more
+// than kShareMost sample records (keys that crowd or repeat), the sample is sorted instead, and the
+// bounds are its records by key and position.
+// A part of more than kSplitCap records, 3.2 times its share, is rare in key orders that know nothing
+// of the sample, the rarer the more sample records a part has: kPerSplit of them up to 170 parts
+// (108,000 records), fewer in longer viewers, whose sample is full, 8 at the longest. Per part (the
+// share of a part is close to a gamma variate): 2e-7 at 12, 1.3e-6 at 200 parts, 4.4e-6 at 225, 1.4e-5
+// at 255, which is one viewer of kSplitMax records in 280. Half of the keys in a tenth of the span,
+// parts that start at their share's edge: the largest of 47,000 parts had 2,027 records; as far into it
+// as above, 1,714 of 63,000.
 //
 // Bound by its dependent steps and the instructions of the ranking: 3.2M records 37.9 us with four
 // workgroups per CU, where 38 MB in and out alone take 12. Sorting the sample by 16 key bits instead
@@ -886,6 +890,11 @@ constexpr int kBinBits = 13;
 constexpr int kBins = 1 << kBinBits;
 constexpr uint32_t kShareMost = 8;
 constexpr uint32_t kPerSplit = 12;                       // sample records per part
+// A bound is its share's lower edge plus less than a share, which in the last share that holds a sample
+// record could pass the largest key and wrap. It does not: a bound's record has S / G records of
+// the sample or more from itself on, so one that is not the last share's first would make it hold
+// more than kShareMost, and the sample is then sorted.
+static_assert(kPerSplit >= kShareMost && kSplitCap / kRadix >= kShareMost, "S / G >= kShareMost");
 
 struct SplitShared {
     union {
