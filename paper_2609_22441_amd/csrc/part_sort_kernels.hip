@@ -693,7 +693,9 @@ __device__ __forceinline__ void big_part(SH &sh, const int64_t *__restrict__ key
 #pragma unroll 4
     for (int64_t c = tid; c < chunks; c += kPartThreads) {
         const uint32_t i = (uint32_t)((uint64_t)c / (uint32_t)o.row_chunks);
-        const int64_t from = pt.kb + min<int64_t>((int64_t)a[i].pos, pt.n - 1);
+        // Viewers that overlap (malformed offsets) share slices of a and b and may leave places of
+        // them unwritten: whatever those hold names a record of this viewer.
+        const int64_t from = pt.kb + (int64_t)min<uint64_t>(a[i].pos, pt.n - 1);
         o.rows_out[to * o.row_chunks + c] =
             o.rows_in[from * o.row_chunks + (c - (int64_t)i * o.row_chunks)];
     }

@@ -275,3 +275,32 @@ def test_split_malformed_offsets_stay_inside_the_buffers(off):
     got = r_all[pad:pad + n].cpu()
     src = got[(got != 0xCD).any(dim=1)].contiguous().view(torch.int64)[:, 0]
     assert bool(((src >= 0) & (src < n)).all())
+
+
+@pytest.mark.parametrize("n,part,per,most", [(8_000, PART, 10, 4_096), (40_000, SPLIT, 12, WHOLE)])
+def test_viewers_that_overlap_in_an_overlong_part(n, part, per, most):
+    """Offsets that give the same records to two viewers, whose first part does not fit in LDS: both
+    sort it through the same slices of the workspace, which start out as indexes far below zero. Every
+    row written is one of the call's rows, whatever the two leave there."""
+    note(f"sort: overlapping overlong parts, {n} records")
+    total, pad = n + 5_000, 4_096
+    keys = torch.randint(0, 700, (total,), generator=W.gen("cpu", n, 7))
+    at = torch.from_numpy(_sample_positions(n, 1 + (n - 1) // part, per, most))
+    keys[at] = torch.randint(1_000, 1_000_000_000, (at.numel(),), generator=W.gen("cpu", n, 8))
+    assert int((keys[:n] < 700).sum()) > most
+    rows = torch.arange(total).repeat_interleave(2).view(torch.uint8).reshape(total, 16)
+    k_all = torch.full((total + 2 * pad,), -7, dtype=torch.int64, device=DEV)
+    r_all = torch.full((total + 2 * pad, 16), 0xCD, dtype=torch.uint8, device=DEV)
+    size = P.cc_sort_workspace_bytes(total, 3)
+    for fill in (0xEE, 0x7F):
+        ws = torch.full((size + pad,), fill, dtype=torch.uint8, device=DEV)
+        P.cc_sort_affinity(torch.tensor([0, n, 0, n]).to(DEV), keys.to(DEV), rows.to(DEV),
+                           k_all[pad:pad + total], r_all[pad:pad + total], ws[:size],
+                           max_keys=8_192 if part == PART else n)
+        torch.cuda.synchronize()
+        assert bool((k_all[:pad] == -7).all()) and bool((k_all[pad + total:] == -7).all())
+        assert bool((r_all[:pad] == 0xCD).all()) and bool((r_all[pad + total:] == 0xCD).all())
+        assert bool((ws[size:] == fill).all())
+        got = r_all[pad:pad + total].cpu()
+        src = got[(got != 0xCD).any(dim=1)].contiguous().view(torch.int64)[:, 0]
+        assert src.numel() > most and bool(((src >= 0) & (src < total)).all())
