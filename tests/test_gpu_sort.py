@@ -25,7 +25,7 @@ def _shuffle_within(key_offsets, keys, rows, seed):
     return k, r
 
 
-METHODS = (P.SORT_MERGE, P.SORT_RADIX)
+METHODS = (P.SORT_AUTO, P.SORT_MERGE, P.SORT_RADIX)
 
 
 def _gpu_sort(ko, keys, rows, max_keys=0, method=P.SORT_AUTO, key_bits=0):
@@ -42,7 +42,8 @@ def _gpu_sort(ko, keys, rows, max_keys=0, method=P.SORT_AUTO, key_bits=0):
 
 
 def _check(ko, keys, rows, what, max_keys=0):
-    """Both sort methods (merge rounds; radix passes and a row gather) against the oracle."""
+    """The automatic choice and both named methods (merge rounds; radix passes and a row gather)
+    against the oracle."""
     wk, wr = oracle.sort_affinity(ko, keys, rows)
     for method in METHODS:
         gk, gr = _gpu_sort(ko, keys, rows, max_keys, method)
@@ -242,7 +243,7 @@ def test_radix_with_a_key_bits_bound_that_does_not_hold():
 def test_multi_tile_viewers_with_wide_keys():
     """Viewers of several tiles whose keys span all 64 bits: the radix method takes the wide
     16-byte elements (4,096-record tiles) and all 8 digit passes, the last 5 of them on the
-    looping workgroups; repeats across tiles check stability. Both methods against the oracle."""
+    looping workgroups; repeats across tiles check stability. Every method against the oracle."""
     note("sort: multi-tile viewers, 64-bit key span")
     g = W.gen("cpu", 43, 3)
     sizes = torch.tensor([12_000, 4_097, 9_000, 1])
