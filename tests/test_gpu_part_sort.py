@@ -1,7 +1,8 @@
-"""GPU parity of the partition sort (cc_sort_affinity's choice for viewers of moderate length)
-against the oracle's stable sort: sizes around a part, the LDS tile and the sample; key
-distributions that break the sample's estimate; bounds; malformed offsets; and the same of the split
-method that calls with long viewers take."""
+"""GPU parity of the sort's methods that only the automatic choice takes (ranks by comparison, the
+partition in one launch, and in two for long viewers) against the oracle's stable sort: sizes around
+a part, the LDS tile and the sample; key distributions that break the sample's estimate; bounds;
+malformed offsets. Every case names the method that its sizes are meant to lead to, and asks the rule
+itself (kernel_choice) whether they do."""
 from __future__ import annotations
 
 import numpy as np
@@ -12,11 +13,14 @@ import oracle
 import paper_2609_22441_amd as P
 import workload as W
 from gpu_common import note
+from kernel_choice import MERGE, PART, RANK, SPLIT, choice
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
 
-PART = 1024              # records per part in calls of at most 2^18 records
+SHORT, LONG = 1024, 1280     # records per part in calls of at most 2^18 records, and of more
+BOUND = 8_192                # the longest list that the partition takes in one launch by its bound
+KINDS = ["ids", "few", "equal", "ascending", "descending", "wide", "top"]
 
 
 def _sort(ko, keys, rows, max_keys=0):
@@ -30,8 +34,10 @@ def _sort(ko, keys, rows, max_keys=0):
     return k_out.cpu().numpy(), r_out.cpu().numpy()
 
 
-def _check(sizes, keys, what, row=16, max_keys=0):
-    note(f"partition sort: {what}")
+def _check(sizes, keys, what, want, row=16, max_keys=0):
+    """`want`: the method that the call is meant to take."""
+    note(f"sort method {want}: {what}")
+    assert choice(sizes, max_keys) == want, what
     sizes = torch.as_tensor(sizes, dtype=torch.int64)
     ko = torch.cat([torch.zeros(1, dtype=torch.int64), torch.cumsum(sizes, 0)])
     n = int(ko[-1])
@@ -61,21 +67,46 @@ def _keys(kind, n, seed):
         k[::97] = -(1 << 63)
         k[1::101] = (1 << 63) - 1
         return k
+    if kind == "top":                            # up to the largest key, in few values at the end
+        k = (1 << 63) - 1 - torch.randint(0, 50_000, (n,), generator=g)
+        k[::5] = (1 << 63) - 1 - torch.randint(0, 40, ((n + 4) // 5,), generator=g)
+        return k
     raise ValueError(kind)
 
 
-@pytest.mark.parametrize("kind", ["ids", "few", "equal", "ascending", "descending", "wide"])
-@pytest.mark.parametrize("n", [1, 65, 513, PART, PART + 1, 4097, 9_001, 20_011, 140_003])
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n", [1, 65, 513, SHORT, SHORT + 1, 4097, 9_001, 20_011, 140_003])
 def test_one_viewer(n, kind):
-    _check([n], _keys(kind, n, n), f"one viewer, {n} {kind} records", row=48 if n < 5000 else 16)
+    """By the method that one viewer of n records takes: one part, ranks, or two launches."""
+    want = PART if n < 128 else RANK if n <= 10_240 else SPLIT
+    _check([n], _keys(kind, n, n), f"one viewer, {n} {kind} records", want, row=48 if n < 5000 else 16)
 
 
-@pytest.mark.parametrize("kind", ["ids", "few", "equal", "ascending", "descending", "wide"])
-@pytest.mark.parametrize("n", [1, 513, PART, PART + 1, 4097])
-def test_one_viewer_beside_a_long_one(n, kind):
-    """The same with a 40,000-record viewer in the call: above the size whose ranks are counted by
-    comparison, so that both viewers are cut into parts."""
-    _check([n, 40_000], _keys(kind, n + 40_000, n), f"{n} and 40,000 {kind} records")
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n", [1, 513, SHORT, SHORT + 1, 1_537, 4097, BOUND])
+def test_viewers_cut_into_parts(n, kind):
+    """Viewers of up to eight parts in one launch: above the size whose ranks are counted, within the
+    bound that keeps them from being split beforehand."""
+    sizes = [n, 8_000, 0, 2_999]
+    _check(sizes, _keys(kind, sum(sizes), n), f"{n}, 8,000 and 2,999 {kind} records", PART, max_keys=BOUND)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n", [2 * LONG, 7_777])
+def test_viewers_cut_into_long_parts(n, kind):
+    """The same above 2^18 records, whose parts are longer."""
+    sizes = [777] + [n] * (300_000 // n) + [BOUND]
+    assert sum(sizes) > 1 << 18
+    _check(sizes, _keys(kind, sum(sizes), n), f"{n} {kind} records each", PART, max_keys=BOUND)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n", [25 * SHORT, 26 * SHORT + 1, 130_000])
+def test_long_viewer_in_one_launch(n, kind):
+    """A call without a bound holds one long viewer among short ones: samples just small enough to be
+    ranked by counting, just too large for it, and one of 1,270 records."""
+    sizes = [n] + [20] * 60
+    _check(sizes, _keys(kind, sum(sizes), n), f"{n} {kind} records among short lists", PART)
 
 
 @pytest.mark.parametrize("bits", [31, 40, 52, 53, 63])
@@ -85,37 +116,49 @@ def test_ranks_with_and_without_room_for_the_position(bits):
     g = W.gen("cpu", bits, 3)
     keys = torch.randint(0, 40, (1_500,), generator=g)
     keys[1::2] += 1 << (bits - 1)
-    _check([1_500, 130], torch.cat([keys, _keys("few", 130, 1)]), f"two groups, bit {bits - 1}")
+    _check([1_500, 130], torch.cat([keys, _keys("few", 130, 1)]), f"two groups, bit {bits - 1}", RANK)
 
 
+@pytest.mark.parametrize("want", [RANK, PART, SPLIT])
 @pytest.mark.parametrize("row", [16, 32, 80, 128, 16 * 513])
-def test_row_widths(row):
+def test_row_widths(row, want):
     n = 2_500 if row < 1000 else 700
-    _check([n, 0, 300], _keys("ids", n + 300, row), f"row width {row}", row=row)
+    sizes = [n, 0, 300] + {RANK: [], PART: [8_000, 1_500], SPLIT: [9_000, 30_000]}[want]
+    _check(sizes, _keys("ids", sum(sizes), row), f"row width {row}", want, row=row,
+           max_keys={RANK: 0, PART: BOUND, SPLIT: 30_000}[want])
 
 
-@pytest.mark.parametrize("max_keys", [0, 30_000])
-def test_ragged_viewers(max_keys):
+@pytest.mark.parametrize("longest,want", [(BOUND, PART), (30_000, SPLIT)])
+def test_ragged_viewers(longest, want):
     """Viewers that start and end anywhere against the multiples of a part, empty ones included;
-    the call is above 2^18 records, so the longer parts are used."""
+    the call is above 2^18 records, so the partition's longer parts are used."""
     g = W.gen("cpu", 8, 3)
-    sizes = torch.cat([torch.tensor([0, 1, 1023, 1024, 1025, 1536, 1537, 30_000, 0, 4096, 4097]),
-                       torch.randint(0, 9_000, (80,), generator=g), torch.tensor([0, 2, 0])])
+    sizes = torch.cat([torch.tensor([0, 1, 1023, 1024, 1025, 1536, 1537, longest, 0, 4096, 4097]),
+                       torch.randint(0, min(longest, 9_000), (80,), generator=g), torch.tensor([0, 2, 0])])
     n = int(sizes.sum())
     assert n > 1 << 18
-    _check(sizes, _keys("ids", n, 9), f"ragged, max_keys {max_keys}", max_keys=max_keys)
+    _check(sizes, _keys("ids", n, 9), f"ragged, up to {longest}", want, max_keys=longest)
 
 
 def test_more_viewers_than_one_search_round():
     g = W.gen("cpu", 9, 3)
     sizes = torch.randint(0, 12, (1_700,), generator=g)
     sizes[::230] = 3_000
-    _check(sizes, _keys("few", int(sizes.sum()), 3), "1,700 viewers")
+    _check(sizes, _keys("few", int(sizes.sum()), 3), "1,700 viewers", PART)
+
+
+def test_very_short_lists_without_a_bound():
+    """200,000 records in lists of 10 on average, one of 50,000: one launch, above the size up to which
+    a call without a bound may otherwise take it."""
+    sizes = torch.full((15_000,), 10)
+    sizes[7_000] = 50_000
+    _check(sizes, _keys("ids", int(sizes.sum()), 3), "15,000 short lists and a long one", PART)
 
 
 def test_above_the_radix_threshold_with_a_bound():
     """2^20 records and more in viewers that the caller bounds by 2^17 or less."""
-    _check([60_000] * 18, _keys("ids", 18 * 60_000, 4), "18 x 60,000", max_keys=60_000)
+    _check([60_000] * 18, _keys("ids", 18 * 60_000, 4), "18 x 60,000", SPLIT, max_keys=60_000)
+    _check([3_000] * 400, _keys("ids", 400 * 3_000, 4), "400 x 3,000", PART, max_keys=3_000)
 
 
 def _sample_positions(n, parts, per=10, most=4096):
@@ -128,19 +171,33 @@ def _sample_positions(n, parts, per=10, most=4096):
     return (a + ((h * (b - a)) >> np.uint64(32))).astype(np.int64)
 
 
-@pytest.mark.parametrize("lead", [0, 777])
-@pytest.mark.parametrize("n", [20_000, 33_333])
-def test_part_that_the_sample_misjudged(n, lead):
-    """Every sampled record outside the band that all others share: one part then holds far more
-    records than LDS does and is sorted through the workspace."""
-    parts = 1 + (lead + n - 1) // PART - lead // PART
+def _misjudged(n, parts, per, most):
+    """Keys whose sampled records all lie outside the band that the others share (with repeats)."""
     g = W.gen("cpu", n, 7)
-    keys = 500_000_000 + torch.randint(0, 700, (n,), generator=g)        # repeats in the band
-    at = torch.from_numpy(_sample_positions(n, parts))
+    keys = 500_000_000 + torch.randint(0, 700, (n,), generator=g)
+    at = torch.from_numpy(_sample_positions(n, parts, per, most))
     keys[at] = torch.randint(0, 1_000_000_000, (at.numel(),), generator=g)
     band = (keys >= 500_000_000) & (keys < 500_000_700)
-    assert int(band.sum()) > 2 * 4096 - 1000
-    _check([lead, n], torch.cat([_keys("ids", lead, 1), keys]), f"misjudged part, {n} after {lead}")
+    assert int(band.sum()) > most
+    return keys
+
+
+def _parts(lead, n, part):
+    return 1 + (lead + n - 1) // part - lead // part
+
+
+@pytest.mark.parametrize("lead,n,part,max_keys", [
+    ([], BOUND, SHORT, BOUND), ([6_000], 8_000, SHORT, BOUND), ([7_777, 3], 5_000, SHORT, BOUND),
+    ([777] + [7_000] * 38, 8_000, LONG, BOUND), ([20] * 60, 30_000, SHORT, 0), ([10] * 9, 120_000, SHORT, 0)])
+def test_part_that_the_sample_misjudged(lead, n, part, max_keys):
+    """One part holds far more records than LDS does and is sorted through the workspace; samples of 80
+    to 1,190 records."""
+    at = sum(lead)
+    rest = [3_000] if max_keys else [10] * 9
+    keys = torch.cat([_keys("ids", at, 1), _misjudged(n, _parts(at, n, part), 10, 4_096),
+                      _keys("few", sum(rest), 2)])
+    assert (len(keys) > 1 << 18) == (part == LONG)
+    _check(lead + [n] + rest, keys, f"misjudged part, {n} after {at}", PART, max_keys=max_keys)
 
 
 @pytest.mark.parametrize("max_keys", [1, 1024, 6000])
@@ -150,7 +207,8 @@ def test_viewers_above_the_bound_are_copied_through(max_keys):
     n = int(ko[-1])
     keys = _keys("few", n, max_keys)
     rows = torch.arange(n, dtype=torch.int64).repeat_interleave(2).view(torch.uint8).reshape(n, 16)
-    note(f"partition sort: bound {max_keys}")
+    note(f"sort: bound {max_keys}")
+    assert choice(sizes, max_keys) == (RANK if max_keys == 1 else PART)
     gk, gr = _sort(ko, keys, rows, max_keys)
     wk, wr = oracle.sort_affinity(ko, keys, rows)
     for v, size in enumerate(sizes):
@@ -160,49 +218,87 @@ def test_viewers_above_the_bound_are_copied_through(max_keys):
         assert np.array_equal(gr[sl], want[1]), f"viewer {v} ({size}): rows"
 
 
-def test_malformed_offsets_stay_inside_the_buffers():
-    """Offsets out of order and out of range: the output is unspecified, but the bytes around it
-    stay as they were and every row written is one of the call's rows."""
-    note("partition sort: malformed offsets")
-    n, pad = 5_000, 4_096
-    for off in ([0, 4_000, 1_000, n], [-5, 1 << 40, 3, n], [3_000, 2_000, 1_000, 0],
-                [1_500, 1_500, 9_999, n]):
-        ko = torch.tensor(off, dtype=torch.int64)
-        keys = _keys("ids", n, 2)
-        rows = torch.arange(n).repeat_interleave(2).view(torch.uint8).reshape(n, 16)
-        k_all = torch.full((n + 2 * pad,), -7, dtype=torch.int64, device=DEV)
-        r_all = torch.full((n + 2 * pad, 16), 0xCD, dtype=torch.uint8, device=DEV)
-        ws = torch.zeros(P.cc_sort_workspace_bytes(n, 3), dtype=torch.uint8, device=DEV)
-        P.cc_sort_affinity(ko.to(DEV), keys.to(DEV), rows.to(DEV), k_all[pad:pad + n],
-                           r_all[pad:pad + n], ws)
-        torch.cuda.synchronize()
-        assert bool((k_all[:pad] == -7).all()) and bool((k_all[pad + n:] == -7).all())
-        assert bool((r_all[:pad] == 0xCD).all()) and bool((r_all[pad + n:] == 0xCD).all())
-        got = r_all[pad:pad + n].cpu()
-        wrote = (got != 0xCD).any(dim=1)
-        src = got[wrote].contiguous().view(torch.int64)[:, 0]
-        assert bool(((src >= 0) & (src < n)).all())
+def _check_inside(off, n, max_keys, want, keys=None, fill=0xEE):
+    """The output for offsets that break the rules is unspecified, but the bytes around the buffers stay
+    as they were and every row written is one of the call's rows. Returns the number of those."""
+    assert choice([n] + [0] * (len(off) - 2), max_keys) == want
+    pad = 4_096
+    keys = _keys("ids", n, 2) if keys is None else keys
+    rows = torch.arange(n).repeat_interleave(2).view(torch.uint8).reshape(n, 16)
+    k_all = torch.full((n + 2 * pad,), -7, dtype=torch.int64, device=DEV)
+    r_all = torch.full((n + 2 * pad, 16), 0xCD, dtype=torch.uint8, device=DEV)
+    size = P.cc_sort_workspace_bytes(n, len(off) - 1)
+    ws = torch.full((size + pad,), fill, dtype=torch.uint8, device=DEV)
+    P.cc_sort_affinity(torch.tensor(off).to(DEV), keys.to(DEV), rows.to(DEV), k_all[pad:pad + n],
+                       r_all[pad:pad + n], ws[:size], max_keys=max_keys)
+    torch.cuda.synchronize()
+    assert bool((k_all[:pad] == -7).all()) and bool((k_all[pad + n:] == -7).all())
+    assert bool((r_all[:pad] == 0xCD).all()) and bool((r_all[pad + n:] == 0xCD).all())
+    assert bool((ws[size:] == fill).all())
+    got = r_all[pad:pad + n].cpu()
+    src = got[(got != 0xCD).any(dim=1)].contiguous().view(torch.int64)[:, 0]
+    assert bool(((src >= 0) & (src < n)).all())
+    return src.numel()
+
+
+@pytest.mark.parametrize("off", [[0, 4_000, 1_000, 5_000], [-5, 1 << 40, 3, 5_000],
+                                 [3_000, 2_000, 1_000, 0], [1_500, 1_500, 9_999, 5_000]])
+def test_malformed_offsets_stay_inside_the_buffers(off):
+    note(f"ranks: offsets {off}")
+    _check_inside(off, 5_000, 0, RANK)
+
+
+@pytest.mark.parametrize("max_keys", [0, BOUND])
+@pytest.mark.parametrize("off", [[0, 8_000, 1_000, 9_000], [-5, 1 << 40, 3, 12_000],
+                                 [8_000, 4_000, 2_000, 0], [6_000, 6_000, 99_999, 12_000],
+                                 [0, 7_000, 0, 7_000]])
+def test_malformed_offsets_in_the_partition(off, max_keys):
+    """In one launch: with a bound, and without one (a viewer may then hold all records)."""
+    note(f"partition: offsets {off}, bound {max_keys}")
+    _check_inside(off, 12_000, max_keys, PART)
+
+
+@pytest.mark.parametrize("n,want,part,per,most", [(8_000, PART, SHORT, 10, 4_096),
+                                                  (40_000, SPLIT, 640, 12, 2_048)])
+def test_viewers_that_overlap_in_an_overlong_part(n, want, part, per, most):
+    """Offsets that give the same records to two viewers, whose first part does not fit in LDS: both
+    sort it through the same slices of the workspace, which start out as indexes far below zero. Every
+    row written is one of the call's rows, whatever the two leave there."""
+    note(f"sort: overlapping overlong parts, {n} records")
+    total = n + 5_000
+    keys = torch.randint(0, 700, (total,), generator=W.gen("cpu", n, 7))
+    at = torch.from_numpy(_sample_positions(n, _parts(0, n, part), per, most))
+    keys[at] = torch.randint(1_000, 1_000_000_000, (at.numel(),), generator=W.gen("cpu", n, 8))
+    assert int((keys[:n] < 700).sum()) > most
+    for fill in (0xEE, 0x7F):
+        wrote = _check_inside([0, n, 0, n], total, BOUND if want == PART else n, want, keys, fill)
+        assert wrote > most
 
 
 # ---- calls with viewers of more than 8,192 records, at most 162,560: split by chunks beforehand ----
 
-SPLIT, CHUNK, WHOLE, LONGEST = 640, 3072, 2048, 254 * 640
+SPLIT_PART, CHUNK, WHOLE, LONGEST = 640, 3072, 2048, 254 * 640
 
 
-@pytest.mark.parametrize("kind", ["ids", "few", "equal", "ascending", "descending", "wide"])
+@pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("lead", [0, 1, WHOLE, CHUNK - 1])
 def test_split_sizes(lead, kind):
     """Viewers around the largest one that is sorted whole, one chunk and several, at offsets that
     put the multiples of a part and a chunk anywhere."""
-    sizes = [lead, WHOLE, WHOLE + 1, CHUNK, CHUNK + 1, 0, 20_000, 2 * CHUNK, 1, 16 * SPLIT + 1, 8193]
-    _check(sizes, _keys(kind, sum(sizes), lead + 1), f"split, {kind} after {lead}", max_keys=20_000)
+    sizes = [lead, WHOLE, WHOLE + 1, CHUNK, CHUNK + 1, 0, 20_000, 2 * CHUNK, 1, 16 * SPLIT_PART + 1, 8193]
+    _check(sizes, _keys(kind, sum(sizes), lead + 1), f"split, {kind} after {lead}", SPLIT, max_keys=20_000)
 
 
-@pytest.mark.parametrize("kind", ["ids", "few", "wide"])
-@pytest.mark.parametrize("n", [8_193, LONGEST, LONGEST + 1])
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n", [10_241, LONGEST - 1, LONGEST, LONGEST + 1])
 def test_split_range_of_lengths(n, kind):
-    _check([777, n, 5_000], _keys(kind, n + 5_777, 3), f"{kind}, longest {n}", max_keys=n)
-    _check([n], _keys(kind, n, 4), f"{kind}, one viewer of {n}")
+    """Around the shortest and the longest single viewer that takes two launches, and the bound from which
+    they are taken."""
+    want = SPLIT if n <= LONGEST else MERGE
+    _check([777, n, 5_000], _keys(kind, n + 5_777, 3), f"{kind}, longest {n}", want, max_keys=n)
+    _check([n], _keys(kind, n, 4), f"{kind}, one viewer of {n}", want)
+    _check([8_193, 5_000], _keys(kind, 13_193, 5), f"{kind}, bound 8,193", SPLIT, max_keys=8_193)
+    _check([8_192, 5_000], _keys(kind, 13_192, 5), f"{kind}, bound 8,192", PART, max_keys=8_192)
 
 
 @pytest.mark.parametrize("dup", [1, 300, 3_000])
@@ -214,28 +310,15 @@ def test_split_keys_that_crowd(dup):
     keys[::1000] = (1 << 62) - torch.arange(60)
     keys[7::1000] = -(1 << 62) + torch.arange(60)
     keys = keys[torch.randperm(n, generator=W.gen("cpu", dup, 1))]
-    _check([n, 9_000], torch.cat([keys, _keys("ids", 9_000, 2)]), f"crowded, {dup}", max_keys=n)
+    _check([n, 9_000], torch.cat([keys, _keys("ids", 9_000, 2)]), f"crowded, {dup}", SPLIT, max_keys=n)
 
 
 @pytest.mark.parametrize("lead", [0, 777])
-def test_split_part_that_the_sample_misjudged(lead):
-    n = 33_333
-    parts = 1 + (lead + n - 1) // SPLIT - lead // SPLIT
-    keys = 500_000_000 + torch.randint(0, 700, (n,), generator=W.gen("cpu", n, 7))
-    at = torch.from_numpy(_sample_positions(n, parts, 12, WHOLE))
-    keys[at] = torch.randint(0, 1_000_000_000, (at.numel(),), generator=W.gen("cpu", n, 8))
-    assert int(((keys >= 500_000_000) & (keys < 500_000_700)).sum()) > 2 * WHOLE
-    _check([lead, n], torch.cat([_keys("ids", lead, 1), keys]), f"split, misjudged after {lead}",
+@pytest.mark.parametrize("n", [33_333, 150_000])
+def test_split_part_that_the_sample_misjudged(n, lead):
+    keys = _misjudged(n, _parts(lead, n, SPLIT_PART), 12, WHOLE)
+    _check([lead, n], torch.cat([_keys("ids", lead, 1), keys]), f"split, misjudged after {lead}", SPLIT,
            max_keys=n)
-
-
-def test_part_of_a_short_viewer_that_the_sample_misjudged():
-    n, lead = 8_000, 6_000                       # viewers of at most 8,192 records: not split
-    parts = 1 + (lead + n - 1) // PART - lead // PART
-    keys = 500_000_000 + torch.randint(0, 700, (n,), generator=W.gen("cpu", n, 7))
-    at = torch.from_numpy(_sample_positions(n, parts))
-    keys[at] = torch.randint(0, 1_000_000_000, (at.numel(),), generator=W.gen("cpu", n, 8))
-    _check([lead, n], torch.cat([_keys("ids", lead, 1), keys]), "misjudged, 8,000", max_keys=n)
 
 
 def test_split_viewers_above_the_bound_are_copied_through():
@@ -245,6 +328,7 @@ def test_split_viewers_above_the_bound_are_copied_through():
     keys = _keys("few", n, 1)
     rows = torch.arange(n, dtype=torch.int64).repeat_interleave(2).view(torch.uint8).reshape(n, 16)
     note("split sort: bound 9,000")
+    assert choice(sizes, 9_000) == SPLIT
     gk, gr = _sort(ko, keys, rows, 9_000)
     wk, wr = oracle.sort_affinity(ko, keys, rows)
     for v, size in enumerate(sizes):
@@ -258,49 +342,5 @@ def test_split_viewers_above_the_bound_are_copied_through():
 def test_split_malformed_offsets_stay_inside_the_buffers(off):
     """Viewers that overlap write each other's chunk tables; whatever they hold, what is read and
     written stays inside the call's buffers."""
-    note("split sort: malformed offsets")
-    n, pad = 50_000, 4_096
-    keys = _keys("ids", n, 2)
-    rows = torch.arange(n).repeat_interleave(2).view(torch.uint8).reshape(n, 16)
-    k_all = torch.full((n + 2 * pad,), -7, dtype=torch.int64, device=DEV)
-    r_all = torch.full((n + 2 * pad, 16), 0xCD, dtype=torch.uint8, device=DEV)
-    size = P.cc_sort_workspace_bytes(n, 3)
-    ws = torch.full((size + pad,), 0xEE, dtype=torch.uint8, device=DEV)
-    P.cc_sort_affinity(torch.tensor(off).to(DEV), keys.to(DEV), rows.to(DEV), k_all[pad:pad + n],
-                       r_all[pad:pad + n], ws[:size], max_keys=50_000)
-    torch.cuda.synchronize()
-    assert bool((k_all[:pad] == -7).all()) and bool((k_all[pad + n:] == -7).all())
-    assert bool((r_all[:pad] == 0xCD).all()) and bool((r_all[pad + n:] == 0xCD).all())
-    assert bool((ws[size:] == 0xEE).all())
-    got = r_all[pad:pad + n].cpu()
-    src = got[(got != 0xCD).any(dim=1)].contiguous().view(torch.int64)[:, 0]
-    assert bool(((src >= 0) & (src < n)).all())
-
-
-@pytest.mark.parametrize("n,part,per,most", [(8_000, PART, 10, 4_096), (40_000, SPLIT, 12, WHOLE)])
-def test_viewers_that_overlap_in_an_overlong_part(n, part, per, most):
-    """Offsets that give the same records to two viewers, whose first part does not fit in LDS: both
-    sort it through the same slices of the workspace, which start out as indexes far below zero. Every
-    row written is one of the call's rows, whatever the two leave there."""
-    note(f"sort: overlapping overlong parts, {n} records")
-    total, pad = n + 5_000, 4_096
-    keys = torch.randint(0, 700, (total,), generator=W.gen("cpu", n, 7))
-    at = torch.from_numpy(_sample_positions(n, 1 + (n - 1) // part, per, most))
-    keys[at] = torch.randint(1_000, 1_000_000_000, (at.numel(),), generator=W.gen("cpu", n, 8))
-    assert int((keys[:n] < 700).sum()) > most
-    rows = torch.arange(total).repeat_interleave(2).view(torch.uint8).reshape(total, 16)
-    k_all = torch.full((total + 2 * pad,), -7, dtype=torch.int64, device=DEV)
-    r_all = torch.full((total + 2 * pad, 16), 0xCD, dtype=torch.uint8, device=DEV)
-    size = P.cc_sort_workspace_bytes(total, 3)
-    for fill in (0xEE, 0x7F):
-        ws = torch.full((size + pad,), fill, dtype=torch.uint8, device=DEV)
-        P.cc_sort_affinity(torch.tensor([0, n, 0, n]).to(DEV), keys.to(DEV), rows.to(DEV),
-                           k_all[pad:pad + total], r_all[pad:pad + total], ws[:size],
-                           max_keys=8_192 if part == PART else n)
-        torch.cuda.synchronize()
-        assert bool((k_all[:pad] == -7).all()) and bool((k_all[pad + total:] == -7).all())
-        assert bool((r_all[:pad] == 0xCD).all()) and bool((r_all[pad + total:] == 0xCD).all())
-        assert bool((ws[size:] == fill).all())
-        got = r_all[pad:pad + total].cpu()
-        src = got[(got != 0xCD).any(dim=1)].contiguous().view(torch.int64)[:, 0]
-        assert src.numel() > most and bool(((src >= 0) & (src < total)).all())
+    note(f"split sort: offsets {off}")
+    _check_inside(off, 50_000, 50_000, SPLIT)
