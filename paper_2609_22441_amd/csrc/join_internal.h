@@ -52,6 +52,7 @@ struct JoinArgs {
     int32_t lds_keys;            // capacity of the dynamic LDS key table
     int32_t fence_stride;        // 0 = chosen per viewer segment
     int32_t fence_budget;        // fences staged per candidate of a segment (automatic stride)
+    int32_t fence_least;         // fences that a segment of any size may have; set by launch_join
     int8_t *valid;               // valid mask of the padded layout's slots (n_max > 0)
     bool wide;                   // rows or strides too long for the pipelined copy; set by launch_join
     bool one_wave;               // automatic grid: one resident wave (long key lists)

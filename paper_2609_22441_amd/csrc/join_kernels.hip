@@ -32,6 +32,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "join_choice.h"
 #include "join_internal.h"
 
 namespace ccj {
@@ -217,15 +218,14 @@ __device__ __forceinline__ void find_key_pair(int64_t x0, int64_t x1, bool valid
 }
 
 // Fence stride for one segment: the smallest power of two whose fence count fits the LDS
-// table and is not much larger than the number of candidates that will use it. A segment of any
-// size may have kStageBatch fences: they are staged by one round of loads. (17,187 candidates in
-// shares of 67, two lookups into 68,767 keys: 22.2 us with at least 512 fences, 17.1 with 4,096.)
+// table and is not much larger than the number of candidates that will use it, or `least`, the
+// fences that a segment of any size may have (least_fences).
 constexpr int kStageUnroll = 16;
-constexpr int64_t kStageBatch = kStageUnroll * kBlock;
+static_assert(kFencesShort == kStageUnroll * kBlock, "one round of staging loads");
 
-__device__ __forceinline__ int choose_stride(int64_t K, int64_t seg_len, int32_t cap,
+__device__ __forceinline__ int choose_stride(int64_t K, int64_t seg_len, int32_t cap, int32_t least,
                                              int32_t forced, int32_t per_cand) {
-    int64_t budget = forced > 0 ? cap : min<int64_t>(cap, max<int64_t>(kStageBatch, per_cand * seg_len));
+    int64_t budget = forced > 0 ? cap : min<int64_t>(cap, max<int64_t>(least, per_cand * seg_len));
     int S = forced > 0 ? forced : 1;
     while ((K + S - 1) / S > budget)
         S <<= 1;
@@ -732,7 +732,8 @@ __global__ __launch_bounds__(kBlock) void join_kernel(JoinArgs a) {
 
         const int64_t K = uniform64(ke - kb);
         const int64_t *gk = a.keys + kb;
-        const int S = choose_stride(K, s1 - s0, a.lds_keys, a.fence_stride, a.fence_budget);
+        const int S = choose_stride(K, s1 - s0, a.lds_keys, a.fence_least, a.fence_stride,
+                                    a.fence_budget);
         const int64_t M = (K + S - 1) / S;
         // Stage the fences into LDS (after the previous segment's readers are done), after the
         // segment's first loads are issued, so the two latencies overlap.
@@ -828,6 +829,7 @@ hipError_t launch_one(JoinArgs &a, int32_t workgroups, int device, hipStream_t s
     if (a.lds_auto && workgroups <= 0 && L == 1 && one_per_cu)
         a.lds_keys = (int32_t)(a.total_keys < kWideLdsKeys ? (a.total_keys > 0 ? a.total_keys : 1)
                                                           : kWideLdsKeys);
+    a.fence_least = least_fences(a.total_keys, std::max(1, a.n_viewers), a.one_wave);
     const size_t lds = (size_t)max(1, a.lds_keys) * sizeof(int64_t);
     // Raise the kernel's dynamic LDS limit once per device (the attribute is per device).
     static std::once_flag lds_limit[kMaxDevices];

@@ -11,6 +11,7 @@ import oracle
 import paper_2609_22441_amd as P
 import workload as W
 from gpu_common import FILL, note
+from kernel_choice import least_fences
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -126,3 +127,40 @@ def test_pad_slots(n_max, wd, we, L):
             assert np.array_equal(valid.cpu().numpy(), want_valid), f"{what}: valid"
         finally:
             P.cc_store_destroy(store)
+
+
+@pytest.mark.parametrize("L", [1, 2])
+@pytest.mark.parametrize("viewers", [78, 79])
+def test_few_candidates_of_many_long_lists(viewers, L):
+    """Either side of the line past which short segments stage few fences: windows of 16 keys below
+    it, and searches between fences 128 keys apart above."""
+    k, n_docs = 40_000, 3_000
+    assert least_fences(viewers, k) == (4_096 if viewers == 78 else 512)
+    note(f"join: {viewers} viewers of {k} keys, {L} lookups")
+    g = W.gen("cpu", viewers, 4)
+    author = torch.randint(-5, 2 * k + 5, (n_docs,), generator=g)
+    doc = torch.randint(0, 256, (n_docs, 48), generator=g, dtype=torch.int64).to(torch.uint8)
+    sizes = [(7 * v) % 41 for v in range(viewers)]
+    reqs = []
+    for n in sizes:
+        keys = 2 * torch.arange(k) + torch.randint(0, 2, (k,), generator=g)
+        edge = torch.arange(k).repeat_interleave(2).view(torch.uint8).reshape(k, 16)
+        cand = torch.randint(-1, n_docs, (n,), generator=g)
+        actor = torch.randint(-1, 2 * k, (n,), generator=g) if L == 2 else None
+        reqs.append(W.Request(keys, edge, cand, actor))
+    b = W.pack(reqs)
+    store = P.cc_store_create(author.to(DEV), doc.to(DEV))
+    try:
+        d, total = b.to(DEV), sum(sizes)
+        out = torch.full((total + GUARD, 48 + 16 * L), FILL, dtype=torch.uint8, device=DEV)
+        hit = torch.full((total + GUARD, L), -7, dtype=torch.int8, device=DEV)
+        P.cc_join_batched(store, d.cand_offsets, d.cand_idx, d.key_offsets, d.keys, d.edge_rows, out,
+                          hit, extra_keys=[d.actor] if L == 2 else None)
+        torch.cuda.synchronize()
+        wo, wh, _ = oracle.join(author, doc, b.cand_offsets, b.cand_idx, b.key_offsets, b.keys,
+                                b.edge_rows, n_lookups=L, extra_keys=[b.actor] if L == 2 else None)
+        assert np.array_equal(out.cpu().numpy()[:total], wo)
+        assert np.array_equal(hit.cpu().numpy()[:total], wh) and 0.3 < wh.mean() < 0.7
+        assert bool((out[total:] == FILL).all()) and bool((hit[total:] == -7).all())
+    finally:
+        P.cc_store_destroy(store)

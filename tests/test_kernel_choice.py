@@ -1,8 +1,8 @@
 """Which kernels a call of given sizes takes, on the CPU (the rules' measured reasons stand in
-csrc/sort_choice.h and csrc/ingest_choice.h)."""
+csrc/sort_choice.h, csrc/ingest_choice.h and csrc/join_choice.h)."""
 import pytest
 
-from kernel_choice import MERGE, PART, RADIX, RANK, SPLIT, choice, commit_apart
+from kernel_choice import MERGE, PART, RADIX, RANK, SPLIT, choice, commit_apart, least_fences
 
 
 @pytest.mark.parametrize("sizes,max_keys,want", [
@@ -50,3 +50,11 @@ def test_very_many_very_short_lists():
 def test_batches_of_many_row_bytes_update_the_map_apart(n, row, want):
     """1,500,000 records of 1,024 bytes: 862 us in one launch, 781 in two."""
     assert commit_apart(n, row) == want
+
+
+@pytest.mark.parametrize("viewers,keys,want", [
+    (1, 68_767, 4_096), (1, 5_000_000, 4_096), (100, 20_000, 4_096), (300, 20_000, 4_096),
+    (32, 60_000, 4_096), (64, 60_000, 512), (100, 40_000, 512), (100, 60_000, 512)])
+def test_short_segments_of_many_long_lists_stage_few_fences(viewers, keys, want):
+    """100 viewers of 60,000 keys with 10 candidates each: 10 us with 512 fences, 15.7 with 4,096."""
+    assert least_fences(viewers, keys) == want
