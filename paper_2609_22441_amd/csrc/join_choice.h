@@ -25,4 +25,18 @@ inline int32_t least_fences(int64_t total_keys, int64_t viewers, bool long_lists
     return long_lists && bytes > kFenceBytes ? kFencesLeast : kFencesShort;
 }
 
+// Number of ranges near n, at most `most`, that is a multiple of the viewers; 0 where there is none. A
+// range that holds the end of one viewer and the start of the next goes through two segments one after
+// the other, each with its own fences and first sub-tile. With equal viewers a multiple of them avoids
+// it: 16 viewers of 160 candidates and 10,000 keys 12.0 -> 8.3, 3 of 250 11.8 -> 8.3, 16 of 1,000 and
+// 20,000 keys 13.5 -> 9.7, 100 of 10 and 60,000 keys 65.4 -> 10.0. More ranges than asked for cost little
+// (a few candidates less for each); fewer are taken down to 15 of 16 only, for ragged viewers gain nothing
+// from them (150 of 1,000 on average: 17.6 on 512 ranges, 19.0 on 450).
+inline int64_t ranges_of_viewers(int64_t n, int64_t viewers, int64_t most) {
+    const int64_t up = (n + viewers - 1) / viewers * viewers, down = n / viewers * viewers;
+    if (up <= most)
+        return up;
+    return 16 * down >= 15 * n ? down : 0;
+}
+
 }  // namespace ccj

@@ -59,6 +59,7 @@ struct JoinArgs {
     bool lds_auto;               // lds_keys chosen by the library (not by a tuning)
     bool balanced;               // CSR ranges weighted by an estimated cost per candidate
     int32_t n_wg;                // workgroups launched (a multiple of 8); set by launch_join
+    int32_t n_ranges;            // weighted ranges (balanced), at most n_wg; set by launch_join
     int64_t per_wg;              // candidates per workgroup; set by launch_join
 };
 

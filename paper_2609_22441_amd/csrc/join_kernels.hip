@@ -284,8 +284,8 @@ __device__ __forceinline__ int64_t wave_scan_incl(int64_t x) {
 // Weighted ranges for a CSR batch of at most kBalanceViewers viewers. Candidate i of viewer v
 // weighs w_v = cand_cost(K_v) (in the padded layout only its first n_max candidates, the ones
 // joined, count); with prefix weights P, logical range r of n covers the candidates
-// whose weight starts in [T_r, T_{r+1}), T_r = floor(r * W / n), W the total. Every workgroup
-// computes the same prefix, so the ranges tile the candidates. Ranges of equal weight take
+// whose weight starts in [T_r, T_{r+1}), T_r = floor(r * W / n), W the total (none where r >= n).
+// Every workgroup computes the same prefix, so the ranges tile the candidates. Ranges of equal weight take
 // fewer candidates of long lists, which would otherwise finish last. (A cost for starting a
 // viewer, charged to the range that holds its first candidate, helped ragged batches by 1% but
 // slowed batches of equal viewers, whose ranges start exactly at viewer starts, by 2%.) Returns
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(kBlock) void join_kernel(JoinArgs a) {
     int64_t begin, end;
     int32_t v = 0;                                // first viewer that may hold `begin`
     if (batched && a.balanced) {
-        balanced_range(a, rng, gridDim.x, reinterpret_cast<int64_t *>(&s_ptr[0]), begin, end, v);
+        balanced_range(a, rng, a.n_ranges, reinterpret_cast<int64_t *>(&s_ptr[0]), begin, end, v);
     } else {
         begin = rng * a.per_wg;
         end = min(begin + a.per_wg, a.total_cand);
@@ -858,7 +858,9 @@ hipError_t launch_one(JoinArgs &a, int32_t workgroups, int device, hipStream_t s
     //     6.5 on 256, 7.4 on 320), or of one per 128 keys up to a sub-tile: every share stages its
     //     viewer's fences, a line each (17,187 candidates, two lookups into 68,767 keys: 17.3 us
     //     in sub-tiles, 22.6 in shares of 67).
-    int64_t n_wg = workgroups;
+    //   * Launches of up to four sub-tiles per CU: a multiple of the viewers, where one is near
+    //     (ranges_of_viewers), so that ranges of equal viewers do not share one.
+    int64_t n_wg = workgroups, ranges = 0;
     if (n_wg <= 0) {
         const int resident = resident_per_cu(fn, lds);
         const int64_t share = std::min<int64_t>(
@@ -871,17 +873,20 @@ hipError_t launch_one(JoinArgs &a, int32_t workgroups, int device, hipStream_t s
             n_wg = cus * std::min(2, resident);
         else
             n_wg = std::min(cus, (a.total_cand + share - 1) / share);
+        if (a.balanced && !one_per_cu && tiles <= 2 * std::max(n_wg, cus))
+            ranges = ranges_of_viewers((n_wg + 7) & ~int64_t(7), a.n_viewers, std::max(n_wg, cus));
     }
     // The padded layout's slots are filled by the same launch: 8 blocks of 64 per wavefront.
     const int64_t fill = a.n_max > 0 ? (int64_t)a.n_viewers * ((a.n_max + 63) / 64) / 32 : 0;
     const int64_t least = std::max<int64_t>(1, std::min(cus, fill));
     const int64_t most = (a.total_cand + kMinRange - 1) / kMinRange;
-    n_wg = std::max(least, std::min(n_wg, most));
+    n_wg = std::max(least, ranges ? ranges : std::min(n_wg, most));
     a.per_wg = (a.total_cand + n_wg - 1) / n_wg;
     if (!a.balanced && a.per_wg > 0)      // none left empty
         n_wg = std::max(least, (a.total_cand + a.per_wg - 1) / a.per_wg);
     n_wg = (n_wg + 7) & ~int64_t(7);
     a.n_wg = (int32_t)n_wg;
+    a.n_ranges = (int32_t)(ranges ? ranges : n_wg);
     hipLaunchKernelGGL((join_kernel<D, E, L, BATCHED, A32>), dim3(a.n_wg), dim3(kBlock), lds, stream,
                        a);
     return hipGetLastError();

@@ -21,6 +21,9 @@ extern "C" int choice(int64_t total, int64_t n_viewers, int64_t max_keys) {
 extern "C" int apart(int64_t n_records, int64_t row_bytes) {
     return ccj::commit_apart(n_records, row_bytes);
 }
+extern "C" int64_t ranges(int64_t n, int64_t viewers, int64_t most) {
+    return ccj::ranges_of_viewers(n, viewers, most);
+}
 extern "C" int fences(int64_t total_keys, int64_t viewers, int long_lists) {
     return ccj::least_fences(total_keys, viewers, long_lists);
 }
@@ -37,6 +40,7 @@ def _shim():
         lib = ctypes.CDLL(str(out))
     lib.choice.argtypes = [ctypes.c_int64] * 3
     lib.apart.argtypes = [ctypes.c_int64] * 2
+    lib.ranges.argtypes, lib.ranges.restype = [ctypes.c_int64] * 3, ctypes.c_int64
     lib.fences.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
     return lib
 
@@ -53,3 +57,7 @@ def commit_apart(n_records, row_bytes) -> bool:
 def least_fences(viewers, keys) -> int:
     """Of viewers with `keys` keys each (lists of more than 32,768 on average count as long)."""
     return _shim().fences(viewers * keys, viewers, keys > 32_768)
+
+
+def ranges_of_viewers(n, viewers, most) -> int:
+    return _shim().ranges(n, viewers, most)

@@ -130,6 +130,17 @@ def test_pad_slots(n_max, wd, we, L):
 
 
 @pytest.mark.parametrize("L", [1, 2])
+@pytest.mark.parametrize("wd,we", [(128, 64), (48, 80)])
+@pytest.mark.parametrize("viewers", [2, 3, 7, 12, 100, 255, 256, 257])
+def test_ranges_by_viewers(viewers, wd, we, L):
+    """Small launches whose ranges are a multiple of the viewers (idle workgroups behind them, ranges of
+    one candidate) and, past 256 viewers, are not; equal viewers and ragged ones."""
+    for sizes in ([1] * viewers, [160] * viewers, [(37 * v + 11) % 301 for v in range(viewers)],
+                  [0] * (viewers - 1) + [700]):
+        _check(sizes, wd, we, L, viewers, wd + L * we, True, f"{viewers} viewers of {sizes[:3]}.., x{L}")
+
+
+@pytest.mark.parametrize("L", [1, 2])
 @pytest.mark.parametrize("viewers", [78, 79])
 def test_few_candidates_of_many_long_lists(viewers, L):
     """Either side of the line past which short segments stage few fences: windows of 16 keys below
