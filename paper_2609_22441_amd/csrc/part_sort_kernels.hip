@@ -90,6 +90,14 @@ __device__ __forceinline__ int wave_index() {
     return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
 }
 
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) {
+    return __builtin_amdgcn_readfirstlane((int)x);
+}
+__device__ __forceinline__ int64_t uniform(int64_t x) {
+    return (int64_t)(((uint64_t)uniform((uint32_t)((uint64_t)x >> 32)) << 32) | uniform((uint32_t)x));
+}
+
 __device__ __forceinline__ int lanes_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -599,26 +607,17 @@ __device__ __forceinline__ int64_t split_record(const SH &sh, const Part &pt,
     return sp.key[pt.kb + at];
 }
 
-// A part of m > kCap records, by digit passes through the workspace's element arrays: the
-// records in input order into a[0, m), then one stable pass per digit between a and b, each a
-// count of the digits and a scatter of chunks of kPartThreads. Called by the whole workgroup; a and b
-// are the part's own slices. Written for few registers: it shares the kernel with the path above.
+// The records of a part of m > kCap, in input order, to a[0, m); lo and hi their key range. Called by the
+// whole workgroup; a is the part's own slice of the workspace. Has a barrier behind the range.
 template <typename SH>
-__device__ __forceinline__ void big_part(SH &sh, const int64_t *__restrict__ keys,
-                                         const Part &pt, const Bounds &bd, const Split *sp,
-                                         uint32_t m, Elem *a, Elem *b, int64_t to,
-                                         const SortOut &o) {
+__device__ __forceinline__ void gather_part(SH &sh, const int64_t *__restrict__ keys,
+                                            const Part &pt, const Bounds &bd, uint32_t m, Elem *a,
+                                            int64_t &lo, int64_t &hi) {
     const int tid = thread_index(), lane = tid & 63, w = wave_index();
-    int64_t lo = INT64_MAX, hi = INT64_MIN;
+    lo = INT64_MAX;
+    hi = INT64_MIN;
     uint32_t found = 0;
-    for (uint32_t i = tid; sp && i < m; i += kPartThreads) {
-        uint32_t p;
-        const int64_t k = split_record(sh, pt, *sp, i, p);
-        lo = min(lo, k);
-        hi = max(hi, k);
-        a[i] = Elem{(uint64_t)k, p};
-    }
-    for (uint32_t p0 = 0; !sp && p0 < pt.n; p0 += kPartThreads) {
+    for (uint32_t p0 = 0; p0 < pt.n; p0 += kPartThreads) {
         const uint32_t p = p0 + tid;
         const int64_t k = keys[pt.kb + min(p, pt.n - 1)];
         const bool in = p < pt.n && (k > bd.k0 || (k == bd.k0 && p >= bd.p0)) &&
@@ -642,6 +641,32 @@ __device__ __forceinline__ void big_part(SH &sh, const int64_t *__restrict__ key
         lds_sync();                                      // run is written again
     }
     key_range(sh, lo, hi);
+}
+
+// The same where split_kernel has put the part's records together.
+template <typename SH>
+__device__ __forceinline__ void gather_part(SH &sh, const Part &pt, const Split &sp, uint32_t m,
+                                            Elem *a, int64_t &lo, int64_t &hi) {
+    lo = INT64_MAX;
+    hi = INT64_MIN;
+    for (uint32_t i = thread_index(); i < m; i += kPartThreads) {
+        uint32_t p;
+        const int64_t k = split_record(sh, pt, sp, i, p);
+        lo = min(lo, k);
+        hi = max(hi, k);
+        a[i] = Elem{(uint64_t)k, p};
+    }
+    key_range(sh, lo, hi);
+}
+
+// A part of m > kCap records, by digit passes through the workspace's element arrays: one stable pass
+// per digit between a (where the records are, in input order) and b, each a count of the digits and a
+// scatter of chunks of kPartThreads. Called by the whole workgroup; a and b are the part's own slices.
+// Written for few registers: it shares the kernel with the path above.
+template <typename SH>
+__device__ __forceinline__ void big_part(SH &sh, const Part &pt, uint32_t m, int64_t lo, int64_t hi,
+                                         Elem *a, Elem *b, int64_t to, const SortOut &o) {
+    const int tid = thread_index(), w = wave_index();
     const Digits dg = digits_of((uint64_t)hi - (uint64_t)lo);
     __syncthreads();                                     // the stores, before their readers
 #pragma unroll 1
@@ -763,26 +788,162 @@ __device__ __forceinline__ void sort_part(SH &sh, const int64_t *__restrict__ ke
         emit(sh, pt, (uint64_t)kmin, (int)m, to, o);
     } else {
         const Bounds bd{sh.bound_key[0], sh.bound_key[1], sh.bound_pos[0], sh.bound_pos[1]};
-        big_part(sh, keys, pt, bd, nullptr, m, buf0 + to, buf1 + to, to, o);
+        int64_t lo, hi;
+        gather_part(sh, keys, pt, bd, m, buf0 + to, lo, hi);
+        big_part(sh, pt, m, lo, hi, buf0 + to, buf1 + to, to, o);
     }
 }
 
-// The same for a part whose records split_kernel has put together, or a viewer that was not split
-// (at most SH::kCap records, one part).
+// ---- overlong parts of split calls, a piece at a time -----------------------------------------
+//
+// A part of up to kPieces times what LDS holds is cut once more, by a histogram of its records over
+// 256 equal shares of its key span: runs of shares that fit are picked from its records (in input order,
+// at a[0, m)) and sorted in LDS one after the other. 1 x 100,000 records with one part of 2,300: 25 us
+// without it, 41 in pieces, 71 by digit passes; rows of 128 bytes 33, 54 and 92. 
+constexpr uint32_t kPieces = 4;
+
+// (Bounded whatever an overlapping viewer, from malformed offsets, has left in its place.)
+__device__ __forceinline__ uint32_t share_of(uint64_t key, int64_t lo, int shift) {
+    const uint64_t s = (key - (uint64_t)lo) >> shift;
+    return s < kRadix ? (uint32_t)s : kRadix - 1;
+}
+
+// sh.adj[b] becomes the number of records in shares 0 to b, `shift` the width of a share. False where a
+// share alone does not fit. Called after gather_part; ends with a barrier, behind which a can be read.
+template <typename SH>
+__device__ __forceinline__ bool count_shares(SH &sh, const Elem *a, uint32_t m, int64_t lo, int64_t hi,
+                                             int &shift) {
+    const int tid = thread_index(), lane = tid & 63;
+    const uint64_t span = (uint64_t)hi - (uint64_t)lo;
+    shift = (int)uniform((uint32_t)max(0, (span ? 64 - __clzll(span) : 0) - kBits));
+    if (tid < kRadix)
+        sh.start[tid] = 0;
+    lds_sync();
+    for (uint32_t i = tid; i < m; i += kPartThreads)     // its own records of gather_part
+        atomicAdd(&sh.start[share_of(a[i].key, lo, shift)], 1u);
+    lds_sync();
+    if (wave_index() == 0) {
+        uint32_t c[4], sum = 0, most = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            c[j] = sh.start[lane * 4 + j];
+            sum += c[j];
+            most = max(most, c[j]);
+        }
+        uint32_t at = wave_scan(sum) - sum;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            sh.adj[lane * 4 + j] = at += c[j];
+        const uint64_t over = __ballot(most > (uint32_t)SH::kCap);
+        if (lane == 0)
+            sh.below[0] = over != 0;
+    }
+    __syncthreads();
+    return sh.below[0] == 0;
+}
+
+// The records behind the first `done` of the part, as many whole shares as fit in LDS: to sh.key and
+// sh.pos in input order. Returns their number. Called with a barrier behind the last use of sh.key;
+// ends with one.
+template <typename SH>
+__device__ __forceinline__ uint32_t pick_shares(SH &sh, const Elem *a, uint32_t m, int64_t lo,
+                                                int shift, uint32_t done) {
+    const int tid = thread_index(), lane = tid & 63, w = wave_index();
+    uint32_t b0 = 0, b1 = 0;                             // shares [b0, b1)
+#pragma unroll
+    for (uint32_t half = kRadix / 2; half > 0; half >>= 1) {
+        b0 += sh.adj[b0 + half - 1] <= done ? half : 0;
+        b1 += sh.adj[b1 + half - 1] <= done + SH::kCap ? half : 0;
+    }
+    b1 += sh.adj[b1] <= done + SH::kCap ? 1 : 0;         // the last share too
+    const uint32_t count = sh.adj[b1 - 1] - done;
+    uint32_t found = 0;
+    for (uint32_t p0 = 0, turn = 0; p0 < m; p0 += kPartThreads, turn ^= 1) {
+        const uint32_t p = p0 + tid;
+        const Elem e = a[min(p, m - 1)];
+        const uint32_t s = share_of(e.key, lo, shift);
+        const bool in = p < m && s >= b0 && s < b1;
+        const uint64_t mask = __ballot(in);
+        if (lane == 0)
+            sh.run[turn][w] = __popcll(mask);
+        lds_sync();
+        uint32_t at = found + lanes_below(mask);
+#pragma unroll 1
+        for (int q = 0; q < kPartWaves; ++q) {
+            at += q < w ? sh.run[turn][q] : 0;
+            found += sh.run[turn][q];
+        }
+        if (in && at < (uint32_t)SH::kCap) {
+            sh.key[at] = e.key;
+            sh.pos[at] = (uint32_t)e.pos;
+        }
+    }
+    lds_sync();
+    return count;
+}
+
+// A part of m > kCap records: in pieces, or by digit passes where these do not do.
+template <typename SH>
+__device__ __forceinline__ void overlong_part(SH &sh, const Part &pt, const Split &sp, uint32_t m,
+                                              Elem *a, Elem *b, int64_t to, const SortOut &o) {
+    constexpr int kEpt = SH::kEpt;
+    int64_t lo, hi;
+    int shift;
+    gather_part(sh, pt, sp, m, a, lo, hi);
+    if (m > kPieces * (uint32_t)SH::kCap || !count_shares(sh, a, m, lo, hi, shift)) {
+        big_part(sh, pt, m, lo, hi, a, b, to, o);
+        return;
+    }
+#pragma unroll 1
+    for (uint32_t done = 0; done < m;) {                 // uniform
+        const uint32_t count = uniform(pick_shares(sh, a, m, uniform(lo), shift, done));
+        uint64_t key[kEpt];
+        uint32_t pos[kEpt];
+        const Rounds rs((int)count);
+#pragma unroll
+        for (int r = 0; r < kEpt; ++r) {
+            if (r < rs.R) {                              // uniform
+                const uint32_t i = min((uint32_t)rs.at(r), count - 1);
+                key[r] = sh.key[i];
+                // What an overlapping viewer (malformed offsets) left here may lie past n.
+                pos[r] = min(sh.pos[i], pt.n - 1);
+            }
+        }
+        lds_sync();                                      // sh.key is written again
+        const uint64_t kmin = (uint64_t)sort_lds(sh, rs, key, pos);
+        for (uint32_t i = thread_index(); i < count; i += kPartThreads)
+            o.keys_out[to + done + i] = (int64_t)(sh.key[i] + kmin);
+        const int64_t chunks = (int64_t)count * o.row_chunks;
+        const int64_t first = (to + done) * o.row_chunks;
+#pragma unroll 4
+        for (int64_t c = thread_index(); c < chunks; c += kPartThreads) {
+            const uint32_t i = (uint32_t)((uint64_t)c / (uint32_t)o.row_chunks);
+            const int64_t from = pt.kb + sh.pos[i];
+            o.rows_out[first + c] =
+                o.rows_in[from * o.row_chunks + (c - (int64_t)i * o.row_chunks)];
+        }
+        done += count;
+        lds_sync();                                      // sh.key is written again
+    }
+}
+
+// A part whose records split_kernel has put together, or a viewer that was not split (at most SH::kCap
+// records, one part).
 template <typename SH>
 __device__ __forceinline__ void sort_split_part(SH &sh, const int64_t *__restrict__ keys,
                                                 const Part &pt, const Split &sp, Elem *buf0,
                                                 Elem *buf1, const SortOut &o) {
     constexpr int kEpt = SH::kEpt;
+    constexpr uint32_t kCap = SH::kCap;
     const bool whole = pt.n <= kSplitCap;
     uint32_t below = 0, m = pt.n;
     if (!whole)
-        m = find_records(sh, pt, sp, below);
+        m = uniform(find_records(sh, pt, sp, below));
     if (m == 0)
         return;
-    const int64_t to = pt.kb + below;
-    if (m > SH::kCap) {
-        big_part(sh, keys, pt, Bounds{}, &sp, m, buf0 + to, buf1 + to, to, o);
+    const int64_t to = uniform(pt.kb + below);
+    if (m > kCap) {
+        overlong_part(sh, pt, sp, m, buf0 + to, buf1 + to, to, o);
         return;
     }
     uint64_t key[kEpt];
@@ -856,7 +1017,8 @@ __global__ __launch_bounds__(kPartThreads, SPLIT ? 8 : 4) void part_sort_kernel(
         return;
     }
     if constexpr (SPLIT)
-        sort_split_part(sh, keys, pt, sp, buf0, buf1, o);
+        sort_split_part(sh, keys, Part{uniform(pt.kb), uniform(pt.n), uniform(pt.g), uniform(pt.G)}, sp,
+                        buf0, buf1, o);
     else
         sort_part(sh, keys, pt, buf0, buf1, o);
 }
@@ -881,10 +1043,9 @@ __global__ __launch_bounds__(kPartThreads, SPLIT ? 8 : 4) void part_sort_kernel(
 // of the sample, the rarer the more sample records a part has: kPerSplit of them up to 170 parts
 // (108,000 records), fewer in longer viewers, whose sample is full, 8 at the longest. Per part (the
 // share of a part is close to a gamma variate): 2e-7 at 12, 1.3e-6 at 200 parts, 4.4e-6 at 225, 1.4e-5
-// at 255, which is one viewer of kSplitMax records in 280. A call that has one takes 45 to 55 us longer
-// (1 x 100,000 with a part of 2,400: 25 -> 71, rows of 128 bytes 33 -> 92). Half of the keys in a tenth
-// of the span, parts that start at their share's edge: the largest of 47,000 parts had 2,027 records;
-// as far into it as above, 1,714 of 63,000.
+// at 255, which is one viewer of kSplitMax records in 280. (One is sorted in pieces, below.) Half of the
+// keys in a tenth of the span, parts that start at their share's edge: the largest of 47,000 parts had
+// 2,027 records; as far into it as above, 1,714 of 63,000.
 //
 // Bound by its dependent steps and the instructions of the ranking: 3.2M records 37.9 us with four
 // workgroups per CU, where 38 MB in and out alone take 12. Sorting the sample by 16 key bits instead

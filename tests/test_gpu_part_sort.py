@@ -321,6 +321,31 @@ def test_split_part_that_the_sample_misjudged(n, lead):
            max_keys=n)
 
 
+@pytest.mark.parametrize("row", [16, 144])
+@pytest.mark.parametrize("kind", ["spread", "repeats", "two", "equal"])
+@pytest.mark.parametrize("extra", [1_800, 2_200, 5_000, 7_300, 9_000])
+def test_split_overlong_part_in_pieces(extra, kind, row):
+    """One part of a little more than LDS holds up to more than four times that, its records spread,
+    repeated, in two far groups, or all alike (a share of its key span that does not fit either)."""
+    n = 60_000
+    g = W.gen("cpu", extra, 7)
+    keys = torch.randint(0, 1 << 40, (n,), generator=g)
+    free = torch.ones(n, dtype=torch.bool)
+    free[torch.from_numpy(_sample_positions(n, _parts(0, n, SPLIT_PART), 12, WHOLE))] = False
+    at = free.nonzero()[:, 0]
+    at = at[torch.randperm(at.numel(), generator=g)[:extra]]
+    wide = (1 << 40) // 2_000                    # a fifth of a part's share of the span
+    v = {"spread": torch.randint(0, wide, (extra,), generator=g),
+         "repeats": torch.randint(0, 40, (extra,), generator=g) * (wide // 40),
+         "two": torch.randint(0, 2, (extra,), generator=g) * wide,
+         "equal": torch.zeros(extra, dtype=torch.int64)}[kind]
+    keys[at] = (1 << 39) + v
+    inside = int(((keys >= 1 << 39) & (keys <= (1 << 39) + wide)).sum())
+    assert inside >= extra
+    _check([n, 300], torch.cat([keys, _keys("ids", 300, 1)]), f"part of {inside} {kind}", SPLIT, row=row,
+           max_keys=n)
+
+
 def test_split_viewers_above_the_bound_are_copied_through():
     sizes = [30_000, 9_000, 300, 50_000, 8_200]
     ko = torch.tensor([0] + np.cumsum(sizes).tolist(), dtype=torch.int64)
