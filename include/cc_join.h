@@ -432,9 +432,10 @@ CC_API cc_status cc_sort_affinity(int32_t n_viewers, const int64_t *key_offsets,
  *                  exceed 162,560 records, take two launches: records are put in order of the
  *                  parts of their viewer's key order first. Calls whose records times longest list
  *                  (max_keys, or all records where it is 0) are few enough take one launch, in which
- *                  every workgroup finds and sorts one part. The rest take CC_SORT_RADIX from
- *                  CC_SORT_RADIX_MIN_RECORDS records on, else CC_SORT_MERGE. A call that names
- *                  its longest list as max_keys is therefore often the faster one.
+ *                  every workgroup finds and sorts one part; other calls of up to 2^19 records the
+ *                  two launches. The rest take CC_SORT_RADIX from CC_SORT_RADIX_MIN_RECORDS records
+ *                  on, else CC_SORT_MERGE. A caller that knows its longest list and names it as
+ *                  max_keys often gets the faster method.
  *   key_bits       0, or an upper bound on the bit length of (largest key - smallest key) over
  *                  the call (at most 64): the radix method then launches only the passes such a
  *                  span needs (ceil(key_bits / 9), e.g. 3 for author ids below 2^27), where it

@@ -44,7 +44,7 @@ constexpr int kRadix = 1 << kBits;
 constexpr int kSampleMin = 64;
 constexpr int kPerPart = 10;                   // sample records per part
 constexpr int kSampleCount = 256;              // samples up to this size are ranked by counting
-static_assert(kPartUnboundedTotal < kPartMaxRecords && kPartLarge < kPartMaxRecords &&
+static_assert(kSplitTotal < kPartMaxRecords && kPartLarge < kPartMaxRecords &&
                   kPartMaxWork <= (kPartMaxRecords - 1) * (kPartMaxRecords - 1),
               "every viewer of a call that the automatic choice sends here can be sorted");
 
@@ -555,8 +555,13 @@ __device__ __forceinline__ void emit(const SH &sh, const Part &pt, uint64_t kmin
 // sh.start[c] + i the place of the part's record i, if it is in chunk c. Returns their number, below
 // the number of records below the part (what every chunk holds of earlier parts). Entries are
 // clamped to their chunk, whatever malformed offsets made of them. Ends with a barrier.
-constexpr int kChunks = 128;                   // of one viewer, at most
-static_assert(kSplitMax <= (int64_t)(kChunks - 2) * kChunk && kChunks <= kRadix, "two per lane");
+constexpr int kChunks = 256;                   // of one viewer, at most
+static_assert(kSplitTotal <= (int64_t)(kChunks - 2) * kChunk && kChunks <= kRadix, "four per lane");
+
+// Chunks that a lane looks at: two, or four for viewers of more than 128.
+__device__ __forceinline__ uint32_t chunks_per_lane(const Part &pt) {
+    return parts_of(pt.kb, pt.kb + pt.n, kChunk) > kChunks / 2 ? kChunks / 64 : kChunks / 128;
+}
 
 template <typename SH>
 __device__ __forceinline__ uint32_t find_records(SH &sh, const Part &pt, const Split &sp,
@@ -564,26 +569,33 @@ __device__ __forceinline__ uint32_t find_records(SH &sh, const Part &pt, const S
     if (wave_index() == 0) {
         const int lane = thread_index() & 63;
         const uint32_t C = parts_of(pt.kb, pt.kb + pt.n, kChunk);
-        uint32_t len[2], at[2], under = 0;
+        const int per = (int)chunks_per_lane(pt);
+        uint32_t len[kChunks / 64], at[kChunks / 64], sum = 0, under = 0;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const uint32_t c = min((uint32_t)(2 * lane + j), C - 1);
-            const uint32_t c0 = part_begin(pt.n, c, C), cn = part_begin(pt.n, c + 1, C) - c0;
-            const uint16_t *row = sp.start + sp.row(pt.kb, c) * kRadix;
-            const uint32_t s = min((uint32_t)row[pt.g], cn);
-            const uint32_t e = pt.g + 1 < kRadix ? row[pt.g + 1] : cn;
-            const bool real = (uint32_t)(2 * lane + j) < C;
-            at[j] = c0 + s;
-            len[j] = real ? max(s, min(e, cn)) - s : 0;
-            under += real ? s : 0;
+        for (int j = 0; j < kChunks / 64; ++j) {
+            if (j < per) {                               // uniform
+                const uint32_t q = per * lane + j, c = min(q, C - 1);
+                const uint32_t c0 = part_begin(pt.n, c, C), cn = part_begin(pt.n, c + 1, C) - c0;
+                const uint16_t *row = sp.start + sp.row(pt.kb, c) * kRadix;
+                const uint32_t s = min((uint32_t)row[pt.g], cn);
+                const uint32_t e = pt.g + 1 < kRadix ? row[pt.g + 1] : cn;
+                at[j] = c0 + s;
+                len[j] = q < C ? max(s, min(e, cn)) - s : 0;
+                sum += len[j];
+                under += q < C ? s : 0;
+            }
         }
-        const uint32_t end = wave_scan(len[0] + len[1]);
-        const uint32_t b = end - len[0] - len[1];
+        const uint32_t end = wave_scan(sum);
+        uint32_t b = end - sum;
         under = wave_scan(under);
-        sh.adj[2 * lane] = b;
-        sh.adj[2 * lane + 1] = b + len[0];
-        sh.start[2 * lane] = at[0] - b;                  // modulo 2^32
-        sh.start[2 * lane + 1] = at[1] - b - len[0];
+#pragma unroll
+        for (int j = 0; j < kChunks / 64; ++j) {
+            if (j < per) {
+                sh.adj[per * lane + j] = b;
+                sh.start[per * lane + j] = at[j] - b;    // modulo 2^32
+                b += len[j];
+            }
+        }
         if (lane == 63) {
             sh.run[0][0] = end;
             sh.below[0] = under;
@@ -599,8 +611,10 @@ __device__ __forceinline__ int64_t split_record(const SH &sh, const Part &pt,
                                                 const Split &sp, uint32_t i, uint32_t &p) {
     // The last chunk that starts at or before record i.
     uint32_t c = 0;
+    if (chunks_per_lane(pt) > kChunks / 128)             // uniform
+        c = sh.adj[kChunks / 2] <= i ? kChunks / 2 : 0;
 #pragma unroll
-    for (uint32_t half = kChunks / 2; half > 0; half >>= 1)
+    for (uint32_t half = kChunks / 4; half > 0; half >>= 1)
         c += sh.adj[c + half] <= i ? half : 0;
     const uint32_t at = min(sh.start[c] + i, pt.n - 1);
     p = min(sp.pos[pt.kb + at], pt.n - 1);
@@ -799,7 +813,8 @@ __device__ __forceinline__ void sort_part(SH &sh, const int64_t *__restrict__ ke
 // A part of up to kPieces times what LDS holds is cut once more, by a histogram of its records over
 // 256 equal shares of its key span: runs of shares that fit are picked from its records (in input order,
 // at a[0, m)) and sorted in LDS one after the other. 1 x 100,000 records with one part of 2,300: 25 us
-// without it, 41 in pieces, 71 by digit passes; rows of 128 bytes 33, 54 and 92. 
+// without it, 41 in pieces, 71 by digit passes; rows of 128 bytes 33, 54 and 92. One of 300,000 among
+// 1,000 short lists (parts of 1,170, some overlong), 62-bit keys, rows of 128 bytes: 96 against 189.
 constexpr uint32_t kPieces = 4;
 
 // (Bounded whatever an overlapping viewer, from malformed offsets, has left in its place.)
@@ -974,10 +989,11 @@ __device__ __forceinline__ void copy_slice(const int64_t *__restrict__ keys, int
 
 // Work items: one per viewer (its part 0), then one per multiple of `part` in [part, total). The
 // multiple a * part that falls strictly inside a viewer is one more part of it, so a viewer's
-// parts are numbered by the multiples it covers and no scan over the viewers is needed. False for
-// items without records (and where offsets break the rules).
+// parts are numbered by the multiples it covers and no scan over the viewers is needed. A viewer of
+// more than `most` parts is cut into `most`, its items taken together in even runs. False for items
+// without records or inside a run (and where offsets break the rules).
 __device__ __forceinline__ bool part_of(const int64_t *off, int32_t B, int64_t total, int32_t part,
-                                        int64_t whole, Part &pt, int64_t &n) {
+                                        int64_t whole, uint32_t most, Part &pt, int64_t &n) {
     const int64_t it = blockIdx.x;
     int64_t v, a = 0;
     if (it < B) {
@@ -997,6 +1013,13 @@ __device__ __forceinline__ bool part_of(const int64_t *off, int32_t B, int64_t t
         return false;
     pt.n = (uint32_t)n;
     pt.g = (uint32_t)g;
+    if (pt.G > most && n < kPartMaxRecords) {
+        const uint32_t run = pt.g * most / pt.G;         // both below 2^12: see the limit of n
+        if (pt.g > 0 && run == (pt.g - 1) * most / pt.G)
+            return false;
+        pt.g = run;
+        pt.G = most;
+    }
     return true;
 }
 
@@ -1009,7 +1032,7 @@ __global__ __launch_bounds__(kPartThreads, SPLIT ? 8 : 4) void part_sort_kernel(
     __shared__ PartTables<SPLIT ? kSplitEpt : kEpt> sh;
     Part pt;
     int64_t n;
-    if (!part_of(off, B, o.total, part, SPLIT ? kSplitCap : part, pt, n))
+    if (!part_of(off, B, o.total, part, SPLIT ? kSplitCap : part, SPLIT ? kRadix : ~0u, pt, n))
         return;
     if (n > o.limit || n >= kPartMaxRecords) {        // larger than the caller's bound
         const int64_t b0 = pt.kb + n * pt.g / pt.G, b1 = pt.kb + n * (pt.g + 1) / pt.G;
@@ -1045,7 +1068,8 @@ __global__ __launch_bounds__(kPartThreads, SPLIT ? 8 : 4) void part_sort_kernel(
 // share of a part is close to a gamma variate): 2e-7 at 12, 1.3e-6 at 200 parts, 4.4e-6 at 225, 1.4e-5
 // at 255, which is one viewer of kSplitMax records in 280. (One is sorted in pieces, below.) Half of the
 // keys in a tenth of the span, parts that start at their share's edge: the largest of 47,000 parts had
-// 2,027 records; as far into it as above, 1,714 of 63,000.
+// 2,027 records; as far into it as above, 1,714 of 63,000. Viewers of more than kSplitMax records have
+// longer parts, the longest 2,048 on average.
 //
 // Bound by its dependent steps and the instructions of the ranking: 3.2M records 37.9 us with four
 // workgroups per CU, where 38 MB in and out alone take 12. Sorting the sample by 16 key bits instead
@@ -1167,11 +1191,11 @@ __global__ __launch_bounds__(kPartThreads, 8) void split_kernel(
     PartTables<kSplitEpt> &sh = ss.p;
     Part ck;                                             // the chunk
     int64_t n64;
-    if (!part_of(off, B, o.total, kChunk, kChunk, ck, n64) || n64 <= kSplitCap || n64 > o.limit ||
+    if (!part_of(off, B, o.total, kChunk, kChunk, ~0u, ck, n64) || n64 <= kSplitCap || n64 > o.limit ||
         n64 >= kPartMaxRecords)
         return;
     const int tid = thread_index(), w = wave_index();
-    const Part pt{ck.kb, ck.n, 0, parts_of(ck.kb, ck.kb + n64, kPartSplit)};
+    const Part pt{ck.kb, ck.n, 0, min(parts_of(ck.kb, ck.kb + n64, kPartSplit), (uint32_t)kRadix)};
     const uint32_t c0 = part_begin(ck.n, ck.g, ck.G);
     const int n = (int)(part_begin(ck.n, ck.g + 1, ck.G) - c0);
     const Rounds rs(n);

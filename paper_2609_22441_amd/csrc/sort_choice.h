@@ -53,16 +53,6 @@ constexpr int64_t kPartMaxWorkWhole = (int64_t)1 << 36;      // ... of viewers o
 // x 8 17,460 / 12,306, 600,000 x 16 8,757 / 7,915, 600,000 x 24 8,831 / 10,540.
 constexpr int64_t kPartMinMean = 20;
 
-// A call without a bound on its viewers (max_keys = 0) is taken to hold one viewer of all its records:
-// 1,000 viewers of 20 records and one of 130,000 90 / 90, of 300,000 158 / 116, of 500,000
-// 257 / 126. (Taking none to be longer than 16 times the mean cost such calls up to twice the time;
-// without it 64 x 5,000 records take 70 us instead of 29 where the caller names no bound.) Except up
-// to kPartUnboundedTotal records in viewers of at most kPartUnboundedMean on average, where the
-// merge's time per viewer covers a long one: 20,000 x 10 286 / 888, and 8,000 viewers of 4 with
-// one of 500,000 466 / 466.
-constexpr int64_t kPartUnboundedTotal = (int64_t)1 << 19;
-constexpr int64_t kPartUnboundedMean = 64;
-
 // Two launches, the first of which puts long viewers' records in order of their parts: taken where
 // viewers have at most kSplitMax records (256 parts, of whose number two go to the ends) and by the
 // caller's bound (their mean, without one) may have more than kSplitMin. 1 x 160,000 27 / 84,
@@ -71,6 +61,19 @@ constexpr int64_t kPartUnboundedMean = 64;
 constexpr int32_t kPartSplit = 640;              // records per part
 constexpr int64_t kSplitMin = 8192;
 constexpr int64_t kSplitMax = (256 - 2) * (int64_t)kPartSplit;
+
+// A call without a bound on its viewers (max_keys = 0) may hold one viewer of nearly all its records.
+// One launch would then read that list once per part: 1,000 viewers of 20 records and one of 130,000
+// 90 / 90, of 300,000 158 / 116, of 500,000 257 / 126. Past the partition's limit with `total` for the
+// longest list, and up to kSplitTotal records, such a call takes the two launches, which read each list
+// twice however long; a viewer of more than kSplitMax records is cut into 256 longer parts. One of
+// 165,000 among the 1,000 39 / 97, of 300,000 64 / 116, of 500,000 80 / 126 (62-bit keys, 128-byte rows
+// 126 / 172), alone 65 / 108; 64 x 5,000 30 / 56 (25 with a bound, in one launch), 64 viewers of 100 to
+// 30,000 32 / 92, 300 x 1,700 18 / 56. The same for a bound above kSplitMax. Lists of at most kTinyMean
+// records on average keep the one launch, where the merge's time per viewer covers a long one: 20,000 x
+// 10 286 / 888, 8,000 viewers of 4 with one of 500,000 466 / 466.
+constexpr int64_t kSplitTotal = (int64_t)1 << 19;
+constexpr int64_t kTinyMean = 64;
 
 // The method of a call of total records (1 to 2^32 - 1) in n_viewers viewers (at least 1), none
 // longer than max_keys if that is positive.
@@ -85,11 +88,10 @@ inline int32_t sort_choice(int64_t total, int64_t n_viewers, int64_t max_keys) {
         if ((max_keys > 0 ? limit : total / n_viewers) > kSplitMin && limit <= kSplitMax)
             return kSortSplit;
         const bool short_lists = total >= kSortRadixMinRecords && total < n_viewers * kPartMinMean;
-        if (!short_lists && (max_keys > 0 || total <= kPartUnboundedTotal)) {
-            const bool tiny = max_keys <= 0 && total <= n_viewers * kPartUnboundedMean;
-            if (tiny || limit <= (limit <= kPartLarge ? kPartMaxWorkWhole : kPartMaxWork) / total)
-                return kSortPart;
-        }
+        if (!short_lists && limit <= (limit <= kPartLarge ? kPartMaxWorkWhole : kPartMaxWork) / total)
+            return kSortPart;
+        if (total <= kSplitTotal)
+            return total <= n_viewers * kTinyMean ? kSortPart : kSortSplit;
     }
     return total >= kSortRadixMinRecords ? kSortRadix : kSortMerge;
 }

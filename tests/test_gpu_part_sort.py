@@ -292,13 +292,31 @@ def test_split_sizes(lead, kind):
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("n", [10_241, LONGEST - 1, LONGEST, LONGEST + 1])
 def test_split_range_of_lengths(n, kind):
-    """Around the shortest and the longest single viewer that takes two launches, and the bound from which
-    they are taken."""
-    want = SPLIT if n <= LONGEST else MERGE
-    _check([777, n, 5_000], _keys(kind, n + 5_777, 3), f"{kind}, longest {n}", want, max_keys=n)
-    _check([n], _keys(kind, n, 4), f"{kind}, one viewer of {n}", want)
+    """Around the shortest single viewer that takes two launches and the longest whose parts are of 640
+    records, and the bound from which they are taken."""
+    _check([777, n, 5_000], _keys(kind, n + 5_777, 3), f"{kind}, longest {n}", SPLIT, max_keys=n)
+    _check([n], _keys(kind, n, 4), f"{kind}, one viewer of {n}", SPLIT)
     _check([8_193, 5_000], _keys(kind, 13_193, 5), f"{kind}, bound 8,193", SPLIT, max_keys=8_193)
     _check([8_192, 5_000], _keys(kind, 13_192, 5), f"{kind}, bound 8,192", PART, max_keys=8_192)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("lead,n", [(0, 1 << 19), (777, 128 * CHUNK), (777, 128 * CHUNK + 1), (3_071, 165_000),
+                                    (500, 263_000)])
+def test_long_viewers_without_a_bound(lead, n, kind):
+    """Viewers of 256 parts that are longer than 640 records, some of them overlong, up to 172 chunks,
+    among short ones; the longest call that may take two launches without a bound, and one record more."""
+    sizes = [lead] + [n] + [70] * min(100, ((1 << 19) - lead - n) // 70)
+    _check(sizes, _keys(kind, sum(sizes), n), f"{n} {kind} after {lead}", SPLIT)
+    if n == 1 << 19:
+        _check([n, 1], _keys(kind, n + 1, n), f"{n} and 1 {kind}", MERGE)
+
+
+@pytest.mark.parametrize("kind", ["ids", "wide"])
+def test_several_long_viewers_without_a_bound(kind):
+    """Each cut into 256 parts of its own length; and ordinary lists of a call of that size."""
+    _check([170_000, 0, 180_001, 5, 163_841], _keys(kind, 513_847, 2), f"three long, {kind}", SPLIT)
+    _check([5_000] * 64, _keys(kind, 320_000, 2), f"64 x 5,000, {kind}", SPLIT)
 
 
 @pytest.mark.parametrize("dup", [1, 300, 3_000])
@@ -314,9 +332,9 @@ def test_split_keys_that_crowd(dup):
 
 
 @pytest.mark.parametrize("lead", [0, 777])
-@pytest.mark.parametrize("n", [33_333, 150_000])
+@pytest.mark.parametrize("n", [33_333, 150_000, 300_000])
 def test_split_part_that_the_sample_misjudged(n, lead):
-    keys = _misjudged(n, _parts(lead, n, SPLIT_PART), 12, WHOLE)
+    keys = _misjudged(n, min(_parts(lead, n, SPLIT_PART), 256), 12, WHOLE)
     _check([lead, n], torch.cat([_keys("ids", lead, 1), keys]), f"split, misjudged after {lead}", SPLIT,
            max_keys=n)
 
@@ -369,3 +387,11 @@ def test_split_malformed_offsets_stay_inside_the_buffers(off):
     written stays inside the call's buffers."""
     note(f"split sort: offsets {off}")
     _check_inside(off, 50_000, 50_000, SPLIT)
+
+
+@pytest.mark.parametrize("off", [[0, 400_000, 100_000, 500_000], [-5, 1 << 40, 3, 500_000],
+                                 [300_000, 200_000, 100_000, 0], [0, 400_000, 0, 400_000]])
+def test_split_malformed_offsets_of_long_viewers(off):
+    """The same with viewers of 256 longer parts, some of them overlong."""
+    note(f"split sort: offsets {off}")
+    _check_inside(off, 500_000, 0, SPLIT)
