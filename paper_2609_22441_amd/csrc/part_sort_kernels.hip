@@ -551,55 +551,59 @@ __device__ __forceinline__ void emit(const SH &sh, const Part &pt, uint64_t kmin
     });
 }
 
-// Where split_kernel left the records of the part: sh.adj[c] those in the chunks before chunk c,
-// sh.start[c] + i the place of the part's record i, if it is in chunk c. Returns their number, below
-// the number of records below the part (what every chunk holds of earlier parts). Entries are
-// clamped to their chunk, whatever malformed offsets made of them. Ends with a barrier.
 constexpr int kChunks = 256;                   // of one viewer, at most
 static_assert(kSplitTotal <= (int64_t)(kChunks - 2) * kChunk && kChunks <= kRadix, "four per lane");
 
 // Chunks that a lane looks at: two, or four for viewers of more than 128.
-__device__ __forceinline__ uint32_t chunks_per_lane(const Part &pt) {
+__device__ __forceinline__ int chunks_per_lane(const Part &pt) {
     return parts_of(pt.kb, pt.kb + pt.n, kChunk) > kChunks / 2 ? kChunks / 64 : kChunks / 128;
 }
 
+// By one wavefront, PER chunks per lane. (PER is a constant, so that all entries are read together.)
+template <int PER, typename SH>
+__device__ __forceinline__ void look_at_chunks(SH &sh, const Part &pt, const Split &sp) {
+    const int lane = thread_index() & 63;
+    const uint32_t C = parts_of(pt.kb, pt.kb + pt.n, kChunk);
+    uint32_t len[PER], at[PER], sum = 0, under = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint32_t q = PER * lane + j, c = min(q, C - 1);
+        const uint32_t c0 = part_begin(pt.n, c, C), cn = part_begin(pt.n, c + 1, C) - c0;
+        const uint16_t *row = sp.start + sp.row(pt.kb, c) * kRadix;
+        const uint32_t s = min((uint32_t)row[pt.g], cn);
+        const uint32_t e = pt.g + 1 < kRadix ? row[pt.g + 1] : cn;
+        at[j] = c0 + s;
+        len[j] = q < C ? max(s, min(e, cn)) - s : 0;
+        sum += len[j];
+        under += q < C ? s : 0;
+    }
+    const uint32_t end = wave_scan(sum);
+    uint32_t b = end - sum;
+    under = wave_scan(under);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        sh.adj[PER * lane + j] = b;
+        sh.start[PER * lane + j] = at[j] - b;            // modulo 2^32
+        b += len[j];
+    }
+    if (lane == 63) {
+        sh.run[0][0] = end;
+        sh.below[0] = under;
+    }
+}
+
+// Where split_kernel left the records of the part: sh.adj[c] those in the chunks before chunk c,
+// sh.start[c] + i the place of the part's record i, if it is in chunk c. Returns their number, below
+// the number of records below the part (what every chunk holds of earlier parts). Entries are
+// clamped to their chunk, whatever malformed offsets made of them. Ends with a barrier.
 template <typename SH>
 __device__ __forceinline__ uint32_t find_records(SH &sh, const Part &pt, const Split &sp,
                                                  uint32_t &below) {
     if (wave_index() == 0) {
-        const int lane = thread_index() & 63;
-        const uint32_t C = parts_of(pt.kb, pt.kb + pt.n, kChunk);
-        const int per = (int)chunks_per_lane(pt);
-        uint32_t len[kChunks / 64], at[kChunks / 64], sum = 0, under = 0;
-#pragma unroll
-        for (int j = 0; j < kChunks / 64; ++j) {
-            if (j < per) {                               // uniform
-                const uint32_t q = per * lane + j, c = min(q, C - 1);
-                const uint32_t c0 = part_begin(pt.n, c, C), cn = part_begin(pt.n, c + 1, C) - c0;
-                const uint16_t *row = sp.start + sp.row(pt.kb, c) * kRadix;
-                const uint32_t s = min((uint32_t)row[pt.g], cn);
-                const uint32_t e = pt.g + 1 < kRadix ? row[pt.g + 1] : cn;
-                at[j] = c0 + s;
-                len[j] = q < C ? max(s, min(e, cn)) - s : 0;
-                sum += len[j];
-                under += q < C ? s : 0;
-            }
-        }
-        const uint32_t end = wave_scan(sum);
-        uint32_t b = end - sum;
-        under = wave_scan(under);
-#pragma unroll
-        for (int j = 0; j < kChunks / 64; ++j) {
-            if (j < per) {
-                sh.adj[per * lane + j] = b;
-                sh.start[per * lane + j] = at[j] - b;    // modulo 2^32
-                b += len[j];
-            }
-        }
-        if (lane == 63) {
-            sh.run[0][0] = end;
-            sh.below[0] = under;
-        }
+        if (chunks_per_lane(pt) == kChunks / 128)        // uniform
+            look_at_chunks<kChunks / 128>(sh, pt, sp);
+        else
+            look_at_chunks<kChunks / 64>(sh, pt, sp);
     }
     lds_sync();
     below = sh.below[0];
