@@ -605,7 +605,16 @@ __device__ __forceinline__ void full_tiles(const JoinArgs &a, Sources<NL> *s_ptr
         const int64_t x0 = author_of<A32>(a, clamp64(c0, last_doc), at(0));
         x1 = author_of<A32>(a, clamp64(c1, last_doc), at(1));
         stage();
-        resolve(0, c0, x0, e0);
+        if ((tid & ~63) < rows(0)) {
+            resolve(0, c0, x0, e0);
+        } else {
+            // A wavefront without candidates searches nothing (2 viewers of 100 candidates and 60,000
+            // keys: 10.2 -> 9.7 us); the copy may read its rows all the same.
+            s_ptr[0][0][tid] = reinterpret_cast<uint64_t>(a.zero_row);
+#pragma unroll
+            for (int l = 0; l < NL; ++l)
+                s_ptr[0][1 + l][tid] = reinterpret_cast<uint64_t>(miss_row);
+        }
     }
     // Let the prologue loads land here (once per segment). Otherwise, where the loop entry and
     // the back edge meet, the compiler keeps the prologue's short distances and waits for the
