@@ -54,7 +54,7 @@ struct JoinArgs {
     int32_t fence_budget;        // fences staged per candidate of a segment (automatic stride)
     int32_t fence_least;         // fences that a segment of any size may have; set by launch_join
     int8_t *valid;               // valid mask of the padded layout's slots (n_max > 0)
-    bool wide;                   // rows or strides too long for the pipelined copy; set by launch_join
+    bool wide;                   // run-time widths: no pipelined copy; set by launch_join
     bool one_wave;               // automatic grid: one resident wave (long key lists)
     bool lds_auto;               // lds_keys chosen by the library (not by a tuning)
     bool balanced;               // CSR ranges weighted by an estimated cost per candidate

@@ -472,7 +472,7 @@ __device__ __forceinline__ void copy_tile_any(const JoinArgs &a, const Sources<N
 }
 
 // Copy the first n rows of a sub-tile of any widths and any stride: for rows longer than the
-// zero row, or strides past a buffer's offsets. A null source reads as zero bytes.
+// zero row, strides past a buffer's offsets, or plain_copy. A null source reads as zero bytes.
 template <int NL>
 __device__ __forceinline__ void copy_wide_rows(const JoinArgs &a, const Sources<NL> &s_ptr,
                                                int64_t t0, int n) {
@@ -757,7 +757,7 @@ __global__ __launch_bounds__(kBlock) void join_kernel(JoinArgs a) {
             continue;
         }
         if constexpr (DOC_CH == 0) {
-            // Rows or strides too long for the pipeline: one sub-tile after the other.
+            // Rows or strides that the pipeline does not take: one sub-tile after the other.
             stage();
             for (int64_t t0 = s0; t0 < s1; t0 += kBlock) {
                 const int n = (int)min<int64_t>(kBlock, s1 - t0);
@@ -915,7 +915,9 @@ hipError_t dispatch_widths(JoinArgs &a, int32_t wgs, int device, hipStream_t str
     const int d = a.doc_bytes >> 4, e = a.edge_bytes >> 4;
     // A sub-tile's output offsets fit a buffer's 32 bits, and absent rows the zero row.
     const bool far = a.out_stride > kMaxTileStride;
-    a.wide = far || a.doc_bytes > kZeroRowBytes || a.edge_bytes > kZeroRowBytes;
+    a.wide = far || a.doc_bytes > kZeroRowBytes || a.edge_bytes > kZeroRowBytes ||
+             plain_copy(a.n_max > 0 ? a.n_viewers * a.n_max : a.total_cand, a.out_stride,
+                        a.doc_bytes + L * (int64_t)a.edge_bytes);
     if (far) return launch_form<0, 0, L>(a, wgs, device, stream);
     if (d == 4 && e == 2) return launch_form<4, 2, L>(a, wgs, device, stream);
     if (d == 8 && e == 4) return launch_form<8, 4, L>(a, wgs, device, stream);

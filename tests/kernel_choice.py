@@ -24,6 +24,9 @@ extern "C" int apart(int64_t n_records, int64_t row_bytes) {
 extern "C" int64_t ranges(int64_t n, int64_t viewers, int64_t most) {
     return ccj::ranges_of_viewers(n, viewers, most);
 }
+extern "C" int plain(int64_t rows, int64_t stride, int64_t width) {
+    return ccj::plain_copy(rows, stride, width);
+}
 extern "C" int fences(int64_t total_keys, int64_t viewers, int long_lists) {
     return ccj::least_fences(total_keys, viewers, long_lists);
 }
@@ -41,6 +44,7 @@ def _shim():
     lib.choice.argtypes = [ctypes.c_int64] * 3
     lib.apart.argtypes = [ctypes.c_int64] * 2
     lib.ranges.argtypes, lib.ranges.restype = [ctypes.c_int64] * 3, ctypes.c_int64
+    lib.plain.argtypes = [ctypes.c_int64] * 3
     lib.fences.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
     return lib
 
@@ -61,3 +65,7 @@ def least_fences(viewers, keys) -> int:
 
 def ranges_of_viewers(n, viewers, most) -> int:
     return _shim().ranges(n, viewers, most)
+
+
+def plain_copy(rows, stride, width) -> bool:
+    return bool(_shim().plain(rows, stride, width))

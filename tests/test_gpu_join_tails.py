@@ -11,7 +11,7 @@ import oracle
 import paper_2609_22441_amd as P
 import workload as W
 from gpu_common import FILL, note
-from kernel_choice import least_fences
+from kernel_choice import plain_copy, least_fences
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -77,6 +77,15 @@ def test_ragged_viewers_with_a_stride(wd, we, L):
     """Segments of 0 to 700 candidates and rows inside a wider stride."""
     sizes = [0, 1, 700, 256, 3, 0, 257, 64, 511, 2, 90]
     _check(sizes, wd, we, L, 9, wd + L * we + 48, True, f"ragged, {wd}+{we} x{L}, stride +48")
+
+
+@pytest.mark.parametrize("L", [1, 2])
+@pytest.mark.parametrize("n", [60_000, 90_000])
+def test_short_rows_with_gaps_by_either_copy(n, L):
+    """Short rows with gaps, below and above the size of the output up to which they are copied without
+    the pipeline; one viewer's candidates end inside a sub-tile."""
+    assert plain_copy(n, 96, 16 + 16 * L) == (n == 60_000)
+    _check([n - 9_001, 9_001], 16, 16, L, 3, 96, L == 2, f"{n} rows at 96, x{L}")
 
 
 def test_stride_past_a_sub_tiles_offsets():

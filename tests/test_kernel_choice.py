@@ -2,7 +2,7 @@
 csrc/sort_choice.h, csrc/ingest_choice.h and csrc/join_choice.h)."""
 import pytest
 
-from kernel_choice import MERGE, PART, RADIX, RANK, SPLIT, choice, commit_apart, least_fences, ranges_of_viewers
+from kernel_choice import MERGE, PART, RADIX, RANK, SPLIT, plain_copy, choice, commit_apart, least_fences, ranges_of_viewers
 
 
 @pytest.mark.parametrize("sizes,max_keys,want", [
@@ -69,3 +69,11 @@ def test_ranges_of_small_launches_are_a_multiple_of_the_viewers(n, viewers, want
     40 ranges."""
     got = ranges_of_viewers(n, viewers, 256)
     assert got == want and got % viewers == 0 and got <= 256
+
+
+@pytest.mark.parametrize("rows,stride,width,want", [
+    (10_000, 32, 32, False), (10_000, 80, 32, True), (50_000, 80, 32, True), (200_000, 48, 32, False),
+    (10_000, 80, 64, False)])
+def test_small_outputs_of_short_rows_with_gaps_take_no_pipeline(rows, stride, width, want):
+    """10,000 rows of 32 bytes at 80: 5.7 us with it, 5.0 without."""
+    assert plain_copy(rows, stride, width) == want
