@@ -5,11 +5,11 @@
 // search-and-copy: no matrix cores, no arithmetic on the row payloads.
 //
 // Work decomposition
-//   * The flattened candidate array [0, total_cand) is cut into n_wg contiguous ranges: of
-//     per_wg candidates each, or, for CSR batches of up to kBalanceViewers viewers, of equal
-//     estimated cost (balanced_range). Hardware dispatches workgroup b to XCD b % 8, so the
-//     range index is (b % 8) * (n_wg / 8) + b / 8: each XCD walks one contiguous eighth of the
-//     candidates, which keeps a viewer's keys and edge rows in a single XCD's L2.
+//   * The flattened candidate array [0, total_cand) is cut into n_wg contiguous ranges (a few less
+//     in small batches): of per_wg candidates each, or, for CSR batches of up to kBalanceViewers
+//     viewers, of equal estimated cost (balanced_range). Hardware dispatches workgroup b to XCD
+//     b % 8, so the range index is (b % 8) * (n_wg / 8) + b / 8: each XCD walks one contiguous
+//     eighth of the candidates, which keeps a viewer's keys and edge rows in a single XCD's L2.
 //   * A range is split at viewer boundaries into segments. For each segment the workgroup
 //     stages every S-th key of the viewer ("fences") into LDS; S = 1 stages the whole list.
 //   * Sub-tiles of kBlock candidates: each thread resolves one candidate (position check,
@@ -643,7 +643,7 @@ __device__ __forceinline__ void full_tiles(const JoinArgs &a, Sources<NL> *s_ptr
 // wavefront after wavefront over the whole launch; a lane finds one block's viewer and size, so
 // the offsets of 64 blocks are read together. The chunks of a block's pad rows are written in
 // order. (A launch of its own with one thread per slot, row after row of 128 bytes per thread, took
-// 12.8 us after the join's 35.7 for 12 viewers of 41,003 slots, 57% of them pads; one launch 30.3.)
+// 12.8 us after the join's 35.7 for 12 viewers of 37,680 slots, 43% of them pads; one launch 30.3.)
 template <int NL>
 __device__ __forceinline__ void fill_pads(const JoinArgs &a) {
     const int lane = threadIdx.x & 63;
