@@ -25,9 +25,10 @@
 //
 // A part that the sample judged wrong by more than kCap / part (or that malformed offsets made
 // so) does not fit in LDS: its records are then sorted by the same digit passes in chunks,
-// through the two element arrays of the workspace, by the one workgroup. Slower, never wrong. (Parts
-// of split calls are sorted in pieces first, see overlong_part.) The sample has kPerPart records per part: a part of more than kCap / kPartLarge = 3.2 times its
-// share is a 2e-6 event in key orders that know nothing of the sample.
+// through the two element arrays of the workspace, by the one workgroup. Slower, never wrong.
+// (Parts of split calls are sorted in pieces first, see overlong_part.) The sample has kPerPart
+// records per part: a part of more than kCap / kPartLarge = 3.2 times its share is a 2e-6 event in
+// key orders that know nothing of the sample.
 #include "join_internal.h"
 #include "sort_choice.h"
 #include "sort_device.h"
